@@ -58,6 +58,7 @@ struct DomDev {
   double2* rec;
   float2* rec32;     // FP32 records (tile-local eta offsets over the tile radius, |v|^2, weights, b = w conj(v))
   float2* far32;     // FP32 far-tile sources [8-column block][64-node tile][field][node] (see far32_size)
+  double2* w1;       // weights of the two-sided one-column launch (null: none)
   double2* parts;    // partial sums [splits][wcols][N]
   double4* sb;       // bounds of the 64-node source tiles {cx, cy, r, 0}
   double4* sbf;      // bounds of the FP64 far-form source tiles (kFarTile nodes)
@@ -71,6 +72,7 @@ struct DomDev {
   int ncols;         // real columns of the domain
   int c0;            // first global column index
   int splits;        // source splits
+  int symslots;      // partial-sum slots of the two-sided one-column launch (0: none)
   int chunk;         // sources per split
   int c;             // +1 bounded, -1 unbounded
 };
@@ -94,6 +96,17 @@ hipError_t launch_pairs(const DomDev* doms, const int4* items, int nitems, int w
                         bool mixed, bool ext, const int* active, hipStream_t st);
 // resident workgroups per CU of the pair-kernel variant (width columns, tpt, mixed)
 int pairs_blocks_per_cu(int width, int tpt, bool mixed);
+
+// One-column sums of one domain with every unordered pair evaluated once
+// (csrc/pairs_sym.hip): T nodes per lane (4 or 8), nb blocks of 256 T nodes, F
+// forward slots, H = nb/2 backward slots, P (at most 3 T) parts of a block's own
+// pairs, slots = F + H + P + 2.
+struct SymPlan {
+  int T = 4, nb = 0, F = 0, H = 0, P = 0;
+  int slots() const { return F + H + P + 2; }
+};
+hipError_t launch_pairs_sym(const DomDev* doms, const int4* items, int nitems, const SymPlan& P, const int* active,
+                            hipStream_t st);
 
 // bounding circles of the tiles of `tile` nodes of every domain (source tiles
 // of 64 nodes into sb, target tiles into tb)

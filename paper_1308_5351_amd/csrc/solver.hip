@@ -260,6 +260,13 @@ struct Batch {
   };
   std::vector<Circ> circ;
   bool circ_built = false;
+  // two-sided one-column sums (one domain, FP64), see plan_sym
+  struct Sym {
+    bool on = false;
+    SymPlan plan;
+    int4* items = nullptr;
+    int cnt = 0;
+  } sym;
   // treecode far field (one domain, FP64), see build_tree
   struct Tree {
     bool on = false;
@@ -352,6 +359,68 @@ void plan_single(gnk_ctx* c, int64_t N, int align, int width, bool mixed, int* t
   plan_pairs(c, N, N, align, width, mixed, tpt, chunk, splits);
 }
 
+// Two-sided one-column sums (csrc/pairs_sym.hip): the plan of N nodes and its
+// work items, costliest first; false where the one-sided kernel runs.
+//   * From 8000 nodes on: below, its shortest item (256 T nodes against one chunk,
+//     about 20 us with four nodes per lane) outweighs the saved work (launch us,
+//     two-sided / one-sided: 29.6/28.7 at N = 6600, 33.9/36.5 at 8192, 52/68 at
+//     12240, 96/126 at 17408, 318/407 at 33792, 1415/1695 at 73729).
+//   * Up to 600000 nodes: the backward slots take N/4096 partial sums per node
+//     (1.5 GB there; 2.6 times that at 1e6).
+//   * Eight nodes per lane from 40000 on (537/550 us at N = 45000, 1415/1450 at
+//     73729), four below, whose items are half as long (109.5/100.8 at 17408).
+//   * Not in the fixed scratch of gnk_cauchy_sum_noalloc, nor where its partial
+//     sums would pass those of the one-sided launch under a workspace cap, nor
+//     with the launch-shape overrides, which are the one-sided kernel's.
+// A block's stream is cut into F pieces, the same fractions for every block:
+// each layer of nb pieces takes 1/(2 resident workgroups) of the work left per
+// workgroup, but at least two chunks (every piece is a slot that the consumer
+// reads; at N = 17408 a piece is two or three chunks).
+constexpr int64_t kSymMinN = 8000, kSymMaxN = 600000, kSymWideN = 40000;
+bool plan_sym(gnk_ctx* c, int64_t N, int64_t part_cols, SymPlan* P, std::vector<int4>* items) {
+  if (N < kSymMinN || N > kSymMaxN || c->arena || getenv("GNK_CAUCHY_TPT") || getenv("GNK_CAUCHY_SPLITS")) return false;
+  const int T = N >= kSymWideN ? 8 : 4;
+  const int nb = (int)((N + 256 * T - 1) / (256 * T));
+  const int nc = (int)((N + 63) / 64), per = 4 * T;
+  auto len = [&](int I) {   // chunks that block I streams
+    int n = 0;
+    for (int d = 1; d <= nb / 2; ++d) {
+      if (2 * d == nb && I >= nb / 2) break;
+      const int J = (I + d) % nb;
+      n += std::min(nc, (J + 1) * per) - J * per;
+    }
+    return n;
+  };
+  const double resident = (double)c->num_cu * (T == 8 ? 2 : 3);
+  const double shortest = 2.0 / len(0);
+  std::vector<double> cut{0.0};
+  for (double left = 1.0; left > 0.0;) {
+    double piece = std::max(shortest, left * nb / (2.0 * resident));
+    if (left < 1.5 * piece) piece = left;
+    left -= piece;
+    if (left < 1e-9) left = 0.0;
+    cut.push_back(1.0 - left);
+  }
+  P->T = T;
+  P->nb = nb;
+  P->H = nb / 2;
+  P->F = (int)cut.size() - 1;
+  P->P = 3 * T;
+  if (c->ws_limit && P->slots() >= part_cols) return false;
+  std::vector<std::pair<int, int4>> v;   // chunks, item
+  for (int I = 0; I < nb; ++I) {
+    const int n = len(I);
+    for (int f = 0; f < P->F; ++f) {
+      const int a = (int)std::lround(cut[f] * n), b = (int)std::lround(cut[f + 1] * n);
+      v.push_back({b - a, make_int4(I, a, b, f)});
+    }
+    for (int p = 0; p < P->P; ++p) v.push_back({1, make_int4(I, p, P->P, -1)});
+  }
+  std::stable_sort(v.begin(), v.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  for (auto& q : v) items->push_back(q.second);
+  return true;
+}
+
 // Builds the batch tables and workspace. doms: host array; ncols: columns per
 // domain; col_off: flat offset of column 0 of each domain (the columns of a
 // domain are contiguous, N_d apart).
@@ -392,6 +461,14 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
       B.shape.tpt = t;
       D.chunk = ch;
       D.splits = sp;
+      std::vector<int4> items;
+      if (plan_sym(c, D.N, (int64_t)sp * (ncols[d] + 1), &B.sym.plan, &items)) {
+        B.sym.on = true;
+        B.sym.cnt = (int)items.size();
+        B.sym.items = upload(c, "b_sym", items);
+        D.symslots = B.sym.plan.slots();
+        D.w1 = ws<double2>(c, "b_w1", D.N);
+      }
     } else {
       int64_t ch = std::max(align, shape.chunk > 0 ? shape.chunk : 2048);
       ch = (ch + align - 1) / align * align;
@@ -406,7 +483,7 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
     rec_total += (int64_t)D.N * rec_stride(D.ncols + 1);   // head, w.., b.. with a lead column
     rec32_total += (int64_t)D.N * rec32_stride(D.ncols + 1);
     far32_total += far32_size(D.N, D.ncols + 1);
-    part_total += (int64_t)D.splits * (D.ncols + 1) * D.N;
+    part_total += std::max<int64_t>((int64_t)D.splits * (D.ncols + 1), D.symslots) * D.N;
     sb_total += (D.N + 63) / 64;
     tb_total += (D.N + 63) / 64;
     sbf_total += (D.N + kFarTile - 1) / kFarTile;
@@ -452,7 +529,7 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
     orc += (int64_t)D.N * rec_stride(D.ncols + 1);
     orc32 += (int64_t)D.N * rec32_stride(D.ncols + 1);
     ofar += far32_size(D.N, D.ncols + 1);
-    op += (int64_t)D.splits * (D.ncols + 1) * D.N;
+    op += std::max<int64_t>((int64_t)D.splits * (D.ncols + 1), D.symslots) * D.N;
     osb += (D.N + 63) / 64;
     otb += (D.N + 63) / 64;
     osbf += (D.N + kFarTile - 1) / kFarTile;
@@ -790,6 +867,9 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   T.seg = upload(c, "t_seg", seg);
   D.splits = S;
   D.chunk = N;
+  B.sym.on = false;
+  D.symslots = 0;
+  D.w1 = nullptr;
   D.parts = ws<double2>(c, "t_parts", (size_t)S * (D.ncols + 1) * NT);
   B.d_dom = upload(c, "b_dom", B.dom);
   T.on = true;
@@ -831,6 +911,11 @@ int64_t records32_threads(const Batch& B, int p) {
   return t;
 }
 
+// Whether the sums of pattern p come from the two-sided one-column launch.
+bool use_sym(const Batch& B, int p, bool mixed) {
+  return B.sym.on && !B.tree.on && !mixed && kLead[p] + kData[p] * B.dom[0].ncols == 1;
+}
+
 // All Cauchy sums of a pattern for the batch (one launch per column-group width).
 void pairs(gnk_ctx* c, Batch& B, int p, bool mixed, const int* active) {
   if (B.tree.on && !mixed) {
@@ -847,8 +932,10 @@ void pairs(gnk_ctx* c, Batch& B, int p, bool mixed, const int* active) {
                           S.pairs1 > 0 && S.pairs1 == S.pair_cols};
     HIPCHK(c, hipEventRecord(pr.a, c->stream));
   }
+  const bool sym = use_sym(B, p, mixed);
+  if (sym) HIPCHK(c, launch_pairs_sym(B.d_dom, B.sym.items, B.sym.cnt, B.sym.plan, active, c->stream));
   for (int k = 0; k < 4; ++k) {
-    if (!S.cnt[k]) continue;
+    if (sym || !S.cnt[k]) continue;
     HIPCHK(c, launch_pairs(B.d_dom, S.d[k], S.cnt[k], kWidths[k], B.shape.tpt, kLead[p], kData[p], mixed,
                            B.dom[0].tz != nullptr, active, c->stream));
   }
@@ -957,7 +1044,7 @@ void setup_diag(gnk_ctx* c, Batch& B) {
   k_lead_records<<<node_grid(B), kT, 0, c->stream>>>(B.d_dom, C_RHO);
   LAUNCHCHK(c);
   pairs(c, B, P_LEAD, false, nullptr);
-  k_diag_fbie<<<node_grid(B), kT, 0, c->stream>>>(B.d_dom, 1, 0);
+  k_diag_fbie<<<node_grid(B), kT, 0, c->stream>>>(B.d_dom, 1, 0, use_sym(B, P_LEAD, false));
   LAUNCHCHK(c);
 }
 
@@ -966,7 +1053,7 @@ void setup_evec(gnk_ctx* c, Batch& B) {
   k_lead_records<<<node_grid(B), kT, 0, c->stream>>>(B.d_dom, C_ETAP);
   LAUNCHCHK(c);
   pairs(c, B, P_LEAD, false, nullptr);
-  k_evec<<<node_grid(B), kT, 0, c->stream>>>(B.d_dom);
+  k_evec<<<node_grid(B), kT, 0, c->stream>>>(B.d_dom, use_sym(B, P_LEAD, false));
   LAUNCHCHK(c);
 }
 
@@ -1035,7 +1122,7 @@ void apply_op(gnk_ctx* c, Batch& B, int op, const double* x, double* y, const Ap
     pairs(c, B, P_GM, a.mixed, a.active);
   }
   k_epilogue<<<col_grid(B), kT, 0, c->stream>>>(B.d_dom, B.d_col, x, f.cout, f.dsel, f.a0, f.dsign, f.cI, f.cR, mean,
-                                                M, a.active, 0, y);
+                                                M, a.active, 0, use_sym(B, P_GM, a.mixed), y);
   LAUNCHCHK(c);
   if (op == GNK_OP_FC || op == GNK_OP_FC_T) circulant(c, B, x, y, op == GNK_OP_FC ? 1.0 : -1.0);
 }
@@ -1181,8 +1268,13 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
     if (odd) sl.step = step_odd;
     int* const next = odd ? st.step : step_odd;
     pairs(c, B, P_GM, use_mixed, st.active);
-    k_epilogue_dots<<<gv, kT, 0, c->stream>>>(B.d_dom, B.d_col, V, T, form.cout, form.dsel, form.a0, form.dsign,
-                                              form.cI, form.cR, mpart, S, st.active, sl.step, per_blk, P1, ldp);
+    const bool sym = use_sym(B, P_GM, use_mixed);
+    // the many slots of two-sided sums shared by four groups of threads (at N =
+    // 12240 the adjoint solve took 1.65 ms against 1.79 with one)
+    const int epi = sym ? kT * kEpiGroups : kT;
+    k_epilogue_dots<<<gv, epi, 0, c->stream>>>(B.d_dom, B.d_col, V, T, form.cout, form.dsel, form.a0, form.dsign,
+                                              form.cI, form.cR, mpart, S, st.active, sl.step, per_blk,
+                                              sym, P1, ldp);
     LAUNCHCHK(c);
     k_gs_update<<<gv, kT, 0, c->stream>>>(B.d_dom, B.d_col, V, T, per_blk, P1, P2, ldp, sl);
     LAUNCHCHK(c);
@@ -1221,6 +1313,8 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
     for (int q = 0; q < 4; ++q) { pt(IS.d[q]); u((uint64_t)IS.cnt[q]); }
     u((uint64_t)B.shape.tpt); pt(B.d_dom); pt(B.d_col); u((uint64_t)B.ndom); u((uint64_t)B.maxN);
     u((uint64_t)(B.dom[0].tz != nullptr));
+    pt(B.sym.items); u((uint64_t)B.sym.cnt); u((uint64_t)B.sym.on);
+    u((uint64_t)B.sym.plan.nb); u((uint64_t)B.sym.plan.F); u((uint64_t)B.sym.plan.P);
     u((uint64_t)records32_threads(B, use_mixed ? P_GM_MIXED : P_GM));
     for (const void* q : {(const void*)st.bnorm, (const void*)st.true_relres, (const void*)st.relres,
                           (const void*)st.invbeta, (const void*)st.H, (const void*)st.cs, (const void*)st.sn,
@@ -1610,12 +1704,12 @@ GmresOut fbie_batch(gnk_ctx* c, Batch& B, const double* gam, const gnk_opts& o, 
       B.d_dom, B.d_col, C_RHO, gam, nullptr, 1, nullptr, B.maxm1);
   LAUNCHCHK(c);
   pairs(c, B, P_SETUP, false, nullptr);
-  k_diag_fbie<<<node_grid(B), kT, 0, c->stream>>>(B.d_dom, 1, 1);
+  k_diag_fbie<<<node_grid(B), kT, 0, c->stream>>>(B.d_dom, 1, 1, 0);
   LAUNCHCHK(c);
   // b = -y = -(D - diag(D1) + Lhat) gamma
   double* b = ws<double>(c, "rhs", T);
   k_epilogue<<<col_grid(B), kT, 0, c->stream>>>(B.d_dom, B.d_col, gam, C_A, D_D, 0.0, 1.0, 0.0, 1.0, nullptr, 0,
-                                                nullptr, 1, b);
+                                                nullptr, 1, 0, b);
   LAUNCHCHK(c);
   circulant(c, B, gam, b, -1.0);
   // f_B(gamma) from the same sums, for h; without singularity subtraction the
@@ -1627,10 +1721,10 @@ GmresOut fbie_batch(gnk_ctx* c, Batch& B, const double* gam, const gnk_opts& o, 
     fbg = ws<double>(c, "fbg", T);
     if (unsub)
       k_epilogue<<<col_grid(B), kT, 0, c->stream>>>(B.d_dom, B.d_col, gam, C_A, D_BU, 1.0, -1.0, 1.0, 0.0, nullptr,
-                                                    0, nullptr, 1, fbg);
+                                                    0, nullptr, 1, 0, fbg);
     else
       k_epilogue<<<col_grid(B), kT, 0, c->stream>>>(B.d_dom, B.d_col, gam, C_A, D_B, 2.0, 1.0, 1.0, 0.0, nullptr, 0,
-                                                    nullptr, 1, fbg);
+                                                    nullptr, 1, 0, fbg);
     LAUNCHCHK(c);
   }
   validate_finish(c);
@@ -1849,7 +1943,8 @@ void cauchy_sum(gnk_ctx* c, int64_t N, const void* eta, const void* w, int nrhs,
   k_pack_records<<<nblocks(N), kT, 0, c->stream>>>(B.d_dom, static_cast<const double2*>(w), nrhs);
   LAUNCHCHK(c);
   pairs(c, B, P_GM, false, nullptr);
-  k_reduce_parts<<<dim3(nblocks(N), (unsigned)nrhs), kT, 0, c->stream>>>(B.d_dom, static_cast<double2*>(S));
+  k_reduce_parts<<<dim3(nblocks(N), (unsigned)nrhs), kT, 0, c->stream>>>(B.d_dom, use_sym(B, P_GM, false),
+                                                                         static_cast<double2*>(S));
   LAUNCHCHK(c);
   HIPCHK(c, hipStreamSynchronize(c->stream));
 }
@@ -2118,7 +2213,7 @@ gnk_status gnk_cauchy_sum_tree(gnk_ctx* c, int64_t N, const void* eta, const voi
     k_pack_records<<<nblocks(N), kT, 0, c->stream>>>(B.d_dom, static_cast<const double2*>(w), nrhs);
     LAUNCHCHK(c);
     pairs(c, B, P_GM, false, nullptr);
-    k_reduce_parts<<<dim3(nblocks(N), (unsigned)nrhs), kT, 0, c->stream>>>(B.d_dom, static_cast<double2*>(S));
+    k_reduce_parts<<<dim3(nblocks(N), (unsigned)nrhs), kT, 0, c->stream>>>(B.d_dom, 0, static_cast<double2*>(S));
     LAUNCHCHK(c);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return GNK_OK;

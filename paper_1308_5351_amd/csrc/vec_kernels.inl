@@ -128,21 +128,24 @@ __global__ void k_rho(const DomDev* __restrict__ doms) {
 }
 
 // sum over the splits of weight column q (of wcols) of a domain's partial
-// sums, added in split order; the loads go out eight at a time
-__device__ __forceinline__ double2 reduce_parts(const DomDev& D, int wcols, int q, int i) {
-  constexpr int kG = 8;
+// sums (those with index = g0 mod gstep), added in split order; the loads go out
+// sixteen at a time. sym: the sums come from the two-sided one-column launch
+// (its slots in place of the splits)
+__device__ __forceinline__ double2 reduce_parts(const DomDev& D, int wcols, int q, int i, int sym, int g0 = 0,
+                                                int gstep = 1) {
+  constexpr int kG = 16;
   const gptr<const double2> p = (gptr<const double2>)D.parts + (size_t)q * D.N + i;
   const size_t gs = (size_t)wcols * D.N;
-  const int splits = D.splits;
+  const int splits = sym ? D.symslots : D.splits;
   double2 s = make_double2(0.0, 0.0);
-  for (int g = 0; g < splits; g += kG) {
+  for (int g = g0; g < splits; g += kG * gstep) {
     double2 v[kG];
 #pragma unroll
     for (int k = 0; k < kG; ++k)
-      if (g + k < splits) v[k] = p[(size_t)(g + k) * gs];
+      if (g + k * gstep < splits) v[k] = p[(size_t)(g + k * gstep) * gs];
 #pragma unroll
     for (int k = 0; k < kG; ++k)
-      if (g + k < splits) {
+      if (g + k * gstep < splits) {
         s.x += v[k].x;
         s.y += v[k].y;
       }
@@ -153,12 +156,12 @@ __device__ __forceinline__ double2 reduce_parts(const DomDev& D, int wcols, int 
 // From S = E(eta'/A) in weight column 0 (wcols columns):
 //   dB = diag(B1) = -(2/n) Im(A S),  dD = diag(D1) = -(2/n) Re(A S)
 // (eqs. (e:(I-B)x), (e:hD-bt) with x = 1)
-__global__ void k_diag_fbie(const DomDev* __restrict__ doms, int lead, int data) {
+__global__ void k_diag_fbie(const DomDev* __restrict__ doms, int lead, int data, int sym) {
   const DomDev& D = doms[blockIdx.y];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= D.N) return;
   const int wcols = lead + data * D.ncols;
-  const double2 s = reduce_parts(D, wcols, 0, i);
+  const double2 s = reduce_parts(D, wcols, 0, i, sym);
   const double2 as = cmul(D.A[i], s);
   const double two_n = 2.0 / (double)D.n;
   D.dB[i] = -two_n * as.y;
@@ -180,11 +183,11 @@ __global__ void k_ndiag(const DomDev* __restrict__ doms) {
 
 // From S = E eta' (weight column 0 of wcols = 1):
 //   e = 1 - c - (2/n) Im(S) + (2/n) Im(eta''/eta' - A'/A)   (eq. (e:bve))
-__global__ void k_evec(const DomDev* __restrict__ doms) {
+__global__ void k_evec(const DomDev* __restrict__ doms, int sym) {
   const DomDev& D = doms[blockIdx.y];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= D.N) return;
-  const double2 s = reduce_parts(D, 1, 0, i);
+  const double2 s = reduce_parts(D, 1, 0, i, sym);
   const double2 p = D.etap[i], pp = D.etapp[i], a = D.A[i], ap = D.Ap[i];
   const double dp = p.x * p.x + p.y * p.y, da = a.x * a.x + a.y * a.y;
   const double im1 = (pp.y * p.x - pp.x * p.y) / dp;   // Im(eta''/eta')
@@ -220,9 +223,14 @@ __global__ __launch_bounds__(kT) void k_weights(const DomDev* __restrict__ doms,
     const int j = k * D.n + p;
     const double v = xr[p];
     const double2 cf = coef(D, csel, j);
+    const double2 w = make_double2(cf.x * v, cf.y * v);
+    acc += v;
+    if (D.w1 && wcols == 1) {
+      D.w1[j] = w;
+      continue;
+    }
     const double2 ep = eta_rel(D, j);
     double2* rj = D.rec + (size_t)j * stride;
-    const double2 w = make_double2(cf.x * v, cf.y * v);
     rj[kRecHead + lead + C.r] = w;
     rj[kRecHead + wcols + lead + C.r] = cmul_conj(w, ep);
     if (C.r == 0) {
@@ -232,7 +240,6 @@ __global__ __launch_bounds__(kT) void k_weights(const DomDev* __restrict__ doms,
         rj[kRecHead + wcols] = cmul_conj(cf, ep);
       }
     }
-    acc += v;
   }
   if (mean) {
     const double t = block_sum(acc, sh);
@@ -244,10 +251,14 @@ __global__ __launch_bounds__(kT) void k_weights(const DomDev* __restrict__ doms,
 // (wcols = ncols): w = C_j q and w conj(eta'_j); with `head`, the node's head too.
 __device__ __forceinline__ void stage_weight(const DomDev& D, int csel, int r, int j, double q, bool head) {
   const int wcols = D.ncols;
-  const double2 ep = eta_rel(D, j);
   const double2 cf = coef(D, csel, j);
-  double2* rj = D.rec + (size_t)j * rec_stride(wcols);
   const double2 w = make_double2(cf.x * q, cf.y * q);
+  if (D.w1 && wcols == 1) {
+    D.w1[j] = w;
+    if (!D.rec32) return;   // mixed products take the records
+  }
+  const double2 ep = eta_rel(D, j);
+  double2* rj = D.rec + (size_t)j * rec_stride(wcols);
   rj[kRecHead + r] = w;
   rj[kRecHead + wcols + r] = cmul_conj(w, ep);
   if (head) record_head(rj, D.eta[j], ep);
@@ -274,8 +285,12 @@ __global__ void k_lead_records(const DomDev* __restrict__ doms, int csel) {
   const DomDev& D = doms[blockIdx.y];
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= D.N) return;
-  const double2 ep = eta_rel(D, j);
   const double2 cf = coef(D, csel, j);
+  if (D.w1) {
+    D.w1[j] = cf;
+    return;
+  }
+  const double2 ep = eta_rel(D, j);
   double2* rj = D.rec + (size_t)j * rec_stride(1);
   record_head(rj, D.eta[j], ep);
   rj[kRecHead] = cf;
@@ -287,6 +302,10 @@ __global__ void k_pack_records(const DomDev* __restrict__ doms, const double2* _
   const DomDev& D = doms[0];
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= D.N) return;
+  if (D.w1 && ncols == 1) {
+    D.w1[j] = w[j];
+    return;
+  }
   const double2 ep = eta_rel(D, j);
   double2* rj = D.rec + (size_t)j * rec_stride(ncols);
   record_head(rj, D.eta[j], ep);
@@ -472,12 +491,12 @@ __global__ void k_gather_points(const double2* __restrict__ z, const int* __rest
 }
 
 // S[r*N + i] = sum over the splits of column r (one domain, no lead column)
-__global__ void k_reduce_parts(const DomDev* __restrict__ doms, double2* __restrict__ S) {
+__global__ void k_reduce_parts(const DomDev* __restrict__ doms, int sym, double2* __restrict__ S) {
   const DomDev& D = doms[0];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int r = blockIdx.y;
   if (i >= D.N) return;
-  S[(size_t)r * D.N + i] = reduce_parts(D, D.ncols, r, i);
+  S[(size_t)r * D.N + i] = reduce_parts(D, D.ncols, r, i, sym);
 }
 
 // Operator epilogue for column c (grid (blocks over max N, ncol)), S from
@@ -486,14 +505,14 @@ __global__ void k_reduce_parts(const DomDev* __restrict__ doms, double2* __restr
 __global__ void k_epilogue(const DomDev* __restrict__ doms, const ColDev* __restrict__ cols,
                            const double* __restrict__ x, int csel_out, int dsel, double a0, double dsign, double cI,
                            double cR, const double* __restrict__ mean, int M, const int* __restrict__ active,
-                           int lead, double* __restrict__ y) {
+                           int lead, int sym, double* __restrict__ y) {
   const int c = blockIdx.y;
   const ColDev C = cols[c];
   const DomDev& D = doms[C.d];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= D.N) return;
   if (active && !active[c]) return;
-  const double2 s = reduce_parts(D, lead + D.ncols, lead + C.r, i);
+  const double2 s = reduce_parts(D, lead + D.ncols, lead + C.r, i, sym);
   const double2 cs = cmul(coef(D, csel_out, i), s);
   const double two_n = 2.0 / (double)D.n;
   const double xv = x[C.off + i];
@@ -600,14 +619,16 @@ __global__ __launch_bounds__(kT) void k_stage(const DomDev* __restrict__ doms, c
 
 // w = V_{l+1} = op(V_l) on the block's chunk from the Cauchy sums of the last
 // pair launch, then the chunk's dots of w with V_0..V_l.
-__global__ __launch_bounds__(kT) void k_epilogue_dots(const DomDev* __restrict__ doms,
+constexpr int kEpiGroups = 4;   // at most this many groups of kT threads
+__global__ __launch_bounds__(kT * kEpiGroups) void k_epilogue_dots(const DomDev* __restrict__ doms,
                                                       const ColDev* __restrict__ cols, double* __restrict__ V,
                                                       int64_t T, int csel_out, int dsel, double a0, double dsign,
                                                       double cI, double cR, const double* __restrict__ mpart, int S,
                                                       const int* __restrict__ active, const int* __restrict__ step,
-                                                      int per_blk, double* __restrict__ partial, int ldp) {
+                                                      int per_blk, int sym, double* __restrict__ partial, int ldp) {
   __shared__ double sw[kMaxChunk];
   __shared__ double sm[kMaxMeanSlots];
+  __shared__ double2 sg[kEpiGroups - 1][kT];
   const int c = blockIdx.y, blk = blockIdx.x, nblk = gridDim.x;
   if (!active[c]) return;
   const int l = *step;
@@ -626,15 +647,32 @@ __global__ __launch_bounds__(kT) void k_epilogue_dots(const DomDev* __restrict__
   if (mpart) chunk_means(mpart, S, c, nblk, per_blk, i0, i1, D.n, sm);
   const int k0 = i0 / D.n;
   const double two_n = 2.0 / (double)D.n;
-  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-    const double2 s = reduce_parts(D, D.ncols, C.r, i);
-    const double2 cs = cmul(coef(D, csel_out, i), s);
-    const double xv = xl[C.off + i];
-    double v = a0 * xv + two_n * (cI * cs.y + cR * cs.x);
-    if (dsel != D_NONE) v += dsign * diagv(D, dsel, i) * xv;
-    if (mpart) v += sm[i / D.n - k0];
-    w[C.off + i] = v;
-    sw[i - i0] = v;
+  // the block's blockDim / kT groups of kT threads share the partial sums of
+  // kT entries at a time; the first group adds up the groups' sums in order
+  const int grp = threadIdx.x / kT, ng = blockDim.x / kT, t = threadIdx.x - grp * kT;
+  for (int ib = i0; ib < i1; ib += kT) {
+    const int i = ib + t;
+    double2 s = make_double2(0.0, 0.0);
+    if (i < i1) s = reduce_parts(D, D.ncols, C.r, i, sym, grp, ng);
+    if (ng > 1) {
+      if (grp > 0) sg[grp - 1][t] = s;
+      __syncthreads();
+      if (grp == 0)
+        for (int g = 1; g < ng; ++g) {
+          s.x += sg[g - 1][t].x;
+          s.y += sg[g - 1][t].y;
+        }
+    }
+    if (grp == 0 && i < i1) {
+      const double2 cs = cmul(coef(D, csel_out, i), s);
+      const double xv = xl[C.off + i];
+      double v = a0 * xv + two_n * (cI * cs.y + cR * cs.x);
+      if (dsel != D_NONE) v += dsign * diagv(D, dsel, i) * xv;
+      if (mpart) v += sm[i / D.n - k0];
+      w[C.off + i] = v;
+      sw[i - i0] = v;
+    }
+    if (ng > 1) __syncthreads();
   }
   __syncthreads();
   chunk_dots(V, T, C.off, nvec, sw, i0, i1, out);
