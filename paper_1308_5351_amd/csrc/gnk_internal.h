@@ -126,6 +126,31 @@ hipError_t launch_box_bounds(const double2* eta, int N, const int* level_off, co
                              unsigned long long* rbits, double4* out, hipStream_t st);
 // bounding boxes {xmin, xmax, ymin, ymax} of the leaves (kLeaf consecutive nodes)
 hipError_t launch_leaf_boxes(const double2* eta, int N, int nleaf, double4* leafbox, hipStream_t st);
+// perm: the n points (pts, or the centres of boxes when pts is null) in the
+// order of their positions along a Hilbert curve; scratch of hilbert_scratch(n)
+// bytes
+size_t hilbert_scratch(int64_t n);
+hipError_t launch_hilbert_order(const double2* pts, const double4* boxes, int n, void* scratch, int* perm,
+                                hipStream_t st);
+hipError_t launch_invert(const int* perm, int n, int* inv, hipStream_t st);
+// Interaction lists of `tiles` target tiles (kt targets each, bounds tb) against
+// the boxes. Count: entries (then their offsets), cost and work (flops) of every
+// tile, and the list's length at *total (host-mapped). Fill: the list and each
+// tile's nseg + 1 bounds into it.
+struct TreeListArgs {
+  const double4* bounds;
+  const double4* tb;
+  const int* perm;
+  const int* level_off;   // host
+  const int* level_nb;    // host
+  double far_tol, theta;
+  int levels, p, N, NT, kt, tiles, nseg;
+  bool ext;
+};
+hipError_t launch_tree_count(const TreeListArgs& A, int64_t* count, int64_t* cost, double* work, int64_t* total,
+                             hipStream_t st);
+hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* count, int64_t* cost, int* list, int* seg,
+                            hipStream_t st);
 // multipole moments (p per box) of record weight field wo: leaves directly,
 // then every level from its children; level_off/level_nb: host arrays
 hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int N, const double4* bounds, const int* perm,

@@ -24,7 +24,6 @@
 #include <mutex>
 #include <sstream>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "gnk_internal.h"
@@ -643,45 +642,6 @@ int tree_terms(double far_tol) {
   return std::max(4, std::min(kTreeMaxP, p));
 }
 
-// perm: the indices of pts in the order of their positions along a Hilbert
-// curve (16 bits per coordinate over the points' bounding square; ties keep
-// index order). The curve has no jumps, so any run of consecutive indices
-// lies in a compact region of the plane.
-void hilbert_order(const std::vector<double2>& pts, std::vector<int>& perm) {
-  const size_t n = pts.size();
-  double x0 = 1e300, x1 = -1e300, y0 = 1e300, y1 = -1e300;
-  for (const auto& p : pts) {
-    x0 = std::min(x0, p.x), x1 = std::max(x1, p.x), y0 = std::min(y0, p.y), y1 = std::max(y1, p.y);
-  }
-  const double span = std::max(x1 - x0, y1 - y0);
-  const double sc = span > 0.0 ? 65535.0 / span : 0.0;
-  constexpr uint32_t side = 1u << 16;
-  auto distance = [](uint32_t x, uint32_t y) {   // position along the curve of cell (x, y)
-    uint64_t d = 0;
-    for (uint32_t h = side / 2; h > 0; h /= 2) {
-      const uint32_t rx = (x & h) ? 1u : 0u, ry = (y & h) ? 1u : 0u;
-      d += (uint64_t)h * h * ((3u * rx) ^ ry);
-      if (ry == 0) {   // rotate the quadrant
-        if (rx == 1) {
-          x = side - 1 - x;
-          y = side - 1 - y;
-        }
-        std::swap(x, y);
-      }
-    }
-    return d;
-  };
-  std::vector<uint64_t> code(n);
-  perm.resize(n);
-  for (size_t b = 0; b < n; ++b) {
-    const uint32_t qx = (uint32_t)std::min(65535.0, std::max(0.0, (pts[b].x - x0) * sc));
-    const uint32_t qy = (uint32_t)std::min(65535.0, std::max(0.0, (pts[b].y - y0) * sc));
-    code[b] = distance(qx, qy);
-    perm[b] = (int)b;
-  }
-  std::stable_sort(perm.begin(), perm.end(), [&](int a, int b) { return code[a] < code[b]; });
-}
-
 void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   if (B.ndom != 1 || B.mixed) {
     set_err(c, "the treecode takes one domain in FP64");
@@ -718,153 +678,51 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   const int nleaf = T.nb[0];
   double4* lbox = ws<double4>(c, "t_lbox", nleaf);
   HIPCHK(c, launch_leaf_boxes(D.eta, N, nleaf, lbox, c->stream));
-  std::vector<double4> hl((size_t)nleaf);
-  HIPCHK(c, hipMemcpyAsync(hl.data(), lbox, sizeof(double4) * nleaf, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  std::vector<double2> centre((size_t)nleaf);
-  for (int b = 0; b < nleaf; ++b) centre[b] = make_double2(0.5 * (hl[b].x + hl[b].y), 0.5 * (hl[b].z + hl[b].w));
-  std::vector<int> perm, invp((size_t)nleaf);
-  hilbert_order(centre, perm);
-  for (int s2 = 0; s2 < nleaf; ++s2) invp[perm[s2]] = s2;
-  T.perm = upload(c, "t_perm", perm);
-  T.invp = upload(c, "t_invp", invp);
+  int* perm = ws<int>(c, "t_perm", nleaf);
+  int* invp = ws<int>(c, "t_invp", nleaf);
+  // the sort's scratch: the moments' buffer, not yet in use, where it suffices
+  const size_t hb = hilbert_scratch(nleaf);
+  void* hs = hb <= sizeof(double2) * total * T.p ? (void*)T.mom : (void*)ws<char>(c, "t_hilbert", hb);
+  HIPCHK(c, launch_hilbert_order(nullptr, lbox, nleaf, hs, perm, c->stream));
+  HIPCHK(c, launch_invert(perm, nleaf, invp, c->stream));
+  T.perm = perm;
+  T.invp = invp;
   HIPCHK(c, launch_box_bounds(D.eta, N, T.off.data(), T.nb.data(), T.levels, lbox, T.perm, T.invp, bbox, rbits,
                               T.bounds, c->stream));
   T.tiles = (NT + kt - 1) / kt;
-  std::vector<double4> hb(total), ht(T.tiles);
-  HIPCHK(c, hipMemcpyAsync(hb.data(), T.bounds, sizeof(double4) * total, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipMemcpyAsync(ht.data(), D.tb, sizeof(double4) * T.tiles, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
   // about two rounds of resident workgroups
   const int64_t resident = (int64_t)c->num_cu * 5;
   int S = (int)std::max<int64_t>(1, std::min<int64_t>(16, (2 * resident + T.tiles - 1) / T.tiles));
   if (const char* e = getenv("GNK_TREE_SPLITS")) S = std::max(1, atoi(e));
   T.splits = S;
-  const double f2 = (1.0 + kTreeTheta) * (1.0 + kTreeTheta);
-  const double cnear = 13.0, cself = 16.0;
-  // rho^k <= far_tol exactly when rho <= far_tol^(1/k): the order p_e of a far
-  // entry is the least k >= 2 (at most p) whose threshold rho meets
-  std::vector<double> thr((size_t)T.p + 1, 0.0);
-  for (int k = 1; k <= T.p; ++k) thr[k] = std::pow(far_tol, 1.0 / k);
-  std::vector<int> seg((size_t)T.tiles * (4 * S + 1));
-  // the tiles' lists are independent: contiguous tile ranges on a few host
-  // threads, each list local to its thread, then joined in tile order
-  const int nth = std::max(1, std::min({16, (int)std::thread::hardware_concurrency(), (T.tiles + 63) / 64}));
-  std::vector<std::vector<int>> part((size_t)nth);
-  std::vector<char> failed((size_t)nth, 0);
-  std::vector<double> work((size_t)nth, 0.0);
-  auto lists_for = [&](int th) {
-    const int t0 = (int)((int64_t)T.tiles * th / nth), t1 = (int)((int64_t)T.tiles * (th + 1) / nth);
-    std::vector<int>& lst = part[(size_t)th];
-    try {
-      std::vector<int> ent;
-      std::vector<double> cost;
-      int stack[2 * 34][2];   // depth-first: at most one pending sibling per level
-      for (int t = t0; t < t1; ++t) {
-        ent.clear();
-        cost.clear();
-        const double4 tt = ht[t];
-        const int base = t * kt, top = T.levels - 1;
-        const double nt = (double)std::min(kt, NT - base);
-        int sp = 0;
-        for (int b = T.nb[top] - 1; b >= 0; --b) {
-          stack[sp][0] = top;
-          stack[sp][1] = b;
-          ++sp;
-        }
-        while (sp > 0) {
-          --sp;
-          const int l = stack[sp][0], b = stack[sp][1];
-          const double4 bb = hb[T.off[l] + b];
-          const double dx = tt.x - bb.x, dy = tt.y - bb.y, rr = tt.z + bb.z;
-          const double d2 = dx * dx + dy * dy;
-          if (d2 > f2 * rr * rr) {
-            const double rho = bb.z / (std::sqrt(d2) - tt.z);
-            int pe = 2;
-            while (pe < T.p && rho > thr[pe]) ++pe;
-            ent.push_back((pe << 24) | (T.off[l] + b));
-            cost.push_back(4.0 * pe + 24.0);
-            work[(size_t)th] += nt * (8.0 * pe + 8.0);
-          } else if (l == 0) {
-            for (int k = 0; k < kLeaf / 64; ++k) {
-              const int j0 = perm[b] * kLeaf + k * 64;
-              if (j0 >= N) break;
-              const int j1 = std::min(N, j0 + 64);
-              const int ov = ext ? 0 : std::max(0, std::min(j1, base + kt) - std::max(j0, base));
-              ent.push_back(~(j0 / 64));
-              cost.push_back(cnear * (j1 - j0 - ov) + cself * ov);
-              work[(size_t)th] += 16.0 * (nt * (j1 - j0) - ov);
-            }
-          } else {
-            // children pushed in reverse so that the list keeps slot order
-            if (2 * b + 1 < T.nb[l - 1]) {
-              stack[sp][0] = l - 1;
-              stack[sp][1] = 2 * b + 1;
-              ++sp;
-            }
-            stack[sp][0] = l - 1;
-            stack[sp][1] = 2 * b;
-            ++sp;
-          }
-        }
-        double tot = 0.0;
-        for (double x : cost) tot += x;
-        int* sg = seg.data() + (size_t)t * (4 * S + 1);
-        const int64_t start = (int64_t)lst.size();
-        sg[0] = (int)start;
-        double acc = 0.0;
-        size_t e = 0;
-        for (int k = 1; k < 4 * S; ++k) {
-          const double target = tot * k / (4.0 * S);
-          while (e < ent.size() && acc + 0.5 * cost[e] < target) acc += cost[e++];
-          sg[k] = (int)(start + (int64_t)e);
-        }
-        sg[4 * S] = (int)(start + (int64_t)ent.size());
-        if (lst.size() + ent.size() > (size_t)INT32_MAX / 2) {
-          failed[(size_t)th] = 1;   // reported after the join
-          return;
-        }
-        lst.insert(lst.end(), ent.begin(), ent.end());
-      }
-    } catch (...) {
-      failed[(size_t)th] = 1;
-    }
-  };
-  {
-    std::vector<std::thread> pool;
-    int spawned = 1;
-    try {
-      for (; spawned < nth; ++spawned) pool.emplace_back(lists_for, spawned);
-    } catch (...) {
-    }
-    for (int th = spawned; th < nth; ++th) lists_for(th);   // ranges that got no thread
-    lists_for(0);
-    for (auto& t : pool) t.join();
-  }
-  size_t len = 0;
-  bool cut = false;
-  T.flops = 0.0;
-  for (int th = 0; th < nth; ++th) {
-    T.flops += work[(size_t)th];
-    len += part[(size_t)th].size();
-    cut = cut || failed[(size_t)th];
-  }
-  if (cut || len > (size_t)INT32_MAX / 2) {
+  const TreeListArgs la{T.bounds, D.tb, T.perm, T.off.data(), T.nb.data(), far_tol, kTreeTheta,
+                        T.levels, T.p, N, NT, kt, T.tiles, 4 * S, ext};
+  int64_t* count = ws<int64_t>(c, "t_count", T.tiles);
+  int64_t* cost = ws<int64_t>(c, "t_cost", T.tiles);
+  double* work = ws<double>(c, "t_work", T.tiles);
+  volatile int64_t* len = reinterpret_cast<int64_t*>(hostio(c, sizeof(int64_t)));
+  HIPCHK(c, launch_tree_count(la, count, cost, work, hostio_dev(c, const_cast<int64_t*>(len)), c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  if (*len > INT32_MAX / 2) {
     set_err(c, "treecode interaction lists too long");
     throw Fail{GNK_ERR_OOM};
   }
-  std::vector<int> list;
-  list.reserve(len);
-  for (int th = 0; th < nth; ++th) {
-    const int t0 = (int)((int64_t)T.tiles * th / nth), t1 = (int)((int64_t)T.tiles * (th + 1) / nth);
-    const int off = (int)list.size();
-    for (int t = t0; t < t1; ++t)
-      for (int k = 0; k <= 4 * S; ++k) seg[(size_t)t * (4 * S + 1) + k] += off;
-    list.insert(list.end(), part[(size_t)th].begin(), part[(size_t)th].end());
+  T.list_len = (size_t)*len;
+  // an eighth more than needed when the buffer grows, so that the lists of other
+  // domains of the same size, a little longer, find room
+  const bool grow = !c->ws_limit && c->bufs["t_list"].bytes < T.list_len * sizeof(int);
+  int* list = ws<int>(c, "t_list", grow ? T.list_len + T.list_len / 8 : T.list_len);
+  int* seg = ws<int>(c, "t_seg", (size_t)T.tiles * (4 * S + 1));
+  HIPCHK(c, launch_tree_fill(la, count, cost, list, seg, c->stream));
+  T.list = list;
+  T.seg = seg;
+  T.flops = 0.0;
+  if (c->prof) {
+    std::vector<double> hw((size_t)T.tiles);
+    HIPCHK(c, hipMemcpyAsync(hw.data(), work, sizeof(double) * T.tiles, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    for (double x : hw) T.flops += x;
   }
-  T.list_len = list.size();
-  T.list = upload(c, "t_list", list);
-  T.seg = upload(c, "t_seg", seg);
   D.splits = S;
   D.chunk = N;
   B.sym.on = false;
@@ -2250,23 +2108,23 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
     DomDev& D = B.dom[0];
     D.tz = static_cast<const double2*>(z);
     D.Nt = (int)nz;
+    D.parts = ws<double2>(c, "f_parts", (size_t)D.splits * wcols * nz);
     // treecode: the points in the Hilbert order of their positions, so that a
     // tile of consecutive targets is a compact cluster (results go back to the
     // caller's order in the epilogue)
     const int* tperm = nullptr;
     if (far_tol > 0.0) {
-      std::vector<double2> hz((size_t)nz);
-      HIPCHK(c, hipMemcpyAsync(hz.data(), z, sizeof(double2) * nz, hipMemcpyDeviceToHost, c->stream));
-      HIPCHK(c, hipStreamSynchronize(c->stream));
-      std::vector<int> perm;
-      hilbert_order(hz, perm);
-      tperm = upload(c, "f_tperm", perm);
+      int* perm = ws<int>(c, "f_tperm", nz);
+      // the sort's scratch: the partial sums' buffer, not yet in use, where it suffices
+      const size_t hb = hilbert_scratch(nz);
+      void* hs = hb <= sizeof(double2) * D.splits * wcols * nz ? (void*)D.parts : (void*)ws<char>(c, "f_hilbert", hb);
+      HIPCHK(c, launch_hilbert_order(static_cast<const double2*>(z), nullptr, (int)nz, hs, perm, c->stream));
+      tperm = perm;
       double2* zp = ws<double2>(c, "f_zp", (size_t)nz);
       k_gather_points<<<nblocks(nz), kT, 0, c->stream>>>(static_cast<const double2*>(z), tperm, nz, zp);
       LAUNCHCHK(c);
       D.tz = zp;
     }
-    D.parts = ws<double2>(c, "f_parts", (size_t)D.splits * wcols * nz);
     D.tb = ws<double4>(c, "f_tb", (size_t)((nz + 63) / 64));
     B.d_dom = upload(c, "b_dom", B.dom);
     HIPCHK(c, launch_tile_bounds(B.d_dom, 1, (int)nz, 64 * B.shape.tpt, 3, c->stream));

@@ -12,8 +12,9 @@
 //     truncated with error below (r_b/|z - c_b|)^p times sum |w_j|/(|z - c_b| - r_b);
 //   * every other source is summed directly, in blocks of 64 nodes, by the
 //     FP64 pair loops (j != i excluded);
-//   * the interaction lists (far boxes and near blocks per target tile) come
-//     from the host; each (target tile, split) workgroup takes four
+//   * the order of the leaves (and of separate targets) along a Hilbert curve
+//     and the interaction lists (far boxes and near blocks per target tile) are
+//     made on the GPU; each (target tile, split) workgroup takes four
 //     cost-balanced ranges of its tile's list, one per wavefront, and writes
 //     one partial sum, which the consumer adds in split order like those of
 //     the direct kernels.
@@ -363,7 +364,453 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   }
 }
 
+
+// ------------------------------------------------ order along a Hilbert curve
+// The points (or the centres of boxes) in the order of their positions along a
+// Hilbert curve, 16 bits per coordinate over their bounding square, ties in
+// index order: the curve has no jumps, so any run of consecutive entries lies in
+// a compact region of the plane. The sort is bound by its launches: 0.2 ms for
+// 200003 points (on the host about 15 ms of a 20.7 ms call).
+constexpr int kMinMaxBlocks = 64;
+
+__device__ __forceinline__ double2 point_at(const double2* pts, const double4* boxes, int i) {
+  if (pts) return pts[i];
+  const double4 b = boxes[i];
+  return make_double2(0.5 * (b.x + b.y), 0.5 * (b.z + b.w));
+}
+
+// per block {xmin, xmax, ymin, ymax} of its share of the points
+__global__ __launch_bounds__(256) void k_point_range(const double2* __restrict__ pts,
+                                                     const double4* __restrict__ boxes, int n,
+                                                     double4* __restrict__ range) {
+  __shared__ double4 sh[4];
+  double4 v = make_double4(1e300, -1e300, 1e300, -1e300);
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    const double2 p = point_at(pts, boxes, i);
+    v = make_double4(fmin(v.x, p.x), fmax(v.y, p.x), fmin(v.z, p.y), fmax(v.w, p.y));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    v.x = fmin(v.x, __shfl_xor(v.x, off, 64));
+    v.y = fmax(v.y, __shfl_xor(v.y, off, 64));
+    v.z = fmin(v.z, __shfl_xor(v.z, off, 64));
+    v.w = fmax(v.w, __shfl_xor(v.w, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < 4; ++k)
+      v = make_double4(fmin(v.x, sh[k].x), fmax(v.y, sh[k].y), fmin(v.z, sh[k].z), fmax(v.w, sh[k].w));
+    range[blockIdx.x] = v;
+  }
+}
+
+// position along the curve of cell (x, y) of the 2^16 x 2^16 grid
+__device__ __forceinline__ uint32_t hilbert_position(uint32_t x, uint32_t y) {
+  constexpr uint32_t side = 1u << 16;
+  uint32_t d = 0;
+  for (uint32_t h = side / 2; h > 0; h /= 2) {
+    const uint32_t rx = (x & h) ? 1u : 0u, ry = (y & h) ? 1u : 0u;
+    d += h * h * ((3u * rx) ^ ry);
+    if (ry == 0) {   // rotate the quadrant
+      if (rx == 1) {
+        x = side - 1 - x;
+        y = side - 1 - y;
+      }
+      const uint32_t t = x;
+      x = y;
+      y = t;
+    }
+  }
+  return d;
+}
+
+// the points' bounding box from the blocks' (by every lane of a wave together)
+__device__ __forceinline__ double4 whole_range(const double4* __restrict__ range) {
+  static_assert(kMinMaxBlocks == 64, "one block's range per lane");
+  double4 v = range[threadIdx.x & 63];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    v.x = fmin(v.x, __shfl_xor(v.x, off, 64));
+    v.y = fmax(v.y, __shfl_xor(v.y, off, 64));
+    v.z = fmin(v.z, __shfl_xor(v.z, off, 64));
+    v.w = fmax(v.w, __shfl_xor(v.w, off, 64));
+  }
+  return v;
+}
+
+__device__ __forceinline__ uint32_t point_code(const double2* pts, const double4* boxes, int i, double4 v) {
+  const double span = fmax(v.y - v.x, v.w - v.z);
+  const double sc = span > 0.0 ? 65535.0 / span : 0.0;
+  const double2 p = point_at(pts, boxes, i);
+  const uint32_t qx = (uint32_t)fmin(65535.0, fmax(0.0, (p.x - v.x) * sc));
+  const uint32_t qy = (uint32_t)fmin(65535.0, fmax(0.0, (p.y - v.z) * sc));
+  return hilbert_position(qx, qy);
+}
+
+__global__ __launch_bounds__(256) void k_point_codes(const double2* __restrict__ pts,
+                                                     const double4* __restrict__ boxes, int n,
+                                                     const double4* __restrict__ range, uint32_t* __restrict__ key,
+                                                     int* __restrict__ idx) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  const double4 v = whole_range(range);
+  if (i >= n) return;
+  key[i] = point_code(pts, boxes, i, v);
+  idx[i] = i;
+}
+
+// Up to kSmallSort points in one block: codes and indices as 64-bit keys
+// (unique, so any sort keeps ties in index order), bitonic in LDS.
+constexpr int kSmallSort = 4096;
+__global__ __launch_bounds__(1024) void k_sort_small(const double2* __restrict__ pts,
+                                                     const double4* __restrict__ boxes, int n,
+                                                     const double4* __restrict__ range, int* __restrict__ perm) {
+  __shared__ unsigned long long k[kSmallSort];
+  const double4 v = whole_range(range);
+  int m = 1;
+  while (m < n) m *= 2;
+  for (int i = threadIdx.x; i < m; i += blockDim.x)
+    k[i] = i < n ? ((unsigned long long)point_code(pts, boxes, i, v) << 32) | (unsigned)i : ~0ull;
+  __syncthreads();
+  for (int len = 2; len <= m; len *= 2)
+    for (int h = len / 2; h > 0; h /= 2) {
+      for (int q = threadIdx.x; q < m / 2; q += blockDim.x) {
+        const int a = 2 * h * (q / h) + q % h, b = a + h;
+        const unsigned long long x = k[a], y = k[b];
+        if ((x > y) == ((a & len) == 0)) {
+          k[a] = y;
+          k[b] = x;
+        }
+      }
+      __syncthreads();
+    }
+  for (int i = threadIdx.x; i < n; i += blockDim.x) perm[i] = (int)(k[i] & 0xffffffffu);
+}
+
+// More points: least-significant-digit radix sort, eight bits a pass, stable.
+// A block takes kSortTile consecutive entries in rounds of 256.
+constexpr int kSortTile = 2048;
+__global__ __launch_bounds__(256) void k_sort_count(const uint32_t* __restrict__ key, int n, int shift, int nblk,
+                                                    int* __restrict__ hist) {
+  __shared__ int cnt[256];
+  cnt[threadIdx.x] = 0;
+  __syncthreads();
+  const int i0 = blockIdx.x * kSortTile;
+  for (int r = 0; r < kSortTile; r += 256) {
+    const int i = i0 + r + threadIdx.x;
+    if (i < n) atomicAdd(&cnt[(key[i] >> shift) & 255], 1);
+  }
+  __syncthreads();
+  hist[(size_t)threadIdx.x * nblk + blockIdx.x] = cnt[threadIdx.x];
+}
+
+// exclusive sums of v[0..n) in place, one block; the total to *total when given
+template <class T>
+__device__ __forceinline__ void block_scan(T* __restrict__ v, int64_t n, T* total) {
+  __shared__ T wsum[16];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;   // 1024 threads
+  T run = 0;
+  for (int64_t base = 0; base < n; base += 4096) {
+    T x[4], s = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = base + 4 * t + k;
+      x[k] = i < n ? v[i] : (T)0;
+      s += x[k];
+    }
+    T inc = s;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const T o = __shfl_up(inc, off, 64);
+      if (lane >= off) inc += o;
+    }
+    if (lane == 63) wsum[wv] = inc;
+    __syncthreads();
+    T before = run, all = 0;
+    for (int k = 0; k < 16; ++k) {
+      if (k < wv) before += wsum[k];
+      all += wsum[k];
+    }
+    T e = before + inc - s;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = base + 4 * t + k;
+      if (i < n) v[i] = e;
+      e += x[k];
+    }
+    run += all;
+    __syncthreads();
+  }
+  if (total && t == 0) *total = run;
+}
+
+__global__ __launch_bounds__(1024) void k_sort_scan(int* __restrict__ hist, int64_t n) {
+  block_scan<int>(hist, n, nullptr);
+}
+
+__global__ __launch_bounds__(256) void k_sort_scatter(const uint32_t* __restrict__ key, const int* __restrict__ idx,
+                                                      int n, int shift, int nblk, const int* __restrict__ hist,
+                                                      uint32_t* __restrict__ key_out, int* __restrict__ idx_out) {
+  __shared__ int next[256];       // where the block's next entry of a digit goes
+  __shared__ int wcnt[4][256];    // entries of a digit in each wave of the round
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  next[t] = hist[(size_t)t * nblk + blockIdx.x];
+  const int i0 = blockIdx.x * kSortTile;
+  for (int r = 0; r < kSortTile && i0 + r < n; r += 256) {
+    const int i = i0 + r + t;
+    const bool in = i < n;
+    const uint32_t k = in ? key[i] : 0u;
+    const int dg = (k >> shift) & 255;
+    for (int w = 0; w < 4; ++w) wcnt[w][t] = 0;
+    __syncthreads();
+    unsigned long long same = __ballot(in);   // lanes with this lane's digit
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const unsigned long long m = __ballot(in && ((dg >> b) & 1));
+      same &= ((dg >> b) & 1) ? m : ~m;
+    }
+    const int rank = __popcll(same & ((1ull << lane) - 1ull));
+    if (in && rank == 0) wcnt[wv][dg] = __popcll(same);
+    __syncthreads();
+    if (in) {
+      int pos = next[dg] + rank;
+      for (int w = 0; w < wv; ++w) pos += wcnt[w][dg];
+      key_out[pos] = k;
+      idx_out[pos] = idx[i];
+    }
+    __syncthreads();
+    next[t] += wcnt[0][t] + wcnt[1][t] + wcnt[2][t] + wcnt[3][t];
+    __syncthreads();
+  }
+}
+
+__global__ void k_invert(const int* __restrict__ perm, int n, int* __restrict__ inv) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s < n) inv[perm[s]] = s;
+}
+
+// --------------------------------------------------------- interaction lists
+// One wavefront per target tile walks the boxes from the root, up to 64 of one
+// level at a time (the stack holds at most 128 boxes of each level, since a level
+// is pushed to only when nothing deeper is left). A box separated from the tile
+// by (1 + theta)(r_t + r_b) becomes a far entry of the order its own ratio needs,
+// a leaf that is not its near blocks, any other box its two children. The first
+// pass counts the entries and their cost (far 4 p_e + 24, near source 13, the
+// tile's own window 16: integers, so every sum is exact), the second writes them
+// and cuts the list into nseg ranges of about equal cost. Bound by the latency of
+// the box loads; 0.58 + 0.65 ms for the 9 million entries of 1089 x 4096 nodes (on
+// 16 host threads, with the copies both ways, the lists took most of the 40 ms
+// that a solve spent outside the GPU).
+constexpr int kTreeLevels = 24;   // leaves < 2^23
+
+struct TreeWalk {
+  const double4* bounds;
+  const double4* tb;
+  const int* perm;
+  int off[kTreeLevels + 1], nb[kTreeLevels + 1];
+  double thr[kTreeMaxP + 1];   // far_tol^(1/k)
+  double f2;                   // (1 + theta)^2
+  int levels, p, N, NT, kt, tiles, nseg, ext;
+};
+
+__device__ __forceinline__ int64_t wave_prefix(int64_t v, int lane, int64_t* total) {
+  int64_t inc = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int64_t o = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += o;
+  }
+  *total = __shfl(inc, 63, 64);
+  return inc - v;
+}
+
+template <bool FILL>
+__global__ __launch_bounds__(256) void k_tree_lists(TreeWalk W, int64_t* __restrict__ count, int64_t* __restrict__ cost,
+                                                    double* __restrict__ work, int* __restrict__ list,
+                                                    int* __restrict__ seg) {
+  __shared__ int stk[4][128 * kTreeLevels];   // level in bits 24.., box of the level below
+  __shared__ double thr[kTreeMaxP + 1];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (threadIdx.x <= (unsigned)W.p) thr[threadIdx.x] = W.thr[threadIdx.x];
+  __syncthreads();
+  const int t = blockIdx.x * 4 + wv;
+  if (t >= W.tiles) return;
+  int* st = stk[wv];
+  const double4 tt = W.tb[t];
+  const int base = t * W.kt;
+  const double nt = (double)min(W.kt, W.NT - base);
+  const int64_t start = FILL ? count[t] : 0, tot = FILL ? cost[t] : 0;
+  int64_t n = 0, acc = 0;
+  double wk = 0.0;
+  int sp = 1;
+  if (lane == 0) st[0] = (W.levels - 1) << 24;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  while (sp > 0) {
+    // the run of entries of the top's level, at most 64
+    const int mine = lane < sp ? st[sp - 1 - lane] : -1;
+    const int l = __shfl(mine, 0, 64) >> 24;
+    const unsigned long long other = ~__ballot(lane < sp && (mine >> 24) == l);
+    const int take = other ? __ffsll((unsigned long long)other) - 1 : 64;
+    sp -= take;
+    const bool on = lane < take;
+    const int b = mine & 0xffffff;
+    const int g = W.off[l] + b;
+    int kind = 0;   // 1 far, 2 near leaf, 3 children
+    int pe = 2, nblk = 0, j0 = 0, nch = 0;
+    int64_t c = 0;
+    if (on) {
+      const double4 bb = W.bounds[g];
+      const double dx = tt.x - bb.x, dy = tt.y - bb.y, rr = tt.z + bb.z;
+      const double d2 = dx * dx + dy * dy;
+      if (d2 > W.f2 * rr * rr) {
+        kind = 1;
+        const double rho = bb.z / (sqrt(d2) - tt.z);
+        while (pe < W.p && rho > thr[pe]) ++pe;
+        c = 4 * pe + 24;
+        if (!FILL) wk += nt * (8.0 * pe + 8.0);
+      } else if (l == 0) {
+        kind = 2;
+        j0 = W.perm[b] * kLeaf;
+        nblk = (min(W.N - j0, kLeaf) + 63) / 64;
+        const int j1 = min(W.N, j0 + kLeaf);
+        const int ov = W.ext ? 0 : max(0, min(j1, base + W.kt) - max(j0, base));
+        c = 13 * (j1 - j0 - ov) + 16 * ov;
+        if (!FILL) wk += 16.0 * (nt * (j1 - j0) - ov);
+      } else {
+        kind = 3;
+        nch = 2 * b + 1 < W.nb[l - 1] ? 2 : 1;
+      }
+    }
+    int64_t tn, tc, th;
+    const int64_t pn = wave_prefix(kind == 1 ? 1 : nblk, lane, &tn);
+    const int64_t pc = wave_prefix(c, lane, &tc);
+    const int64_t ph = wave_prefix(nch, lane, &th);
+    if (FILL && (kind == 1 || kind == 2)) {
+      int64_t e = n + pn, a = acc + pc;
+      int* sg = seg + (size_t)t * (W.nseg + 1);
+      const int ne = kind == 1 ? 1 : nblk;
+      for (int q = 0; q < ne; ++q, ++e) {
+        int64_t ce = c;
+        int ent = (pe << 24) | g;
+        if (kind == 2) {
+          const int b0 = j0 + 64 * q, b1 = min(W.N, b0 + 64);
+          const int ov = W.ext ? 0 : max(0, min(b1, base + W.kt) - max(b0, base));
+          ce = 13 * (b1 - b0 - ov) + 16 * ov;
+          ent = ~(b0 / 64);
+        }
+        list[start + e] = ent;
+        // the cuts tot k / nseg that fall into this entry go before it or, past
+        // its middle, behind it
+        for (int64_t k = a * W.nseg / tot + 1; k < W.nseg && k * tot <= (a + ce) * W.nseg; ++k)
+          sg[k] = (int)(start + (2 * k * tot <= (2 * a + ce) * W.nseg ? e : e + 1));
+        a += ce;
+      }
+    }
+    // a box's children keep their order when they come off the stack
+    if (kind == 3)
+      for (int q = 0; q < nch; ++q) st[sp + (int)th - 1 - (int)ph - q] = ((l - 1) << 24) | (2 * b + q);
+    sp += (int)th;
+    n += tn;
+    acc += tc;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  if constexpr (!FILL) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) wk += __shfl_xor(wk, off, 64);
+    if (lane == 0) {
+      count[t] = n;
+      cost[t] = acc;
+      work[t] = wk;
+    }
+  } else if (lane == 0) {
+    int* sg = seg + (size_t)t * (W.nseg + 1);
+    sg[0] = (int)start;
+    sg[W.nseg] = (int)(start + n);
+  }
+}
+
+// counts to offsets; the list's length to host-mapped memory
+__global__ __launch_bounds__(1024) void k_list_offsets(int64_t* __restrict__ count, int tiles, int64_t* total) {
+  block_scan<int64_t>(count, tiles, total);
+}
+
 }  // namespace
+
+// scratch: 2 n uint32 keys, n ints, 256 ceil(n / 2048) ints, kMinMaxBlocks double4
+size_t hilbert_scratch(int64_t n) {
+  const int64_t nblk = (n + kSortTile - 1) / kSortTile;
+  return (size_t)(n <= kSmallSort ? 0 : 12 * n + 1024 * nblk) + kMinMaxBlocks * sizeof(double4);
+}
+
+hipError_t launch_hilbert_order(const double2* pts, const double4* boxes, int n, void* scratch, int* perm,
+                                hipStream_t st) {
+  double4* range = static_cast<double4*>(scratch);
+  k_point_range<<<kMinMaxBlocks, 256, 0, st>>>(pts, boxes, n, range);
+  if (n <= kSmallSort) {
+    k_sort_small<<<1, 1024, 0, st>>>(pts, boxes, n, range, perm);
+    return hipGetLastError();
+  }
+  const int nblk = (n + kSortTile - 1) / kSortTile;
+  uint32_t* key[2] = {reinterpret_cast<uint32_t*>(range + kMinMaxBlocks), nullptr};
+  key[1] = key[0] + n;
+  int* idx[2] = {perm, reinterpret_cast<int*>(key[1] + n)};   // four passes: back in perm
+  int* hist = idx[1] + n;
+  k_point_codes<<<(n + 255) / 256, 256, 0, st>>>(pts, boxes, n, range, key[0], idx[0]);
+  for (int pass = 0; pass < 4; ++pass) {
+    const int a = pass & 1, b = a ^ 1;
+    k_sort_count<<<nblk, 256, 0, st>>>(key[a], n, 8 * pass, nblk, hist);
+    k_sort_scan<<<1, 1024, 0, st>>>(hist, (int64_t)256 * nblk);
+    k_sort_scatter<<<nblk, 256, 0, st>>>(key[a], idx[a], n, 8 * pass, nblk, hist, key[b], idx[b]);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_invert(const int* perm, int n, int* inv, hipStream_t st) {
+  k_invert<<<(n + 255) / 256, 256, 0, st>>>(perm, n, inv);
+  return hipGetLastError();
+}
+
+static TreeWalk tree_walk(const TreeListArgs& A) {
+  TreeWalk W{};
+  W.bounds = A.bounds;
+  W.tb = A.tb;
+  W.perm = A.perm;
+  for (int l = 0; l < A.levels; ++l) {
+    W.off[l] = A.level_off[l];
+    W.nb[l] = A.level_nb[l];
+  }
+  // rho^k <= far_tol exactly when rho <= far_tol^(1/k): the order of a far
+  // entry is the least k >= 2 (at most p) whose threshold its ratio meets
+  for (int k = 1; k <= A.p; ++k) W.thr[k] = std::pow(A.far_tol, 1.0 / k);
+  W.f2 = (1.0 + A.theta) * (1.0 + A.theta);
+  W.levels = A.levels;
+  W.p = A.p;
+  W.N = A.N;
+  W.NT = A.NT;
+  W.kt = A.kt;
+  W.tiles = A.tiles;
+  W.nseg = A.nseg;
+  W.ext = A.ext ? 1 : 0;
+  return W;
+}
+
+hipError_t launch_tree_count(const TreeListArgs& A, int64_t* count, int64_t* cost, double* work, int64_t* total,
+                             hipStream_t st) {
+  if (A.levels < 1 || A.levels > kTreeLevels || A.p > kTreeMaxP) return hipErrorInvalidValue;
+  k_tree_lists<false><<<(A.tiles + 3) / 4, 256, 0, st>>>(tree_walk(A), count, cost, work, nullptr, nullptr);
+  k_list_offsets<<<1, 1024, 0, st>>>(count, A.tiles, total);
+  return hipGetLastError();
+}
+
+hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* count, int64_t* cost, int* list, int* seg,
+                            hipStream_t st) {
+  k_tree_lists<true><<<(A.tiles + 3) / 4, 256, 0, st>>>(tree_walk(A), count, cost, nullptr, list, seg);
+  return hipGetLastError();
+}
 
 hipError_t launch_leaf_boxes(const double2* eta, int N, int nleaf, double4* leafbox, hipStream_t st) {
   k_leaf_bbox<<<nleaf, 64, 0, st>>>(eta, N, leafbox);
