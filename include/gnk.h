@@ -126,7 +126,9 @@ typedef struct {
  *   far_tol    : 0 (every pair summed directly); > 0: the Cauchy sums take
  *                their far field from multipole expansions of boxes of
  *                consecutive nodes (a treecode; the paper uses the FMM), each
- *                truncated where (r_box / distance)^p <= far_tol; FP64 only
+ *                truncated where (r_box / distance)^p <= far_tol, and entering
+ *                the targets' through expansions of target tiles truncated at
+ *                far_tol/64; FP64 only
  *                (prec GNK_FP64), gnk_fbie and gnk_fbie_ad only; 1e-15..0.1
  *   hist, hist_len : optional residual history (the paper reports GMRES's
  *                convergence, Sec. 7): HOST array of hist_len doubles per
@@ -212,8 +214,11 @@ GNK_API const char* gnk_version(void);
  *   *_tree            : the treecode products (also in the totals; their flops
  *                       field counts the direct sum they replace): launches,
  *                       time, and the work their interaction lists imply,
- *                       8 p_e + 8 flops per target and far box (a p_e-term
- *                       expansion), 16 per near pair, for each column
+ *                       64 p_e flops per tile and far box (p_e terms of the
+ *                       box converted into 16 of the tile's expansion; twice
+ *                       or three times that where 32 or 48 are needed), 384
+ *                       per target (the tile's expansion), 16 per near pair,
+ *                       for each column
  *   *_fft             : the circulant products L-hat x (not in the totals):
  *                       launches (one per call, all block lengths), time, and
  *                       algorithmic bytes, 24 per unknown and column (read x,

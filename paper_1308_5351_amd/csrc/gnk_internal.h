@@ -29,6 +29,8 @@ constexpr int kFarTile = 1 << kFarTileLog2;
 // then wcols products b_q = w_q conj(eta')
 constexpr int kRecHead = 3;
 __host__ __device__ constexpr int rec_stride(int wcols) { return kRecHead + 2 * wcols; }
+// the treecode's slim records: {eta, w_q..}
+__host__ __device__ constexpr int slim_stride(int wcols) { return 1 + wcols; }
 // FP32 records of mixed products: {v, (|v|^2, 0), w.., b..} (float2 fields;
 // v the offset from the node's 64-node tile centre in units of its radius)
 __host__ __device__ constexpr int rec32_stride(int wcols) { return 2 + 2 * wcols; }
@@ -75,6 +77,7 @@ struct DomDev {
   int symslots;      // partial-sum slots of the two-sided one-column launch (0: none)
   int chunk;         // sources per split
   int c;             // +1 bounded, -1 unbounded
+  int slim;          // records are the treecode's slim ones
 };
 
 struct ColDev {
@@ -114,16 +117,16 @@ hipError_t launch_pairs_sym(const DomDev* doms, const int4* items, int nitems, c
 // 3 target tiles of the separate targets tz (tb)
 hipError_t launch_tile_bounds(const DomDev* doms, int ndom, int maxN, int tile, int which, hipStream_t st);
 hipError_t launch_node_tile_bounds(const DomDev* doms, int ndom, int maxN, int tpt, hipStream_t st);
-// Treecode (csrc/tree.hip): boxes of kLeaf << l consecutive nodes at level l
-constexpr int kLeaf = 256;
-constexpr int kTreeMaxP = 48;
+// Treecode (csrc/tree.hip): boxes of kLeaf << l nodes at level l
+constexpr int kLeaf = 64;
+constexpr int kTreeMaxP = 48;   // terms of a box's and of a tile's expansion
 // bounding circles of the boxes of every level (at out + level_off[l]): level
-// 0 holds the leaves in slot order (perm: slot -> leaf, invp: leaf -> slot),
-// box b of level l the slots [b 2^l, (b + 1) 2^l); leafbox: the leaves'
-// bounding boxes; bbox and rbits: scratch of one entry per box
+// 0 holds the leaves in slot order (perm: slot -> leaf), box b of level l the
+// slots [b 2^l, (b + 1) 2^l); leafbox: the leaves' bounding boxes; bbox and
+// rbits: scratch of one entry per box
 hipError_t launch_box_bounds(const double2* eta, int N, const int* level_off, const int* level_nb, int levels,
-                             const double4* leafbox, const int* perm, const int* invp, double4* bbox,
-                             unsigned long long* rbits, double4* out, hipStream_t st);
+                             const double4* leafbox, const int* perm, double4* bbox, unsigned long long* rbits,
+                             double4* out, hipStream_t st);
 // bounding boxes {xmin, xmax, ymin, ymax} of the leaves (kLeaf consecutive nodes)
 hipError_t launch_leaf_boxes(const double2* eta, int N, int nleaf, double4* leafbox, hipStream_t st);
 // perm: the n points (pts, or the centres of boxes when pts is null) in the
@@ -132,11 +135,11 @@ hipError_t launch_leaf_boxes(const double2* eta, int N, int nleaf, double4* leaf
 size_t hilbert_scratch(int64_t n);
 hipError_t launch_hilbert_order(const double2* pts, const double4* boxes, int n, void* scratch, int* perm,
                                 hipStream_t st);
-hipError_t launch_invert(const int* perm, int n, int* inv, hipStream_t st);
 // Interaction lists of `tiles` target tiles (kt targets each, bounds tb) against
-// the boxes. Count: entries (then their offsets), cost and work (flops) of every
-// tile, and the list's length at *total (host-mapped). Fill: the list and each
-// tile's nseg + 1 bounds into it.
+// the boxes: far entries {box, p_e | chunks of 16 tile terms << 8} and near blocks
+// (64-node indices). Count: offsets of every tile into the two lists (tiles + 1
+// each), its work (flops: 64 p_e per chunk of a far entry, 8 kTreeMaxP per target,
+// 16 per near pair) and the lists' lengths at total[0..1] (host-mapped).
 struct TreeListArgs {
   const double4* bounds;
   const double4* tb;
@@ -144,23 +147,41 @@ struct TreeListArgs {
   const int* level_off;   // host
   const int* level_nb;    // host
   double far_tol, theta;
-  int levels, p, N, NT, kt, tiles, nseg;
+  int levels, p, N, NT, kt, tiles;
   bool ext;
 };
-hipError_t launch_tree_count(const TreeListArgs& A, int64_t* count, int64_t* cost, double* work, int64_t* total,
+hipError_t launch_tree_count(const TreeListArgs& A, int64_t* faroff, int64_t* nearoff, double* work, int64_t* total,
                              hipStream_t st);
-hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* count, int64_t* cost, int* list, int* seg,
+hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* faroff, int64_t* nearoff, int2* far, int* near,
                             hipStream_t st);
-// multipole moments (p per box) of record weight field wo: leaves directly,
-// then every level from its children; level_off/level_nb: host arrays
-hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int N, const double4* bounds, const int* perm,
-                               const int* level_off, const int* level_nb, int levels, int p, double2* mom,
-                               hipStream_t st);
-// far boxes by their moments, near 64-node blocks directly, for weight column
-// col of doms[0]; seg: per target tile, 4 splits + 1 bounds into list
-hipError_t launch_tree_eval(const DomDev* doms, int tiles, int tpt, const int* seg, const int* list,
-                            const double4* bounds, const double2* mom, int p, int splits, int col, int wcols,
-                            const int* active, int lead, bool ext, hipStream_t st);
+// multipole moments (p per box, column c at mom + c colstride) of ncols record
+// weight fields from wo on: leaves directly, then every level from its children;
+// level_off/level_nb: host arrays; active: null, or a flag on the device (0: skip)
+hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols, int N, const double4* bounds,
+                               const int* perm, const int* level_off, const int* level_nb, int levels, int p,
+                               double2* mom, size_t colstride, const int* active, hipStream_t st);
+// C(k + l, l), kTreeMaxP x kTreeMaxP
+std::vector<double> tree_binomials();
+// The tiles' local expansions (loc: kTreeMaxP per tile and column, terms: per tile)
+// and the sums of weight columns col .. col + ncols - 1 (ncols 1 or 2) of doms[0];
+// flag: as `active` of launch_tree_moments, for the expansions
+struct TreeEvalArgs {
+  const double4* tb;
+  const int64_t* faroff;
+  const int2* far;
+  const int64_t* nearoff;
+  const int* near;
+  const double4* bounds;
+  const double2* mom;
+  size_t colstride;
+  int p;
+  const double* binom;
+  double2* loc;
+  int* terms;
+};
+hipError_t launch_tree_eval(const DomDev* doms, int tiles, int tpt, const TreeEvalArgs& A, int ncols, int splits,
+                            int col, int wcols, const int* active, int lead, bool ext, const int* flag,
+                            hipStream_t st);
 // FP32 records from the FP64 records of every domain; threads: the largest
 // N_d * (weight columns rounded up to a multiple of 8) over the domains
 hipError_t launch_records32(const DomDev* doms, int ndom, int64_t threads, int lead, int data, hipStream_t st);

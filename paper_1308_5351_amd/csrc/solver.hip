@@ -271,14 +271,10 @@ struct Batch {
     bool on = false;
     int p = 0, levels = 0, nbox = 0, splits = 0, tiles = 0;
     std::vector<int> off, nb;
-    double4* bounds = nullptr;
+    TreeEvalArgs ev{};
     double2* mom = nullptr;
-    int* seg = nullptr;
-    int* list = nullptr;
-    size_t list_len = 0;
-    double flops = 0.0;   // per column: 8 p_e + 8 per (target, far box), 16 per near pair
-    int* perm = nullptr;  // level-0 slot -> leaf (device), and leaf -> slot
-    int* invp = nullptr;
+    double flops = 0.0;   // per column (see TreeListArgs)
+    int* perm = nullptr;  // level-0 slot -> leaf (device)
     bool ext = false;     // targets are the points tz (no j != i window), not the nodes
   } tree;
 };
@@ -625,15 +621,14 @@ hipEvent_t pool_event(gnk_ctx* c) {
 
 // ----------------------------------------------------------------- treecode
 // Far-field compression for one domain (the treecode of csrc/tree.hip): box
-// bounds on the device, then on the host one depth-first pass per target
-// tile over the box hierarchy: a box whose bounding circle is separated from
-// the tile's by (1 + theta)(r_t + r_b) is far (its expansion), a leaf that is
-// not is near (its four 64-node blocks, summed directly); each tile's list is
-// cut into 4 splits ranges of about equal estimated cost (far box 4p_e + 24,
-// near source 13 per target, the tile's own window 16). theta = 1.5 bounds
-// r_b/|z - c_b| by 0.4, so p = log(far_tol)/log(0.4) terms meet far_tol for
-// every far box; each (tile, box) entry takes the p_e its own ratio
-// rho_e = r_b/(|c_t - c_b| - r_t) >= r_b/|z - c_b| needs, which keeps the bound.
+// bounds, then one pass per target tile over the box hierarchy: a box whose
+// bounding circle is separated from the tile's by (1 + theta)(r_t + r_b) is far
+// (it enters the tile's local expansion), a leaf that is not is near (its 64 nodes
+// are summed directly). theta = 1.5 bounds r_b/|z - c_b| by 0.4, so p =
+// log(far_tol)/log(0.4) terms meet far_tol for every far box; each (tile, box)
+// entry takes the p_e its own ratio rho_e = r_b/(|c_t - c_b| - r_t) >= r_b/|z - c_b|
+// needs, and as many terms of the tile's expansion as r_t/(|c_t - c_b| - r_b)
+// needs for far_tol/64 (at most 48, in chunks of 16).
 constexpr double kTreeTheta = 1.5;
 
 int tree_terms(double far_tol) {
@@ -655,11 +650,6 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   T.ext = ext;
   T.p = tree_terms(far_tol);
   int total = 0;
-  // far entries carry the box index in 24 bits
-  if ((int64_t)2 * ((N + kLeaf - 1) / kLeaf) + 64 >= ((int64_t)1 << 24)) {
-    set_err(c, "the treecode takes at most about 2^31 nodes");
-    throw Fail{GNK_ERR_ARG};
-  }
   for (int nb = (N + kLeaf - 1) / kLeaf;; nb = (nb + 1) / 2) {
     T.off.push_back(total);
     T.nb.push_back(nb);
@@ -668,8 +658,21 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   }
   T.levels = (int)T.nb.size();
   T.nbox = total;
-  T.bounds = ws<double4>(c, "t_bounds", total);
-  T.mom = ws<double2>(c, "t_mom", (size_t)total * T.p);
+  double4* bounds = ws<double4>(c, "t_bounds", total);
+  // moments of up to two weight columns at a time
+  const int mcols = std::min(2, D.ncols + 1);
+  // (in the rest of the record buffer, which the slim records leave free, where
+  // they fit: below 37 terms; likewise the tiles' expansions)
+  double2* spare = D.rec + (size_t)N * slim_stride(D.ncols + 1);
+  size_t spare_len = (size_t)N * (rec_stride(D.ncols + 1) - slim_stride(D.ncols + 1));
+  auto carve = [&](const char* name, size_t n) {
+    if (n > spare_len) return ws<double2>(c, name, n);
+    double2* q = spare;
+    spare += n;
+    spare_len -= n;
+    return q;
+  };
+  T.mom = carve("t_mom", (size_t)mcols * total * T.p);
   double4* bbox = ws<double4>(c, "t_bbox", total);
   unsigned long long* rbits = ws<unsigned long long>(c, "t_rbits", total);
   // The leaves take the level-0 slots in the Hilbert order of their centres, so
@@ -679,43 +682,43 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   double4* lbox = ws<double4>(c, "t_lbox", nleaf);
   HIPCHK(c, launch_leaf_boxes(D.eta, N, nleaf, lbox, c->stream));
   int* perm = ws<int>(c, "t_perm", nleaf);
-  int* invp = ws<int>(c, "t_invp", nleaf);
   // the sort's scratch: the moments' buffer, not yet in use, where it suffices
   const size_t hb = hilbert_scratch(nleaf);
   void* hs = hb <= sizeof(double2) * total * T.p ? (void*)T.mom : (void*)ws<char>(c, "t_hilbert", hb);
   HIPCHK(c, launch_hilbert_order(nullptr, lbox, nleaf, hs, perm, c->stream));
-  HIPCHK(c, launch_invert(perm, nleaf, invp, c->stream));
   T.perm = perm;
-  T.invp = invp;
-  HIPCHK(c, launch_box_bounds(D.eta, N, T.off.data(), T.nb.data(), T.levels, lbox, T.perm, T.invp, bbox, rbits,
-                              T.bounds, c->stream));
+  HIPCHK(c, launch_box_bounds(D.eta, N, T.off.data(), T.nb.data(), T.levels, lbox, T.perm, bbox, rbits, bounds,
+                              c->stream));
   T.tiles = (NT + kt - 1) / kt;
   // about two rounds of resident workgroups
   const int64_t resident = (int64_t)c->num_cu * 5;
   int S = (int)std::max<int64_t>(1, std::min<int64_t>(16, (2 * resident + T.tiles - 1) / T.tiles));
   if (const char* e = getenv("GNK_TREE_SPLITS")) S = std::max(1, atoi(e));
   T.splits = S;
-  const TreeListArgs la{T.bounds, D.tb, T.perm, T.off.data(), T.nb.data(), far_tol, kTreeTheta,
-                        T.levels, T.p, N, NT, kt, T.tiles, 4 * S, ext};
-  int64_t* count = ws<int64_t>(c, "t_count", T.tiles);
-  int64_t* cost = ws<int64_t>(c, "t_cost", T.tiles);
+  const TreeListArgs la{bounds, D.tb, T.perm, T.off.data(), T.nb.data(), far_tol, kTreeTheta,
+                        T.levels, T.p, N, NT, kt, T.tiles, ext};
+  int64_t* faroff = ws<int64_t>(c, "t_faroff", (size_t)T.tiles + 1);
+  int64_t* nearoff = ws<int64_t>(c, "t_nearoff", (size_t)T.tiles + 1);
   double* work = ws<double>(c, "t_work", T.tiles);
-  volatile int64_t* len = reinterpret_cast<int64_t*>(hostio(c, sizeof(int64_t)));
-  HIPCHK(c, launch_tree_count(la, count, cost, work, hostio_dev(c, const_cast<int64_t*>(len)), c->stream));
+  volatile int64_t* len = reinterpret_cast<int64_t*>(hostio(c, 2 * sizeof(int64_t)));
+  HIPCHK(c, launch_tree_count(la, faroff, nearoff, work, hostio_dev(c, const_cast<int64_t*>(len)), c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  if (*len > INT32_MAX / 2) {
+  if (len[0] > INT32_MAX / 2 || len[1] > INT32_MAX / 2) {
     set_err(c, "treecode interaction lists too long");
     throw Fail{GNK_ERR_OOM};
   }
-  T.list_len = (size_t)*len;
-  // an eighth more than needed when the buffer grows, so that the lists of other
-  // domains of the same size, a little longer, find room
-  const bool grow = !c->ws_limit && c->bufs["t_list"].bytes < T.list_len * sizeof(int);
-  int* list = ws<int>(c, "t_list", grow ? T.list_len + T.list_len / 8 : T.list_len);
-  int* seg = ws<int>(c, "t_seg", (size_t)T.tiles * (4 * S + 1));
-  HIPCHK(c, launch_tree_fill(la, count, cost, list, seg, c->stream));
-  T.list = list;
-  T.seg = seg;
+  // an eighth more than needed when a list's buffer grows, so that the lists of
+  // other domains of the same size, a little longer, find room
+  auto room = [&](const char* name, size_t n, size_t item) {
+    return !c->ws_limit && c->bufs[name].bytes < n * item ? n + n / 8 : n;
+  };
+  int2* far = ws<int2>(c, "t_far", room("t_far", (size_t)len[0], sizeof(int2)));
+  int* near = ws<int>(c, "t_near", room("t_near", (size_t)len[1], sizeof(int)));
+  HIPCHK(c, launch_tree_fill(la, faroff, nearoff, far, near, c->stream));
+  double2* loc = carve("t_loc", (size_t)mcols * T.tiles * kTreeMaxP);
+  int* terms = ws<int>(c, "t_terms", T.tiles);
+  T.ev = TreeEvalArgs{D.tb, faroff, far, nearoff, near, bounds, T.mom, (size_t)total * T.p, T.p,
+                      upload(c, "t_binom", tree_binomials()), loc, terms};
   T.flops = 0.0;
   if (c->prof) {
     std::vector<double> hw((size_t)T.tiles);
@@ -728,6 +731,7 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   B.sym.on = false;
   D.symslots = 0;
   D.w1 = nullptr;
+  D.slim = 1;
   D.parts = ws<double2>(c, "t_parts", (size_t)S * (D.ncols + 1) * NT);
   B.d_dom = upload(c, "b_dom", B.dom);
   T.on = true;
@@ -746,11 +750,17 @@ void tree_pairs(gnk_ctx* c, Batch& B, int p, const int* active) {
                           wcols == 1 ? pairs : 0.0, false, wcols == 1, T.flops * wcols, true};
     HIPCHK(c, hipEventRecord(pr.a, c->stream));
   }
-  for (int col = 0; col < wcols; ++col) {
-    HIPCHK(c, launch_tree_moments(D.rec, rec_stride(wcols), kRecHead + col, D.N, T.bounds, T.perm, T.off.data(),
-                                  T.nb.data(), T.levels, T.p, T.mom, c->stream));
-    HIPCHK(c, launch_tree_eval(B.d_dom, T.tiles, B.shape.tpt, T.seg, T.list, T.bounds, T.mom, T.p, T.splits, col,
-                               wcols, active, lead, T.ext, c->stream));
+  // two weight columns at a time share the near pairs' reciprocals and the
+  // conversions' powers
+  for (int col = 0; col < wcols;) {
+    const int nc = std::min(2, wcols - col);
+    // the flag of a single data column, whose masked steps skip the expansions too
+    const int* act = active && nc == 1 && col >= lead ? active + D.c0 + col - lead : nullptr;
+    HIPCHK(c, launch_tree_moments(D.rec, slim_stride(wcols), 1 + col, nc, D.N, T.ev.bounds, T.perm, T.off.data(),
+                                  T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, act, c->stream));
+    HIPCHK(c, launch_tree_eval(B.d_dom, T.tiles, B.shape.tpt, T.ev, nc, T.splits, col, wcols, active, lead, T.ext, act,
+                               c->stream));
+    col += nc;
   }
   if (c->prof) {
     HIPCHK(c, hipEventRecord(pr.b, c->stream));
@@ -2102,6 +2112,10 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
     const int width = wcols >= 8 ? 8 : (wcols >= 4 ? 4 : (wcols >= 2 ? 2 : 1));
     int t, ch, sp;
     plan_pairs(c, nz, N, 16, width, false, &t, &ch, &sp);
+    // tiles of 64 points for the treecode: they cover more of the plane than as many
+    // nodes of a curve, and smaller tiles meet fewer near sources (289 x 1024 nodes
+    // at 200003 points: 1600 and 3070 near sources per point, 1.08 and 1.19 ms)
+    if (far_tol > 0.0) t = 1;
     Batch B;
     std::vector<int64_t> off{0};
     build_batch(c, B, 1, &d, &nrhs, off, N * (int64_t)nrhs, false, false, PairShape{t, ch}, N);
@@ -2128,9 +2142,9 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
     D.tb = ws<double4>(c, "f_tb", (size_t)((nz + 63) / 64));
     B.d_dom = upload(c, "b_dom", B.dom);
     HIPCHK(c, launch_tile_bounds(B.d_dom, 1, (int)nz, 64 * B.shape.tpt, 3, c->stream));
+    if (far_tol > 0.0) build_tree(c, B, far_tol, true);
     k_fcau_records<<<nblocks(N), kT, 0, c->stream>>>(B.d_dom, static_cast<const double2*>(f), nrhs);
     LAUNCHCHK(c);
-    if (far_tol > 0.0) build_tree(c, B, far_tol, true);
     pairs(c, B, P_SETUP, false, nullptr);
     const double2* fi = nullptr;
     if (finf) {

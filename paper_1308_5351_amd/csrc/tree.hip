@@ -1,25 +1,34 @@
 // Far-field compression of the Cauchy sums S_i = sum_{j != i} w_j/(eta_i - eta_j)
 // for large N (the paper evaluates these sums with a fast multipole method;
 // this is a treecode on the GPU, FP64 throughout):
-//   * boxes: level 0 holds the leaves of kLeaf = 256 consecutive nodes (the
+//   * boxes: level 0 holds the leaves of kLeaf = 64 consecutive nodes (the
 //     node order follows the boundary curves, so a range of nodes is compact),
 //     level l + 1 pairs the boxes of level l; each box has a bounding circle;
-//   * multipole moments of box b about its centre c_b, for one weight column:
-//     a_k = sum_{j in b} w_j (eta_j - c_b)^k, k < p; leaves from their nodes,
-//     parents from their children by the binomial shift;
-//   * a far box contributes sum_{k<p} a_k u^{k+1}, u = 1/(z - c_b), to a
-//     target z: the expansion of 1/(z - eta_j) in powers of (eta_j - c_b)/(z - c_b),
-//     truncated with error below (r_b/|z - c_b|)^p times sum |w_j|/(|z - c_b| - r_b);
+//   * multipole moments of box b about its centre c_b in units of its radius r_b,
+//     for one weight column: a_k = sum_{j in b} w_j ((eta_j - c_b)/r_b)^k, k < p;
+//     leaves from their nodes, parents from their children by the binomial shift;
+//   * a box far from a target tile (centre c_t, radius r_t) enters the tile's
+//     local expansion sum_l L_l ((z - c_t)/r_t)^l: with D = c_t - c_b, x = r_b/D and
+//     y = -r_t/D,  L_l += y^l sum_{k < p_e} C(k + l, l) a_k x^k / D,
+//     truncated on the box's side with error below (r_b/(|D| - r_t))^p_e and on
+//     the tile's side below (r_t/(|D| - r_b))^q_e, each times a factor of at most
+//     2.4 and sum |w_j|/|z - eta_j|; the expansion is evaluated once per target;
 //   * every other source is summed directly, in blocks of 64 nodes, by the
 //     FP64 pair loops (j != i excluded);
 //   * the order of the leaves (and of separate targets) along a Hilbert curve
 //     and the interaction lists (far boxes and near blocks per target tile) are
-//     made on the GPU; each (target tile, split) workgroup takes four
-//     cost-balanced ranges of its tile's list, one per wavefront, and writes
-//     one partial sum, which the consumer adds in split order like those of
-//     the direct kernels.
+//     made on the GPU; each (target tile, split) workgroup takes four equal
+//     ranges of its tile's near sources, one per wavefront, and writes one partial
+//     sum, which the consumer adds in split order like those of the direct
+//     kernels.
+// Local expansions instead of evaluating every far box at every target (4 p_e +
+// 14 operations each), and leaves of 64 nodes instead of 256: at 1089 x 4096 nodes
+// a target meets 506 near sources and 145 boxes instead of 1020 and 115, and a
+// product took 2.6 ms instead of 5.3 (near sums 1.2, expansions 1.1, moments 0.3).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
+#include <vector>
 
 #include "gnk_device.h"
 #include "gnk_internal.h"
@@ -30,21 +39,14 @@ namespace {
 
 #include "pair_steps.inl"
 
-__device__ __forceinline__ double wave_sum64(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // Bounding circles {cx, cy, r, 0} of the boxes of every level: the centre of
 // the box's bounding box and the largest distance of its nodes from it. The
-// leaves (256 consecutive nodes) take the slots of level 0 in an order chosen
-// on the host (perm: slot -> leaf, invp: leaf -> slot); the box of slots
+// leaves (kLeaf consecutive nodes) take the slots of level 0 in an order chosen
+// by their centres (perm: slot -> leaf); the box of slots
 // [b 2^l, (b + 1) 2^l) is box b of level l. Leaf bounding boxes come from
 // their nodes (one wavefront per leaf), a parent's from its two children
 // (exact: min and max), and the radii of all levels from one pass over the
-// nodes (one 256-thread block per leaf, whose nodes lie in a single box of
-// every level; a block maximum, then an atomic maximum on the radius's bit
+// nodes (maxima over the waves, then an atomic maximum on the radius's bit
 // pattern, which orders non-negative doubles as unsigned integers).
 __global__ __launch_bounds__(64) void k_leaf_bbox(const double2* __restrict__ eta, int N,
                                                   double4* __restrict__ bbox) {
@@ -102,26 +104,41 @@ struct LevelTable {
   int nb[32];    // boxes of each level
 };
 
-__global__ __launch_bounds__(256) void k_box_radii(const double2* __restrict__ eta, int N, LevelTable lv, int levels,
-                                                   const int* __restrict__ invp, const double4* __restrict__ out,
-                                                   unsigned long long* __restrict__ rbits) {
-  __shared__ double sh[4];
-  const int leaf = blockIdx.x, t = threadIdx.x;
-  const int slot = invp[leaf];
-  const int i = leaf * kLeaf + t;
+// A block takes 16 consecutive slots, one wavefront each: from level 4 on they
+// lie in one box, whose maximum the block forms before its atomic (one atomic a
+// leaf would queue 70000 of them on the top box of 4460544 nodes).
+constexpr int kRadiiWaves = 16;
+__global__ __launch_bounds__(64 * kRadiiWaves) void k_box_radii(const double2* __restrict__ eta, int N, LevelTable lv,
+                                                                int levels, int nleaf, const int* __restrict__ perm,
+                                                                const double4* __restrict__ out,
+                                                                unsigned long long* __restrict__ rbits) {
+  static_assert(kLeaf == 64, "one node per lane");
+  __shared__ double sh[32][kRadiiWaves];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int slot = blockIdx.x * kRadiiWaves + wv;
+  const bool has = slot < nleaf;
+  const int i = has ? perm[slot] * kLeaf + lane : N;
   const bool in = i < N;
   const double2 e = in ? eta[i] : make_double2(0.0, 0.0);
   for (int l = 0; l < levels; ++l) {
-    const int box = lv.off[l] + (slot >> l);
-    const double4 c = out[box];
+    const double4 c = out[lv.off[l] + (has ? slot >> l : 0)];
     double r = in ? sqrt((e.x - c.x) * (e.x - c.x) + (e.y - c.y) * (e.y - c.y)) : 0.0;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) r = fmax(r, __shfl_xor(r, off, 64));
-    if ((t & 63) == 0) sh[t >> 6] = r;
-    __syncthreads();
-    if (t == 0)
-      atomicMax(rbits + box, (unsigned long long)__double_as_longlong(fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]))));
-    __syncthreads();
+    if (lane == 0) {
+      if (l < 4) {
+        if (has) atomicMax(rbits + lv.off[l] + (slot >> l), (unsigned long long)__double_as_longlong(r));
+      } else {
+        sh[l][wv] = r;
+      }
+    }
+  }
+  __syncthreads();
+  const int l = threadIdx.x;
+  if (l >= 4 && l < levels) {
+    double r = 0.0;
+    for (int w = 0; w < kRadiiWaves; ++w) r = fmax(r, sh[l][w]);
+    atomicMax(rbits + lv.off[l] + ((blockIdx.x * kRadiiWaves) >> l), (unsigned long long)__double_as_longlong(r));
   }
 }
 
@@ -133,133 +150,389 @@ __global__ void k_box_finish(const unsigned long long* __restrict__ rbits, int n
   out[b].z = r * (1.0 + 1e-12) + 1e-300;
 }
 
-// Leaf moments of weight column wo (record field) about the leaf centres:
-// one wavefront per level-0 slot (leaf perm[slot]), each lane holding up to four nodes; moment k is
-// the wave sum of w_j (eta_j - c)^k, the powers advanced one k at a time.
+// Leaf moments of the launch's weight columns (record fields wo, wo + 1, .. by
+// blockIdx.y): four lanes per level-0 slot (leaf perm[slot]), each CH moments from
+// k = CH q on, the powers advanced from ((eta - c)/r)^(CH q), so that nothing is
+// reduced across lanes and a leaf's records are read once. Bound by the records'
+// loads (32 bytes a node with one column).
+template <int CH>
 __global__ __launch_bounds__(64) void k_leaf_moments(const double2* __restrict__ rec, int stride, int wo, int N,
                                                      const double4* __restrict__ bounds, const int* __restrict__ perm,
-                                                     int p, double2* __restrict__ mom) {
-  const int b = blockIdx.x, lane = threadIdx.x;
-  const int leaf = perm[b];
+                                                     int nleaf, int p, double2* __restrict__ mom, size_t colstride,
+                                                     const int* __restrict__ active) {
+  if (active != nullptr && *active == 0) return;
+  const int b = blockIdx.x * 16 + (threadIdx.x >> 2), q = threadIdx.x & 3;
+  if (b >= nleaf) return;
   const double4 c = bounds[b];
-  double dx[kLeaf / 64], dy[kLeaf / 64], tx[kLeaf / 64], ty[kLeaf / 64];
+  const double inv = 1.0 / c.z;
+  const int j0 = perm[b] * kLeaf, j1 = min(N, j0 + kLeaf);
+  const int w0 = wo + blockIdx.y;
+  double ax[CH], ay[CH];
 #pragma unroll
-  for (int m = 0; m < kLeaf / 64; ++m) {
-    const int j = leaf * kLeaf + m * 64 + lane;
-    if (j < N) {
-      const double2 e = rec[(size_t)j * stride], w = rec[(size_t)j * stride + wo];
-      dx[m] = e.x - c.x;
-      dy[m] = e.y - c.y;
-      tx[m] = w.x;
-      ty[m] = w.y;
-    } else {
-      dx[m] = dy[m] = tx[m] = ty[m] = 0.0;
-    }
-  }
-  for (int k = 0; k < p; ++k) {
-    double sx = 0.0, sy = 0.0;
+  for (int k = 0; k < CH; ++k) ax[k] = ay[k] = 0.0;
+  constexpr int G = 8;   // nodes in flight
+  for (int j = j0; j < j1; j += G) {
+    double2 e[G], w[G];
 #pragma unroll
-    for (int m = 0; m < kLeaf / 64; ++m) {
-      sx += tx[m];
-      sy += ty[m];
-      const double nx = tx[m] * dx[m] - ty[m] * dy[m];
-      ty[m] = tx[m] * dy[m] + ty[m] * dx[m];
-      tx[m] = nx;
+    for (int g = 0; g < G; ++g) {
+      const double2* r = rec + (size_t)min(j + g, j1 - 1) * stride;
+      e[g] = r[0];
+      w[g] = j + g < j1 ? r[w0] : make_double2(0.0, 0.0);
     }
-    sx = wave_sum64(sx);
-    sy = wave_sum64(sy);
-    if (lane == 0) mom[(size_t)b * p + k] = make_double2(sx, sy);
-  }
-}
-
-// Moments of levels l0 + 1 .. l0 + nlev from those of level l0 in one launch:
-// a_k(parent) = sum over its two children sum_{q <= k} C(k, q) a_q(child) d^(k-q),
-// d = c_child - c_parent. One workgroup per box B of level l0 + nlev takes the
-// boxes of its subtree level by level (at most 2^kM2MLevels of the lowest),
-// the children's moments of each level in LDS, one thread per (parent, k).
-// C(k, q) comes from a table that the workgroup fills first (integers below
-// 2^53, exact). Each parent's sums run in the same order whatever the
-// grouping of levels.
-constexpr int kM2MLevels = 4;
-constexpr int kM2MThreads = 512;
-
-__global__ __launch_bounds__(kM2MThreads) void k_m2m_levels(const double4* __restrict__ bounds, LevelTable lt,
-                                                            int l0, int nlev, int p, double2* __restrict__ mom) {
-  __shared__ double2 sm[2][(1 << kM2MLevels) * kTreeMaxP];
-  __shared__ double binom[kTreeMaxP][kTreeMaxP];
-  const int B = blockIdx.x;
-  for (int k = threadIdx.x; k < p; k += blockDim.x) {
-    double c = 1.0;   // C(k, k), then C(k, q - 1) from C(k, q)
-    for (int q = k; q >= 0; --q) {
-      binom[k][q] = c;
-      c = c * (double)q / (double)(k - q + 1);
-    }
-  }
-  int c0 = B << nlev;   // first box of the subtree at the child level
-  int cnt = min(lt.nb[l0] - c0, 1 << nlev);
-  for (int i = threadIdx.x; i < cnt * p; i += blockDim.x) sm[0][i] = mom[(size_t)(lt.off[l0] + c0) * p + i];
-  __syncthreads();
-  int cur = 0;
-  for (int lev = 1; lev <= nlev; ++lev) {
-    const int l = l0 + lev;
-    const int p0 = B << (nlev - lev);
-    const int np = min(lt.nb[l] - p0, 1 << (nlev - lev));
-    for (int tid = threadIdx.x; tid < np * p; tid += blockDim.x) {
-      const int b = tid / p, k = tid - b * p;
-      const double4 cp = bounds[lt.off[l] + p0 + b];
-      double ax = 0.0, ay = 0.0;
-      for (int ch = 2 * b; ch < min(2 * b + 2, cnt); ++ch) {
-        const double4 cc = bounds[lt.off[l - 1] + c0 + ch];
-        const double ddx = cc.x - cp.x, ddy = cc.y - cp.y;
-        const double2* a = &sm[cur][ch * p];
-        double px = 1.0, py = 0.0;
-        for (int q = k; q >= 0; --q) {
-          const double2 aq = a[q];
-          const double tx = aq.x * px - aq.y * py, ty = aq.x * py + aq.y * px;
-          ax = __builtin_fma(binom[k][q], tx, ax);
-          ay = __builtin_fma(binom[k][q], ty, ay);
-          const double nx = px * ddx - py * ddy;
-          py = px * ddy + py * ddx;
-          px = nx;
-        }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const double x = (e[g].x - c.x) * inv, y = (e[g].y - c.y) * inv;
+      double px = 1.0, py = 0.0;   // ((eta - c)/r)^CH
+#pragma unroll
+      for (int m = 0; m < CH; ++m) {
+        const double nx = px * x - py * y;
+        py = px * y + py * x;
+        px = nx;
       }
-      sm[cur ^ 1][b * p + k] = make_double2(ax, ay);
-      mom[(size_t)(lt.off[l] + p0 + b) * p + k] = make_double2(ax, ay);
+      double tx = w[g].x, ty = w[g].y;
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        const double nx = tx * px - ty * py, ny = tx * py + ty * px;
+        tx = m < q ? nx : tx;
+        ty = m < q ? ny : ty;
+      }
+#pragma unroll
+      for (int k = 0; k < CH; ++k) {
+        ax[k] += tx;
+        ay[k] += ty;
+        const double nx = tx * x - ty * y;
+        ty = tx * y + ty * x;
+        tx = nx;
+      }
     }
-    __syncthreads();
-    cur ^= 1;
-    c0 = p0;
-    cnt = np;
+  }
+  double2* o = mom + blockIdx.y * colstride + (size_t)b * p + CH * q;
+#pragma unroll
+  for (int k = 0; k < CH; ++k)
+    if (CH * q + k < p) o[k] = make_double2(ax[k], ay[k]);
+}
+
+// Moments of levels l0 + 1 .. l0 + nlev from those of level l0, one wavefront per
+// 64 boxes of level l0, a lane per box with its moments in registers (P >= p of
+// them): a_k of a child in its parent's terms, scaled by (r_child/r_parent)^k and
+// shifted by e = (c_child - c_parent)/r_parent,
+//   sum_{q <= k} C(k, q) e^(k - q) a_q,
+// as repeated a_k += e a_(k-1) (p^2/2 complex products, no binomials), then added
+// to its sibling's (the lane whose box index differs in that level's bit): after
+// step s every lane of 2^s holds its common ancestor. The children come in through
+// LDS, as the 64 boxes' moments are contiguous. Bound by the arithmetic of one
+// wave (2100 products of p = 33 per level), six levels a launch.
+constexpr int kM2MLevels = 6;
+template <int P>
+__global__ __launch_bounds__(64) void k_m2m_levels(const double4* __restrict__ bounds, LevelTable lt, int l0, int nlev,
+                                                   int p, double2* __restrict__ mom, size_t colstride,
+                                                   const int* __restrict__ active) {
+  constexpr int H = P / 2;
+  __shared__ double2 child[64 * (H + 1)];   // half the terms of 64 boxes at a time
+  if (active != nullptr && *active == 0) return;
+  const int lane = threadIdx.x;
+  const int b0 = blockIdx.x * 64 + lane;
+  mom += blockIdx.y * colstride;
+  double ax[P], ay[P];
+  const bool has = b0 < lt.nb[l0];
+  {
+    const int first = blockIdx.x * 64, cnt = min(64, lt.nb[l0] - first) * H;
+    const double2* m = mom + (size_t)(lt.off[l0] + first) * p;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll 6
+      for (int i = lane; i < cnt; i += 64) {
+        const int q = i / H, k = i - q * H;
+        if (h * H + k < p) child[q * (H + 1) + k] = m[(size_t)q * p + h * H + k];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < H; ++k) {
+        const double2 v = has && h * H + k < p ? child[lane * (H + 1) + k] : make_double2(0.0, 0.0);
+        ax[h * H + k] = v.x;
+        ay[h * H + k] = v.y;
+      }
+      __syncthreads();
+    }
+  }
+  for (int s = 1; s <= nlev; ++s) {
+    const int l = l0 + s, cb = b0 >> (s - 1), pb = b0 >> s;
+    const bool live = cb < lt.nb[l - 1];
+    const double4 cc = bounds[lt.off[l - 1] + (live ? cb : 0)], cp = bounds[lt.off[l] + (live ? pb : 0)];
+    const double inv = 1.0 / cp.z;
+    const double ratio = live ? cc.z * inv : 0.0;
+    const double ex = live ? (cc.x - cp.x) * inv : 0.0, ey = live ? (cc.y - cp.y) * inv : 0.0;
+    double f = ratio;
+#pragma unroll
+    for (int k = 1; k < P; ++k) {
+      ax[k] *= f;
+      ay[k] *= f;
+      f *= ratio;
+    }
+#pragma unroll
+    for (int i = 1; i < P; ++i)
+#pragma unroll
+      for (int k = P - 1; k >= i; --k) {
+        ax[k] = __builtin_fma(ex, ax[k - 1], __builtin_fma(-ey, ay[k - 1], ax[k]));
+        ay[k] = __builtin_fma(ex, ay[k - 1], __builtin_fma(ey, ax[k - 1], ay[k]));
+      }
+    const int bit = 1 << (s - 1);
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      ax[k] += __shfl_xor(ax[k], bit, 64);
+      ay[k] += __shfl_xor(ay[k], bit, 64);
+    }
+    if ((lane & (2 * bit - 1)) == 0 && pb < lt.nb[l]) {
+      double2* o = mom + (size_t)(lt.off[l] + pb) * p;
+#pragma unroll
+      for (int k = 0; k < P; ++k)
+        if (k < p) o[k] = make_double2(ax[k], ay[k]);
+    }
   }
 }
 
-// One workgroup per (target tile, split): wave wv takes the entries
-// [seg[4 split + wv], seg[4 split + wv + 1]) of its tile's list. Entries >= 0
-// are far boxes: global index in bits 0..23, the number of terms this box
-// needs for this tile in bits 24..29; entries < 0 are near blocks ~blk of 64
-// nodes.
-// Partial sums of weight column col go to slot split, like the direct kernels'.
-template <int TPT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_tree(const DomDev* __restrict__ doms, const int* __restrict__ seg,
-                                              const int* __restrict__ list, const double4* __restrict__ bounds,
-                                              const double2* __restrict__ mom, int p, int splits, int col, int wcols,
-                                              const int* __restrict__ active, int lead, int ext) {
-  __shared__ double red[3][TPT][2][64];
+// ---------------------------------------------------- local expansions of tiles
+// Workgroups go to the eight XCDs in turn: with this order each takes a contiguous
+// run of the n items (n a multiple of 8), whose boxes and records its L2 shares.
+__device__ __forceinline__ int xcd_order(int b, int n) { return (b & 7) * (n >> 3) + (b >> 3); }
+
+constexpr int kLoc = kTreeMaxP;   // terms of a local expansion, in chunks of 16
+
+__device__ __forceinline__ double2 zmul(double2 a, double2 b) {
+  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+
+__device__ __forceinline__ double2 zsquare(double2 a) {
+  return make_double2(a.x * a.x - a.y * a.y, 2.0 * (a.x * a.y));
+}
+
+// z^j for j = 0..15 (from the bits of j), and z^8 in z8
+__device__ __forceinline__ double2 power16(double2 z, int j, double2& z8) {
+  const double2 one = make_double2(1.0, 0.0);
+  const double2 z2 = zsquare(z), z4 = zsquare(z2);
+  z8 = zsquare(z4);
+  double2 v = (j & 1) ? z : one;
+  v = zmul(v, (j & 2) ? z2 : one);
+  v = zmul(v, (j & 4) ? z4 : one);
+  return zmul(v, (j & 8) ? z8 : one);
+}
+
+// lane K of the lane's row of 16
+template <int K>
+__device__ __forceinline__ double row_lane(double v) {
+  const long long zero = 0, p = __builtin_bit_cast(long long, v);
+  const long long q = __builtin_amdgcn_update_dpp(zero, p, 0x150 + K, 0xf, 0xf, true);   // row_newbcast:K
+  return __builtin_bit_cast(double, q);
+}
+
+// s[ch] += sum over the four k from 4 G on (of the lane's chunk of 16) of
+// C(k + l, l) b_k, l = j + 16 ch, ch < NQ; tab: the table's row of the chunk's
+// first k at column j. The number of chunks is a template parameter so that the
+// table's reads go out together (with a test per chunk and term instead, the
+// kernel took 1.09 ms at 1089 x 4096 nodes).
+template <int G, int NQ, int NC>
+__device__ __forceinline__ void local_terms(double2 (&s)[3][NC], const double2 (&b)[NC], const double* tab) {
+  double t[4][NQ];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int ch = 0; ch < NQ; ++ch) t[k][ch] = tab[(4 * G + k) * kLoc + 16 * ch];
+  auto term = [&](const double (&tk)[NQ], int c, double bx, double by) {
+#pragma unroll
+    for (int ch = 0; ch < NQ; ++ch) {
+      s[ch][c].x = __builtin_fma(tk[ch], bx, s[ch][c].x);
+      s[ch][c].y = __builtin_fma(tk[ch], by, s[ch][c].y);
+    }
+  };
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    term(t[0], c, row_lane<4 * G>(b[c].x), row_lane<4 * G>(b[c].y));
+    term(t[1], c, row_lane<4 * G + 1>(b[c].x), row_lane<4 * G + 1>(b[c].y));
+    term(t[2], c, row_lane<4 * G + 2>(b[c].x), row_lane<4 * G + 2>(b[c].y));
+    term(t[3], c, row_lane<4 * G + 3>(b[c].x), row_lane<4 * G + 3>(b[c].y));
+  }
+}
+
+// s[ch] for ch < NQ from the moments a and x^j/D (X) of the row's box, pm terms
+template <int NQ, int NC>
+__device__ __forceinline__ void local_sums(double2 (&s)[3][NC], const double2 (&a)[3][NC], double2 X, double2 x16,
+                                           int pm, const double* tab) {
+#pragma unroll
+  for (int kc = 0; kc < 3; ++kc) {
+    if (16 * kc < pm) {
+      if (kc > 0) X = zmul(X, x16);
+      double2 b[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) b[c] = zmul(a[kc][c], X);
+      const double* tk = tab + 16 * kc * kLoc;
+      local_terms<0, NQ, NC>(s, b, tk);
+      if (16 * kc + 4 < pm) local_terms<1, NQ, NC>(s, b, tk);
+      if (16 * kc + 8 < pm) local_terms<2, NQ, NC>(s, b, tk);
+      if (16 * kc + 12 < pm) local_terms<3, NQ, NC>(s, b, tk);
+    }
+  }
+}
+
+// The local expansions of the target tiles for NC weight columns, one wavefront
+// per tile, four far boxes at a time, one per row of 16 lanes: lane j of a row
+// holds x^j/D and the terms a_k x^k/D of its box for k = j, j + 16, j + 32 and
+// forms L_l for l = j, j + 16, j + 32 (as many chunks of 16 as the largest p_e and
+// q_e of the four need), each term broadcast over the row by DPP. binom: C(k + l,
+// l), kLoc x kLoc. Bound by VALU issue (77 % of the cycles at 1089 x 4096 nodes):
+// about 320 instructions per four boxes, where evaluating them at 128 targets took
+// 870. loc: per tile and column kLoc coefficients, of which terms[tile] are used.
+template <int NC>
+__global__ __launch_bounds__(256) void k_tile_locals(const double4* __restrict__ tb, int tiles,
+                                                     const int64_t* __restrict__ faroff, const int2* __restrict__ far,
+                                                     const double4* __restrict__ bounds,
+                                                     const double2* __restrict__ mom, size_t colstride, int p,
+                                                     const double* __restrict__ binom, double2* __restrict__ loc,
+                                                     int* __restrict__ terms, const int* __restrict__ active) {
+  __shared__ double tab[kLoc * kLoc];
+  if (active != nullptr && *active == 0) return;
+  for (int i = threadIdx.x; i < kLoc * kLoc; i += 256) tab[i] = binom[i];
+  __syncthreads();
+  const int lane = threadIdx.x & 63, row = lane >> 4, j = lane & 15;
+  struct Box {
+    double4 bb;
+    double2 a[3][NC];
+    int pe, nq;
+  };
+  const int groups = ((tiles + 3) / 4 + 7) & ~7;
+  for (int gb = blockIdx.x; gb < groups; gb += gridDim.x) {
+    const int t = xcd_order(gb, groups) * 4 + (threadIdx.x >> 6);
+    if (t >= tiles) continue;
+    const double4 tt = tb[t];
+    const int e0 = __builtin_amdgcn_readfirstlane((int)faroff[t]);
+    const int e1 = __builtin_amdgcn_readfirstlane((int)faroff[t + 1]);
+    double2 acc[3][NC];
+    int most = 1;
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[ch][c] = make_double2(0.0, 0.0);
+    auto entry = [&](int e) { return far[max(0, min(e + row, e1 - 1))]; };
+    auto fetch = [&](int e, int2 ent) {
+      Box B;
+      const bool on = e + row < e1;
+      B.pe = on ? (ent.y & 0xff) : 0;
+      B.nq = on ? (ent.y >> 8) : 1;
+      B.bb = bounds[ent.x];
+      const double2* m = mom + (size_t)ent.x * p + j;
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          B.a[ch][c] = 16 * ch + j < B.pe ? m[c * colstride + 16 * ch] : make_double2(0.0, 0.0);
+      return B;
+    };
+    // the next four boxes' moments and the entries after them load during a step
+    Box next{};
+    int2 ent = make_int2(0, 0);
+    if (e0 < e1) {
+      next = fetch(e0, entry(e0));
+      ent = entry(e0 + 4);
+    }
+    for (int e = e0; e < e1; e += 4) {
+      const Box B = next;
+      if (e + 4 < e1) {
+        next = fetch(e + 4, ent);
+        ent = entry(e + 8);
+      }
+      const double4 bb = B.bb;
+      auto most_of = [&](int v) {
+        return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+                   max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+      };
+      const int pm = most_of(B.pe), qm = most_of(B.nq);
+      most = max(most, qm);
+      const double dx = tt.x - bb.x, dy = tt.y - bb.y;
+      const double d2 = __builtin_fma(dy, dy, dx * dx);
+      double inv = refine_rcp(d2);
+      inv = __builtin_fma(inv, __builtin_fma(-d2, inv, 1.0), inv);
+      const double2 v = make_double2(dx * inv, -dy * inv);   // 1/D
+      const double2 x = make_double2(v.x * bb.z, v.y * bb.z), y = make_double2(-v.x * tt.z, -v.y * tt.z);
+      double2 x8, y8;
+      const double2 X = zmul(power16(x, j, x8), v);
+      double2 yl = power16(y, j, y8);
+      double2 s[3][NC];
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) s[ch][c] = make_double2(0.0, 0.0);
+      const double2 x16 = zsquare(x8);
+      if (qm == 1) local_sums<1, NC>(s, B.a, X, x16, pm, tab + j);
+      else if (qm == 2) local_sums<2, NC>(s, B.a, X, x16, pm, tab + j);
+      else local_sums<3, NC>(s, B.a, X, x16, pm, tab + j);
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch)
+        if (ch < qm) {
+          if (ch > 0) yl = zmul(yl, zsquare(y8));
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            const double2 u = zmul(yl, s[ch][c]);
+            acc[ch][c].x += u.x;
+            acc[ch][c].y += u.y;
+          }
+        }
+    }
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        double2 u = acc[ch][c];
+        u.x += __shfl_xor(u.x, 16, 64);
+        u.y += __shfl_xor(u.y, 16, 64);
+        u.x += __shfl_xor(u.x, 32, 64);
+        u.y += __shfl_xor(u.y, 32, 64);
+        if (row == 0) loc[((size_t)t * NC + c) * kLoc + 16 * ch + j] = u;
+      }
+    if (lane == 0) terms[t] = e1 > e0 ? 16 * most : 0;
+  }
+}
+
+// One workgroup per (target tile, split), weight columns col .. col + NC - 1: wave
+// wv takes the range 4 split + wv of 4 splits equal ranges (in fours) of the
+// tile's near sources, 64-node blocks summed directly. In the first split wave t
+// adds the tile's local expansion at the targets of the lanes' t-th set. Partial
+// sums go to slot split, like the direct kernels'.
+#if defined(__HIP_DEVICE_COMPILE__)
+template <class T>
+using cptr = const __attribute__((address_space(4))) T*;   // read-only: scalar loads
+#else
+template <class T>
+using cptr = const T*;
+#endif
+
+template <int TPT, int NC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 8 : 6))) void k_tree(
+    const DomDev* __restrict__ doms, const int64_t* __restrict__ nearoff, const int* __restrict__ near_,
+    const double4* __restrict__ tb, const double2* __restrict__ loc, const int* __restrict__ terms, int items,
+    int splits, int col, int wcols, const int* __restrict__ active, int lead, int ext) {
+  __shared__ double red[4][TPT][NC][2][64];
   constexpr int kTile = 64 * TPT;
   const DomDev& D = doms[0];
-  if (active != nullptr && col >= lead && active[D.c0 + col - lead] == 0) return;
+  if (active != nullptr) {
+    bool any = false;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) any = any || col + c < lead || active[D.c0 + col + c - lead] != 0;
+    if (!any) return;
+  }
   const int N = D.N;
   const int NT = ext ? D.Nt : N;   // targets: the points tz (ext) or the nodes
-  const int tile = blockIdx.x / splits, g = blockIdx.x - tile * splits;
+  const int item = xcd_order(blockIdx.x, gridDim.x);
+  if (item >= items) return;
+  const int tile = item / splits, g = item - tile * splits;
   const int base = tile * kTile;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int stride = rec_stride(wcols);
-  const int wo = kRecHead + col;
+  const int stride = slim_stride(wcols);
+  const int wo = 1 + col;
   const gptr<const double2> rec = (gptr<const double2>)D.rec;
-  const gptr<const int> sg = (gptr<const int>)seg + (size_t)tile * (4 * splits + 1) + 4 * g + wv;
-  const int e0 = __builtin_amdgcn_readfirstlane(sg[0]);
-  const int e1 = __builtin_amdgcn_readfirstlane(sg[1]);
+  const cptr<int64_t> off = (cptr<int64_t>)nearoff + tile;
+  const int n0 = (int)off[0];
+  const int64_t units = 16 * (off[1] - n0);   // of four sources
+  const int u0 = (int)(units * (4 * g + wv) / (4 * splits)) * 4, u1 = (int)(units * (4 * g + wv + 1) / (4 * splits)) * 4;
 
   double2 tg[TPT];
   int ti[TPT];
@@ -268,102 +541,84 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
     ti[t] = base + t * 64 + lane;
     tg[t] = ext ? D.tz[min(ti[t], NT - 1)] : D.eta[min(ti[t], N - 1)];
   }
-  Acc<1, TPT> acc;
+  Acc<NC, TPT> acc;
 #pragma unroll
-  for (int t = 0; t < TPT; ++t) acc.x[t][0] = acc.y[t][0] = 0.0;
+  for (int t = 0; t < TPT; ++t)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc.x[t][c] = acc.y[t][c] = 0.0;
 
   auto plain = [&](int ja, int jb) {
     int j = ja;
     for (; j + 3 < jb; j += 4) {
       gptr<const double2> r = rec + (size_t)j * stride;
-      quad_step<1, TPT>(acc, tg, r, r + stride, r + 2 * stride, r + 3 * stride, wo);
+      quad_step<NC, TPT>(acc, tg, r, r + stride, r + 2 * stride, r + 3 * stride, wo);
     }
     for (; j + 1 < jb; j += 2) {
       gptr<const double2> r = rec + (size_t)j * stride;
-      pair_step<1, TPT>(acc, tg, r, r + stride, wo);
+      pair_step<NC, TPT>(acc, tg, r, r + stride, wo);
     }
-    if (j < jb) single_step<1, TPT>(acc, tg, ti, rec + (size_t)j * stride, wo, j, false);
+    if (j < jb) single_step<NC, TPT>(acc, tg, ti, rec + (size_t)j * stride, wo, j, false);
   };
 
-  const gptr<const int> ls = (gptr<const int>)list;
-  const gptr<const double4> bd = (gptr<const double4>)bounds;
-  const gptr<const double2> mm = (gptr<const double2>)mom;
-  for (int e = e0; e < e1; ++e) {
-    const int ent = ls[e];
-    if (ent >= 0) {
-      const int box = ent & 0xFFFFFF, pe = ent >> 24;
-      const double4 c = bd[box];
-      const gptr<const double2> a = mm + (size_t)box * p;
-      // Horner in u = 1/(z - c) for every target at once: each moment is loaded
-      // once for the TPT targets, four at a time
-      double ux[TPT], uy[TPT], sx[TPT], sy[TPT];
-#pragma unroll
-      for (int t = 0; t < TPT; ++t) {
-        const double dx = tg[t].x - c.x, dy = tg[t].y - c.y;
-        const double inv = refine_rcp(__builtin_fma(dy, dy, dx * dx));
-        ux[t] = dx * inv;
-        uy[t] = -dy * inv;
-        sx[t] = 0.0;
-        sy[t] = 0.0;
-      }
-      auto horner = [&](double2 ak) {
-#pragma unroll
-        for (int t = 0; t < TPT; ++t) {
-          const double nx = __builtin_fma(ux[t], sx[t], __builtin_fma(-uy[t], sy[t], ak.x));
-          sy[t] = __builtin_fma(ux[t], sy[t], __builtin_fma(uy[t], sx[t], ak.y));
-          sx[t] = nx;
-        }
-      };
-      int k = pe - 1;
-      for (; k >= 3; k -= 4) {
-        const double2 a0 = a[k], a1 = a[k - 1], a2 = a[k - 2], a3 = a[k - 3];
-        horner(a0);
-        horner(a1);
-        horner(a2);
-        horner(a3);
-      }
-      for (; k >= 0; --k) horner(a[k]);
-#pragma unroll
-      for (int t = 0; t < TPT; ++t) {
-        acc.x[t][0] += ux[t] * sx[t] - uy[t] * sy[t];
-        acc.y[t][0] += ux[t] * sy[t] + uy[t] * sx[t];
-      }
-    } else {
-      const int ja = (~ent) * 64, jb = min(N, ja + 64);
-      if (ext) {
-        plain(ja, jb);
-        continue;
-      }
-      plain(ja, min(jb, base));
-      const int ma = max(ja, base), mb = min(jb, base + kTile);
-      for (int j = ma; j < mb; ++j) single_step<1, TPT>(acc, tg, ti, rec + (size_t)j * stride, wo, j, true);
-      plain(max(ja, base + kTile), jb);
+  const cptr<int> nl = (cptr<int>)near_ + n0;
+  for (int u = u0; u < u1;) {
+    const int ue = min(u1, (u | 63) + 1);
+    const int blk = nl[u >> 6] * 64;
+    const int ja = blk + (u & 63), jb = min(N, blk + ((ue - 1) & 63) + 1);
+    u = ue;
+    if (ext) {
+      plain(ja, jb);
+      continue;
     }
+    plain(ja, min(jb, base));
+    const int ma = max(ja, base), mb = min(jb, base + kTile);
+    for (int j = ma; j < mb; ++j) single_step<NC, TPT>(acc, tg, ti, rec + (size_t)j * stride, wo, j, true);
+    plain(max(ja, base + kTile), jb);
   }
-
-  // fixed-order reduction over the four wavefronts
-  if (wv > 0) {
 #pragma unroll
-    for (int t = 0; t < TPT; ++t) {
-      red[wv - 1][t][0][lane] = acc.x[t][0];
-      red[wv - 1][t][1][lane] = acc.y[t][0];
+  for (int t = 0; t < TPT; ++t)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      red[wv][t][c][0][lane] = acc.x[t][c];
+      red[wv][t][c][1][lane] = acc.y[t][c];
     }
-  }
   __syncthreads();
-  if (wv == 0) {
+  if (wv >= TPT) return;
+  // wave t closes the sums of the t-th targets: the four waves' in order, then
+  // the local expansion (Horner in (z - c_t)/r_t)
+  double2 z = tg[0];
 #pragma unroll
-    for (int t = 0; t < TPT; ++t) {
-      double x = acc.x[t][0], y = acc.y[t][0];
+  for (int t = 1; t < TPT; ++t)
+    if (wv == t) z = tg[t];
+  const int i = base + wv * 64 + lane;
+  const double4 tt = ((cptr<double4>)tb)[tile];
+  const double inv = 1.0 / tt.z;
+  const double zx = (z.x - tt.x) * inv, zy = (z.y - tt.y) * inv;
+  const int nt = g == 0 ? ((cptr<int>)terms)[tile] : 0;
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        x += red[q][t][0][lane];
-        y += red[q][t][1][lane];
-      }
-      if (ti[t] < NT) D.parts[((size_t)g * wcols + col) * NT + ti[t]] = make_double2(x, y);
+  for (int c = 0; c < NC; ++c) {
+    double x = 0.0, y = 0.0;
+    const cptr<double2> L = (cptr<double2>)loc + ((size_t)tile * NC + c) * kLoc;
+    for (int l = nt - 4; l >= 0; l -= 4) {
+      const double2 l0 = L[l], l1 = L[l + 1], l2 = L[l + 2], l3 = L[l + 3];
+      auto horner = [&](double2 a) {
+        const double nx = __builtin_fma(zx, x, __builtin_fma(-zy, y, a.x));
+        y = __builtin_fma(zx, y, __builtin_fma(zy, x, a.y));
+        x = nx;
+      };
+      horner(l3);
+      horner(l2);
+      horner(l1);
+      horner(l0);
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      x += red[q][wv][c][0][lane];
+      y += red[q][wv][c][1][lane];
+    }
+    if (i < NT) D.parts[((size_t)g * wcols + col + c) * NT + i] = make_double2(x, y);
   }
 }
-
 
 // ------------------------------------------------ order along a Hilbert curve
 // The points (or the centres of boxes) in the order of their positions along a
@@ -584,24 +839,17 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint32_t* __restrict
   }
 }
 
-__global__ void k_invert(const int* __restrict__ perm, int n, int* __restrict__ inv) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < n) inv[perm[s]] = s;
-}
-
 // --------------------------------------------------------- interaction lists
 // One wavefront per target tile walks the boxes from the root, up to 64 of one
 // level at a time (the stack holds at most 128 boxes of each level, since a level
 // is pushed to only when nothing deeper is left). A box separated from the tile
-// by (1 + theta)(r_t + r_b) becomes a far entry of the order its own ratio needs,
-// a leaf that is not its near blocks, any other box its two children. The first
-// pass counts the entries and their cost (far 4 p_e + 24, near source 13, the
-// tile's own window 16: integers, so every sum is exact), the second writes them
-// and cuts the list into nseg ranges of about equal cost. Bound by the latency of
-// the box loads; 0.58 + 0.65 ms for the 9 million entries of 1089 x 4096 nodes (on
-// 16 host threads, with the copies both ways, the lists took most of the 40 ms
-// that a solve spent outside the GPU).
-constexpr int kTreeLevels = 24;   // leaves < 2^23
+// by (1 + theta)(r_t + r_b) becomes a far entry {box, p_e | chunks of 16 of q_e << 8}
+// with the orders its own ratios need, a leaf that is not a near block (the index
+// of its 64 nodes), any other box its two children. The first pass counts, the
+// second writes. Bound by the latency of the box loads (on 16 host threads, with
+// the copies both ways, the lists of 1089 x 4096 nodes took most of the 40 ms that
+// a solve spent outside the GPU).
+constexpr int kTreeLevels = 26;   // leaves < 2^25
 
 struct TreeWalk {
   const double4* bounds;
@@ -609,15 +857,16 @@ struct TreeWalk {
   const int* perm;
   int off[kTreeLevels + 1], nb[kTreeLevels + 1];
   double thr[kTreeMaxP + 1];   // far_tol^(1/k)
+  double qthr[2];              // (far_tol/64)^(1/16), ^(1/32)
   double f2;                   // (1 + theta)^2
-  int levels, p, N, NT, kt, tiles, nseg, ext;
+  int levels, p, N, NT, kt, tiles, ext;
 };
 
-__device__ __forceinline__ int64_t wave_prefix(int64_t v, int lane, int64_t* total) {
-  int64_t inc = v;
+__device__ __forceinline__ int wave_prefix(int v, int lane, int* total) {
+  int inc = v;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
-    const int64_t o = __shfl_up(inc, off, 64);
+    const int o = __shfl_up(inc, off, 64);
     if (lane >= off) inc += o;
   }
   *total = __shfl(inc, 63, 64);
@@ -625,117 +874,98 @@ __device__ __forceinline__ int64_t wave_prefix(int64_t v, int lane, int64_t* tot
 }
 
 template <bool FILL>
-__global__ __launch_bounds__(256) void k_tree_lists(TreeWalk W, int64_t* __restrict__ count, int64_t* __restrict__ cost,
-                                                    double* __restrict__ work, int* __restrict__ list,
-                                                    int* __restrict__ seg) {
-  __shared__ int stk[4][128 * kTreeLevels];   // level in bits 24.., box of the level below
+__global__ __launch_bounds__(256) void k_tree_lists(TreeWalk W, int64_t* __restrict__ nfar,
+                                                    int64_t* __restrict__ nnear, double* __restrict__ work, int2* __restrict__ far,
+                                                    int* __restrict__ near_) {
+  extern __shared__ int stk[];                // 128 levels boxes per wave, deepest level last
+  __shared__ int left[4][kTreeLevels];        // boxes of each level on the stack
   __shared__ double thr[kTreeMaxP + 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (threadIdx.x <= (unsigned)W.p) thr[threadIdx.x] = W.thr[threadIdx.x];
   __syncthreads();
   const int t = blockIdx.x * 4 + wv;
   if (t >= W.tiles) return;
-  int* st = stk[wv];
+  int* st = stk + wv * 128 * W.levels;
+  int* cnt = left[wv];
   const double4 tt = W.tb[t];
-  const int base = t * W.kt;
-  const double nt = (double)min(W.kt, W.NT - base);
-  const int64_t start = FILL ? count[t] : 0, tot = FILL ? cost[t] : 0;
-  int64_t n = 0, acc = 0;
+  const double nt = (double)min(W.kt, W.NT - t * W.kt);
+  int64_t f = FILL ? nfar[t] : 0, n = FILL ? nnear[t] : 0;
   double wk = 0.0;
-  int sp = 1;
-  if (lane == 0) st[0] = (W.levels - 1) << 24;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  int l = W.levels - 1, sp = 1;   // level of the stack's top, boxes on it
+  if (lane < W.levels) cnt[lane] = lane == l ? 1 : 0;
+  if (lane == 0) st[0] = 0;
+  auto fence = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  fence();
   while (sp > 0) {
-    // the run of entries of the top's level, at most 64
-    const int mine = lane < sp ? st[sp - 1 - lane] : -1;
-    const int l = __shfl(mine, 0, 64) >> 24;
-    const unsigned long long other = ~__ballot(lane < sp && (mine >> 24) == l);
-    const int take = other ? __ffsll((unsigned long long)other) - 1 : 64;
+    const int have = __builtin_amdgcn_readfirstlane(cnt[l]);
+    const int take = min(64, have);
+    const int b = lane < take ? st[sp - 1 - lane] : 0;
     sp -= take;
-    const bool on = lane < take;
-    const int b = mine & 0xffffff;
     const int g = W.off[l] + b;
-    int kind = 0;   // 1 far, 2 near leaf, 3 children
-    int pe = 2, nblk = 0, j0 = 0, nch = 0;
-    int64_t c = 0;
-    if (on) {
+    bool is_far = false, is_near = false;
+    int pe = 2, nq = 1, nch = 0;
+    if (lane < take) {
       const double4 bb = W.bounds[g];
       const double dx = tt.x - bb.x, dy = tt.y - bb.y, rr = tt.z + bb.z;
       const double d2 = dx * dx + dy * dy;
       if (d2 > W.f2 * rr * rr) {
-        kind = 1;
-        const double rho = bb.z / (sqrt(d2) - tt.z);
+        is_far = true;
+        const double d = sqrt(d2), rho = bb.z / (d - tt.z), rq = tt.z / (d - bb.z);
         while (pe < W.p && rho > thr[pe]) ++pe;
-        c = 4 * pe + 24;
-        if (!FILL) wk += nt * (8.0 * pe + 8.0);
+        nq = rq <= W.qthr[0] ? 1 : (rq <= W.qthr[1] ? 2 : 3);
+        if (!FILL) wk += 64.0 * pe * nq;
       } else if (l == 0) {
-        kind = 2;
-        j0 = W.perm[b] * kLeaf;
-        nblk = (min(W.N - j0, kLeaf) + 63) / 64;
-        const int j1 = min(W.N, j0 + kLeaf);
-        const int ov = W.ext ? 0 : max(0, min(j1, base + W.kt) - max(j0, base));
-        c = 13 * (j1 - j0 - ov) + 16 * ov;
-        if (!FILL) wk += 16.0 * (nt * (j1 - j0) - ov);
+        is_near = true;
+        if (!FILL) wk += 16.0 * nt * min(kLeaf, W.N - W.perm[b] * kLeaf);
       } else {
-        kind = 3;
         nch = 2 * b + 1 < W.nb[l - 1] ? 2 : 1;
       }
     }
-    int64_t tn, tc, th;
-    const int64_t pn = wave_prefix(kind == 1 ? 1 : nblk, lane, &tn);
-    const int64_t pc = wave_prefix(c, lane, &tc);
-    const int64_t ph = wave_prefix(nch, lane, &th);
-    if (FILL && (kind == 1 || kind == 2)) {
-      int64_t e = n + pn, a = acc + pc;
-      int* sg = seg + (size_t)t * (W.nseg + 1);
-      const int ne = kind == 1 ? 1 : nblk;
-      for (int q = 0; q < ne; ++q, ++e) {
-        int64_t ce = c;
-        int ent = (pe << 24) | g;
-        if (kind == 2) {
-          const int b0 = j0 + 64 * q, b1 = min(W.N, b0 + 64);
-          const int ov = W.ext ? 0 : max(0, min(b1, base + W.kt) - max(b0, base));
-          ce = 13 * (b1 - b0 - ov) + 16 * ov;
-          ent = ~(b0 / 64);
-        }
-        list[start + e] = ent;
-        // the cuts tot k / nseg that fall into this entry go before it or, past
-        // its middle, behind it
-        for (int64_t k = a * W.nseg / tot + 1; k < W.nseg && k * tot <= (a + ce) * W.nseg; ++k)
-          sg[k] = (int)(start + (2 * k * tot <= (2 * a + ce) * W.nseg ? e : e + 1));
-        a += ce;
-      }
+    const unsigned long long below = (1ull << lane) - 1ull, mf = __ballot(is_far), mn = __ballot(is_near);
+    if (FILL) {
+      if (is_far) far[f + __popcll(mf & below)] = make_int2(g, pe | (nq << 8));
+      if (is_near) near_[n + __popcll(mn & below)] = W.perm[b];
     }
+    f += __popcll(mf);
+    n += __popcll(mn);
+    int th;
+    const int ph = wave_prefix(nch, lane, &th);
     // a box's children keep their order when they come off the stack
-    if (kind == 3)
-      for (int q = 0; q < nch; ++q) st[sp + (int)th - 1 - (int)ph - q] = ((l - 1) << 24) | (2 * b + q);
-    sp += (int)th;
-    n += tn;
-    acc += tc;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int q = 0; q < nch; ++q) st[sp + th - 1 - ph - q] = 2 * b + q;
+    sp += th;
+    if (lane == 0) {
+      cnt[l] = have - take;
+      if (th > 0) cnt[l - 1] = th;   // (nothing of that level was left)
+    }
+    fence();
+    if (th > 0) --l;
+    else while (l + 1 < W.levels && __builtin_amdgcn_readfirstlane(cnt[l]) == 0) ++l;
   }
   if constexpr (!FILL) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) wk += __shfl_xor(wk, off, 64);
     if (lane == 0) {
-      count[t] = n;
-      cost[t] = acc;
-      work[t] = wk;
+      nfar[t] = f;
+      nnear[t] = n;
+      work[t] = wk + (f > 0 ? 8.0 * kLoc * nt : 0.0);
     }
-  } else if (lane == 0) {
-    int* sg = seg + (size_t)t * (W.nseg + 1);
-    sg[0] = (int)start;
-    sg[W.nseg] = (int)(start + n);
   }
 }
 
-// counts to offsets; the list's length to host-mapped memory
-__global__ __launch_bounds__(1024) void k_list_offsets(int64_t* __restrict__ count, int tiles, int64_t* total) {
-  block_scan<int64_t>(count, tiles, total);
+// counts to offsets, the totals behind them and in host-mapped memory
+__global__ __launch_bounds__(1024) void k_list_offsets(int64_t* __restrict__ nfar, int64_t* __restrict__ nnear,
+                                                       int tiles, int64_t* total) {
+  int64_t* v = blockIdx.x == 0 ? nfar : nnear;
+  int64_t sum = 0;
+  block_scan<int64_t>(v, tiles, &sum);
+  if (threadIdx.x == 0) {
+    v[tiles] = sum;
+    total[blockIdx.x] = sum;
+  }
 }
 
 }  // namespace
@@ -769,11 +999,6 @@ hipError_t launch_hilbert_order(const double2* pts, const double4* boxes, int n,
   return hipGetLastError();
 }
 
-hipError_t launch_invert(const int* perm, int n, int* inv, hipStream_t st) {
-  k_invert<<<(n + 255) / 256, 256, 0, st>>>(perm, n, inv);
-  return hipGetLastError();
-}
-
 static TreeWalk tree_walk(const TreeListArgs& A) {
   TreeWalk W{};
   W.bounds = A.bounds;
@@ -786,6 +1011,8 @@ static TreeWalk tree_walk(const TreeListArgs& A) {
   // rho^k <= far_tol exactly when rho <= far_tol^(1/k): the order of a far
   // entry is the least k >= 2 (at most p) whose threshold its ratio meets
   for (int k = 1; k <= A.p; ++k) W.thr[k] = std::pow(A.far_tol, 1.0 / k);
+  W.qthr[0] = std::pow(A.far_tol / 64.0, 1.0 / 16.0);
+  W.qthr[1] = std::pow(A.far_tol / 64.0, 1.0 / 32.0);
   W.f2 = (1.0 + A.theta) * (1.0 + A.theta);
   W.levels = A.levels;
   W.p = A.p;
@@ -793,22 +1020,21 @@ static TreeWalk tree_walk(const TreeListArgs& A) {
   W.NT = A.NT;
   W.kt = A.kt;
   W.tiles = A.tiles;
-  W.nseg = A.nseg;
   W.ext = A.ext ? 1 : 0;
   return W;
 }
 
-hipError_t launch_tree_count(const TreeListArgs& A, int64_t* count, int64_t* cost, double* work, int64_t* total,
+hipError_t launch_tree_count(const TreeListArgs& A, int64_t* nfar, int64_t* nnear, double* work, int64_t* total,
                              hipStream_t st) {
   if (A.levels < 1 || A.levels > kTreeLevels || A.p > kTreeMaxP) return hipErrorInvalidValue;
-  k_tree_lists<false><<<(A.tiles + 3) / 4, 256, 0, st>>>(tree_walk(A), count, cost, work, nullptr, nullptr);
-  k_list_offsets<<<1, 1024, 0, st>>>(count, A.tiles, total);
+  k_tree_lists<false><<<(A.tiles + 3) / 4, 256, 4 * 128 * sizeof(int) * A.levels, st>>>(tree_walk(A), nfar, nnear, work, nullptr, nullptr);
+  k_list_offsets<<<2, 1024, 0, st>>>(nfar, nnear, A.tiles, total);
   return hipGetLastError();
 }
 
-hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* count, int64_t* cost, int* list, int* seg,
+hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* nfar, int64_t* nnear, int2* far, int* near_,
                             hipStream_t st) {
-  k_tree_lists<true><<<(A.tiles + 3) / 4, 256, 0, st>>>(tree_walk(A), count, cost, nullptr, list, seg);
+  k_tree_lists<true><<<(A.tiles + 3) / 4, 256, 4 * 128 * sizeof(int) * A.levels, st>>>(tree_walk(A), nfar, nnear, nullptr, far, near_);
   return hipGetLastError();
 }
 
@@ -818,8 +1044,8 @@ hipError_t launch_leaf_boxes(const double2* eta, int N, int nleaf, double4* leaf
 }
 
 hipError_t launch_box_bounds(const double2* eta, int N, const int* level_off, const int* level_nb, int levels,
-                             const double4* leafbox, const int* perm, const int* invp, double4* bbox,
-                             unsigned long long* rbits, double4* out, hipStream_t st) {
+                             const double4* leafbox, const int* perm, double4* bbox, unsigned long long* rbits,
+                             double4* out, hipStream_t st) {
   if (levels < 1 || levels > 32) return hipErrorInvalidValue;
   k_bbox_gather<<<(level_nb[0] + 255) / 256, 256, 0, st>>>(leafbox, perm, level_nb[0], bbox);
   hipError_t e = hipGetLastError();
@@ -834,43 +1060,68 @@ hipError_t launch_box_bounds(const double2* eta, int N, const int* level_off, co
   if ((e = hipGetLastError()) != hipSuccess) return e;
   LevelTable lv{};
   for (int l = 0; l < levels; ++l) lv.off[l] = level_off[l];
-  k_box_radii<<<level_nb[0], 256, 0, st>>>(eta, N, lv, levels, invp, out, rbits);
+  k_box_radii<<<(level_nb[0] + kRadiiWaves - 1) / kRadiiWaves, 64 * kRadiiWaves, 0, st>>>(eta, N, lv, levels,
+                                                                                         level_nb[0], perm, out, rbits);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   k_box_finish<<<(nbox + 255) / 256, 256, 0, st>>>(rbits, nbox, out);
   return hipGetLastError();
 }
 
-hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int N, const double4* bounds, const int* perm,
-                               const int* level_off, const int* level_nb, int levels, int p, double2* mom,
-                               hipStream_t st) {
-  k_leaf_moments<<<level_nb[0], 64, 0, st>>>(rec, stride, wo, N, bounds, perm, p, mom);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols, int N, const double4* bounds,
+                               const int* perm, const int* level_off, const int* level_nb, int levels, int p,
+                               double2* mom, size_t colstride, const int* active, hipStream_t st) {
   if (levels > 32 || p > kTreeMaxP) return hipErrorInvalidValue;
   LevelTable lt{};
   for (int l = 0; l < levels; ++l) {
     lt.off[l] = level_off[l];
     lt.nb[l] = level_nb[l];
   }
-  for (int l = 0; l + 1 < levels;) {
-    const int nlev = min(kM2MLevels, levels - 1 - l);
-    k_m2m_levels<<<level_nb[l + nlev], kM2MThreads, 0, st>>>(bounds, lt, l, nlev, p, mom);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    l += nlev;
-  }
-  return hipSuccess;
+  // instances for 12, 24, 36 and 48 terms (four lanes' shares of a leaf's moments)
+  auto run = [&](auto terms) {
+    constexpr int P = decltype(terms)::value;
+    const dim3 grid((unsigned)((level_nb[0] + 15) / 16), (unsigned)ncols);
+    k_leaf_moments<P / 4><<<grid, 64, 0, st>>>(rec, stride, wo, N, bounds, perm, level_nb[0], p, mom, colstride,
+                                               active);
+    for (int l = 0; l + 1 < levels;) {
+      const int nlev = std::min(kM2MLevels, levels - 1 - l);
+      const dim3 g((unsigned)((level_nb[l] + 63) / 64), (unsigned)ncols);
+      k_m2m_levels<P><<<g, 64, 0, st>>>(bounds, lt, l, nlev, p, mom, colstride, active);
+      l += nlev;
+    }
+  };
+  if (p <= 12) run(std::integral_constant<int, 12>{});
+  else if (p <= 24) run(std::integral_constant<int, 24>{});
+  else if (p <= 36) run(std::integral_constant<int, 36>{});
+  else run(std::integral_constant<int, 48>{});
+  return hipGetLastError();
 }
 
-hipError_t launch_tree_eval(const DomDev* doms, int tiles, int tpt, const int* seg, const int* list,
-                            const double4* bounds, const double2* mom, int p, int splits, int col, int wcols,
-                            const int* active, int lead, bool ext, hipStream_t st) {
-  const unsigned grid = (unsigned)tiles * (unsigned)splits;
+std::vector<double> tree_binomials() {
+  std::vector<double> b((size_t)kLoc * kLoc);
+  for (int k = 0; k < kLoc; ++k)
+    for (int l = 0; l < kLoc; ++l)
+      b[k * kLoc + l] = k == 0 || l == 0 ? 1.0 : b[(k - 1) * kLoc + l] + b[k * kLoc + l - 1];
+  return b;
+}
+
+hipError_t launch_tree_eval(const DomDev* doms, int tiles, int tpt, const TreeEvalArgs& A, int ncols, int splits,
+                            int col, int wcols, const int* active, int lead, bool ext, const int* flag,
+                            hipStream_t st) {
+  const int groups = ((tiles + 3) / 4 + 7) & ~7, items = tiles * splits;
+  const unsigned lg = (unsigned)std::min(groups, 4096), grid = (unsigned)((items + 7) & ~7);
   const int e = ext ? 1 : 0;
-  if (tpt == 2)
-    k_tree<2><<<grid, 256, 0, st>>>(doms, seg, list, bounds, mom, p, splits, col, wcols, active, lead, e);
+  if (ncols == 2)
+    k_tile_locals<2><<<lg, 256, 0, st>>>(A.tb, tiles, A.faroff, A.far, A.bounds, A.mom, A.colstride, A.p, A.binom,
+                                         A.loc, A.terms, nullptr);
   else
-    k_tree<1><<<grid, 256, 0, st>>>(doms, seg, list, bounds, mom, p, splits, col, wcols, active, lead, e);
+    k_tile_locals<1><<<lg, 256, 0, st>>>(A.tb, tiles, A.faroff, A.far, A.bounds, A.mom, A.colstride, A.p, A.binom,
+                                         A.loc, A.terms, flag);
+  auto run = [&](auto kern) {
+    kern<<<grid, 256, 0, st>>>(doms, A.nearoff, A.near, A.tb, A.loc, A.terms, items, splits, col, wcols, active, lead,
+                               e);
+  };
+  if (tpt == 2) ncols == 2 ? run(k_tree<2, 2>) : run(k_tree<2, 1>);
+  else ncols == 2 ? run(k_tree<1, 2>) : run(k_tree<1, 1>);
   return hipGetLastError();
 }
 

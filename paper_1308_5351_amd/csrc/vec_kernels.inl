@@ -65,6 +65,25 @@ __device__ __forceinline__ void record_head(double2* rj, double2 eta, double2 ep
 __device__ __forceinline__ double2 cmul_conj(double2 a, double2 b) {
   return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
+// The record of node j among wcols weight columns: its offset from the far-form
+// tile's centre (not needed in the treecode's slim records {eta, w..}), its head,
+// and weight column q with its product w conj(eta')
+__device__ __forceinline__ double2 record_offset(const DomDev& D, int j) {
+  return D.slim ? make_double2(0.0, 0.0) : eta_rel(D, j);
+}
+__device__ __forceinline__ void put_head(const DomDev& D, int wcols, int j, double2 ep) {
+  if (D.slim) D.rec[(size_t)j * slim_stride(wcols)] = D.eta[j];
+  else record_head(D.rec + (size_t)j * rec_stride(wcols), D.eta[j], ep);
+}
+__device__ __forceinline__ void put_weight(const DomDev& D, int wcols, int j, int q, double2 w, double2 ep) {
+  if (D.slim) {
+    D.rec[(size_t)j * slim_stride(wcols) + 1 + q] = w;
+  } else {
+    double2* rj = D.rec + (size_t)j * rec_stride(wcols) + kRecHead + q;
+    rj[0] = w;
+    rj[wcols] = cmul_conj(w, ep);
+  }
+}
 __device__ __forceinline__ double diagv(const DomDev& D, int sel, int i) {
   return sel == D_B ? D.dB[i] : (sel == D_D ? D.dD[i] : (sel == D_E ? D.e[i] : (sel == D_BU ? D.bu[i] : 0.0)));
 }
@@ -216,7 +235,6 @@ __global__ __launch_bounds__(kT) void k_weights(const DomDev* __restrict__ doms,
   if (k >= D.m1) return;
   if (active && !active[c]) return;
   const int wcols = lead + D.ncols;
-  const int stride = rec_stride(wcols);
   const double* xr = x + C.off + (size_t)k * D.n;
   double acc = 0.0;
   for (int p = threadIdx.x; p < D.n; p += blockDim.x) {
@@ -229,16 +247,11 @@ __global__ __launch_bounds__(kT) void k_weights(const DomDev* __restrict__ doms,
       D.w1[j] = w;
       continue;
     }
-    const double2 ep = eta_rel(D, j);
-    double2* rj = D.rec + (size_t)j * stride;
-    rj[kRecHead + lead + C.r] = w;
-    rj[kRecHead + wcols + lead + C.r] = cmul_conj(w, ep);
+    const double2 ep = record_offset(D, j);
+    put_weight(D, wcols, j, lead + C.r, w, ep);
     if (C.r == 0) {
-      record_head(rj, D.eta[j], ep);
-      if (lead) {
-        rj[kRecHead] = cf;
-        rj[kRecHead + wcols] = cmul_conj(cf, ep);
-      }
+      put_head(D, wcols, j, ep);
+      if (lead) put_weight(D, wcols, j, 0, cf, ep);
     }
   }
   if (mean) {
@@ -257,11 +270,9 @@ __device__ __forceinline__ void stage_weight(const DomDev& D, int csel, int r, i
     D.w1[j] = w;
     if (!D.rec32) return;   // mixed products take the records
   }
-  const double2 ep = eta_rel(D, j);
-  double2* rj = D.rec + (size_t)j * rec_stride(wcols);
-  rj[kRecHead + r] = w;
-  rj[kRecHead + wcols + r] = cmul_conj(w, ep);
-  if (head) record_head(rj, D.eta[j], ep);
+  const double2 ep = record_offset(D, j);
+  put_weight(D, wcols, j, r, w, ep);
+  if (head) put_head(D, wcols, j, ep);
 }
 
 // Sums of a chunk's entries over each component of n entries that it meets:
@@ -290,11 +301,9 @@ __global__ void k_lead_records(const DomDev* __restrict__ doms, int csel) {
     D.w1[j] = cf;
     return;
   }
-  const double2 ep = eta_rel(D, j);
-  double2* rj = D.rec + (size_t)j * rec_stride(1);
-  record_head(rj, D.eta[j], ep);
-  rj[kRecHead] = cf;
-  rj[kRecHead + 1] = cmul_conj(cf, ep);
+  const double2 ep = record_offset(D, j);
+  put_head(D, 1, j, ep);
+  put_weight(D, 1, j, 0, cf, ep);
 }
 
 // records of one domain from column-major complex weights w (N x ncols)
@@ -306,14 +315,9 @@ __global__ void k_pack_records(const DomDev* __restrict__ doms, const double2* _
     D.w1[j] = w[j];
     return;
   }
-  const double2 ep = eta_rel(D, j);
-  double2* rj = D.rec + (size_t)j * rec_stride(ncols);
-  record_head(rj, D.eta[j], ep);
-  for (int r = 0; r < ncols; ++r) {
-    const double2 v = w[(size_t)r * D.N + j];
-    rj[kRecHead + r] = v;
-    rj[kRecHead + ncols + r] = cmul_conj(v, ep);
-  }
+  const double2 ep = record_offset(D, j);
+  put_head(D, ncols, j, ep);
+  for (int r = 0; r < ncols; ++r) put_weight(D, ncols, j, r, w[(size_t)r * D.N + j], ep);
 }
 
 // ------------------------------- conformal maps onto the disc with slits
@@ -415,17 +419,11 @@ __global__ void k_fcau_records(const DomDev* __restrict__ doms, const double2* _
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= D.N) return;
   const int wcols = 1 + nrhs;
-  const double2 ep = eta_rel(D, j);
+  const double2 ep = record_offset(D, j);
   const double2 p = D.etap[j];
-  double2* rj = D.rec + (size_t)j * rec_stride(wcols);
-  record_head(rj, D.eta[j], ep);
-  rj[kRecHead] = p;
-  rj[kRecHead + wcols] = cmul_conj(p, ep);
-  for (int q = 0; q < nrhs; ++q) {
-    const double2 w = cmul(f[(size_t)q * D.N + j], p);
-    rj[kRecHead + 1 + q] = w;
-    rj[kRecHead + wcols + 1 + q] = cmul_conj(w, ep);
-  }
+  put_head(D, wcols, j, ep);
+  put_weight(D, wcols, j, 0, p, ep);
+  for (int q = 0; q < nrhs; ++q) put_weight(D, wcols, j, 1 + q, cmul(f[(size_t)q * D.N + j], p), ep);
 }
 
 // a / b without overflow of |b|^2 (scaled division)

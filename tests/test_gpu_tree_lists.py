@@ -98,3 +98,31 @@ def test_equal_and_nonfinite_points(gk, nz):
         assert bool(torch.isnan(t[bad].real).all())
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("far_tol", [1e-15, 1e-8, 1e-5, 1e-2])
+@pytest.mark.parametrize("kind", ["circles", "random"])
+def test_expansion_orders(gk, kind, far_tol):
+    """Every instance of the moments' and conversions' kernels (p = 48, 21, 13 and 6 terms of a box at most), one
+    and three weight columns, tiles small beside their boxes (circles) and as large (random nodes: up to 48 terms of
+    a tile's expansion). A box's truncation is at most 7/3 far_tol on its own side and 7/3 far_tol/64 on the tile's."""
+    N = 20011
+    eta, w = _circles(N, 300, 5)
+    if kind == "random":
+        r = np.random.default_rng(8)
+        eta = torch.from_numpy(r.uniform(-1, 1, N) + 1j * r.uniform(-1, 1, N)).cuda()
+    w3 = torch.stack([w, w.conj() * 0.5, w.roll(7)], dim=1)
+    ctx = gk.Context(0)
+    try:
+        S = ctx.cauchy_sum(eta, w, far_tol=far_tol)
+        S3 = ctx.cauchy_sum(eta, w3, far_tol=far_tol)
+        rows = torch.from_numpy(np.random.default_rng(1).integers(0, N, 512)).cuda()
+        d = eta[rows, None] - eta[None, :]
+        q = torch.where(d == 0, 0.0, 1.0 / d)
+        for got, x in ((S, w), (S3[:, 0], w), (S3[:, 1], w3[:, 1]), (S3[:, 2], w3[:, 2])):
+            ref, size = q @ x, q.abs() @ x.abs()
+            worst = float(((got[rows] - ref).abs() / size).max())
+            print(f"[tree] {kind} far_tol {far_tol:g}: {worst:.2e}", flush=True)
+            assert worst <= 2.4 * far_tol + 256 * EPS
+    finally:
+        ctx.close()
