@@ -515,7 +515,7 @@ __device__ __forceinline__ void pair_item(gptr<const double2> rec, gptr<const fl
         quad_step<NR, TPT>(acc, tg, r, r + stride, r + 2 * stride, r + 3 * stride, wo);
       } else {
         // four wide records would not fit in scalar registers together
-        if constexpr (NR == 8 && TPT % 2 == 0) {
+        if constexpr (NR != 4 && TPT % 2 == 0) {
           // one reciprocal for two sources and two targets (4 columns: the
           // extra registers cost a wave per SIMD)
           pair_step_t2<NR, TPT>(acc, tg, r, r + stride, wo);
@@ -963,8 +963,9 @@ void launch_k(const DomDev* doms, const int4* items, int nitems, int lead, int d
   k_pairs<NR, TPT, MODE><<<grid, 256, 0, st>>>(doms, items, nitems, lead, data, active);
 }
 
-// FP64: one launch. Mixed: 1-2 columns in one M_MIXED launch; 4-8 columns as
-// k_far then M_NEAR over the same items (the second adds to the first's sums).
+// FP64: one launch. Mixed: 1-2 columns in one M_MIXED launch; 3-8 columns, as a
+// group of 8, in k_far then M_NEAR over the same items (the second adds to the
+// first's sums).
 template <int NR, int TPT>
 void launch_t(const DomDev* doms, const int4* items, int nitems, int lead, int data, bool mixed, bool ext,
               const int* active, int grid, hipStream_t st) {
@@ -972,10 +973,10 @@ void launch_t(const DomDev* doms, const int4* items, int nitems, int lead, int d
     launch_k<NR, TPT, M_EXT>(doms, items, nitems, lead, data, active, grid, st);
   } else if (!mixed) {
     launch_k<NR, TPT, M_FP64>(doms, items, nitems, lead, data, active, grid, st);
-  } else if constexpr (NR >= 4) {
+  } else if constexpr (NR == 8) {
     k_far<NR, TPT><<<grid, 256, 0, st>>>(doms, items, nitems, lead, data, active);
     launch_k<NR, TPT, M_NEAR>(doms, items, nitems, lead, data, active, grid, st);
-  } else {
+  } else if constexpr (NR <= 2) {
     launch_k<NR, TPT, M_MIXED>(doms, items, nitems, lead, data, active, grid, st);
   }
 }
@@ -1000,8 +1001,8 @@ int occupancy_of() {
 template <int NR, int TPT>
 int occupancy_t(bool mixed) {
   if (!mixed) return occupancy_of<NR, TPT, M_FP64>();
-  if constexpr (NR >= 4) return occupancy_of<NR, TPT, M_NEAR>();
-  return occupancy_of<NR, TPT, M_MIXED>();
+  if constexpr (NR <= 2) return occupancy_of<NR, TPT, M_MIXED>();
+  return occupancy_of<8, TPT, M_NEAR>();
 }
 
 template <int NR>
@@ -1014,14 +1015,16 @@ int occupancy_w(int tpt, bool mixed) {
 int pairs_blocks_per_cu(int width, int tpt, bool mixed) {
   // resident 256-thread workgroups per CU of each pair-kernel variant (register
   // and LDS limits), cached after the first query
-  static int cache[4][2][2] = {};
-  const int wi = width >= 8 ? 0 : (width >= 4 ? 1 : (width >= 2 ? 2 : 3));
-  const int ti = tpt == 2 ? 1 : 0;
-  int& v = cache[wi][ti][mixed ? 1 : 0];
+  static int cache[8][2][2] = {};
+  int& v = cache[width - 1][tpt == 2 ? 1 : 0][mixed ? 1 : 0];
   if (v == 0) {
-    switch (wi) {
-      case 0: v = occupancy_w<8>(tpt, mixed); break;
-      case 1: v = occupancy_w<4>(tpt, mixed); break;
+    switch (width) {
+      case 8: v = occupancy_w<8>(tpt, mixed); break;
+      case 7: v = occupancy_w<7>(tpt, mixed); break;
+      case 6: v = occupancy_w<6>(tpt, mixed); break;
+      case 5: v = occupancy_w<5>(tpt, mixed); break;
+      case 4: v = occupancy_w<4>(tpt, mixed); break;
+      case 3: v = occupancy_w<3>(tpt, mixed); break;
       case 2: v = occupancy_w<2>(tpt, mixed); break;
       default: v = occupancy_w<1>(tpt, mixed); break;
     }
@@ -1032,11 +1035,15 @@ int pairs_blocks_per_cu(int width, int tpt, bool mixed) {
 hipError_t launch_pairs(const DomDev* doms, const int4* items, int nitems, int width, int tpt, int lead, int data,
                         bool mixed, bool ext, const int* active, hipStream_t st) {
   if (nitems <= 0) return hipSuccess;
-  if (ext && mixed) return hipErrorInvalidValue;
+  if ((ext && mixed) || width < 1 || width > 8 || (mixed && width > 2 && width < 8)) return hipErrorInvalidValue;
   const int grid = nitems;
   switch (width) {
     case 8: launch_w<8>(doms, items, nitems, tpt, lead, data, mixed, ext, active, grid, st); break;
+    case 7: launch_w<7>(doms, items, nitems, tpt, lead, data, mixed, ext, active, grid, st); break;
+    case 6: launch_w<6>(doms, items, nitems, tpt, lead, data, mixed, ext, active, grid, st); break;
+    case 5: launch_w<5>(doms, items, nitems, tpt, lead, data, mixed, ext, active, grid, st); break;
     case 4: launch_w<4>(doms, items, nitems, tpt, lead, data, mixed, ext, active, grid, st); break;
+    case 3: launch_w<3>(doms, items, nitems, tpt, lead, data, mixed, ext, active, grid, st); break;
     case 2: launch_w<2>(doms, items, nitems, tpt, lead, data, mixed, ext, active, grid, st); break;
     default: launch_w<1>(doms, items, nitems, tpt, lead, data, mixed, ext, active, grid, st); break;
   }

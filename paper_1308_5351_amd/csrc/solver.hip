@@ -227,7 +227,17 @@ int64_t slots_of(const gnk_ctx* c) { return (int64_t)c->num_cu * 4 * 8; }   // 4
 enum Pattern { P_GM = 0, P_SETUP = 1, P_LEAD = 2, P_GM_MIXED = 3 };
 constexpr int kLead[4] = {0, 1, 1, 0};
 constexpr int kData[4] = {1, 1, 0, 1};
-constexpr int kWidths[4] = {8, 4, 2, 1};
+constexpr int kMaxWidth = 8;   // widest column group of the pair kernels (lists are kept by width - 1)
+
+// Width of the next column group of an FP64 product with `left` columns to go:
+// the fewest groups of at most 8 columns, of nearly equal widths, since the
+// distances and the reciprocal of a pair are formed once per group (11 x 600
+// nodes, 5 columns: one launch 43 us, groups of 4 and 1 41 + 22 us; the solve
+// 1.95 and 1.54 ms, with 7 columns 2.51 and 1.75).
+int group_width(int left) {
+  const int groups = (left + kMaxWidth - 1) / kMaxWidth;
+  return (left + groups - 1) / groups;
+}
 
 struct PairShape {
   int tpt = 1;
@@ -246,8 +256,8 @@ struct Batch {
   bool adjoint = false;
   bool second = false;   // eta'' and A' present (adjoint or no-subtraction operators)
   struct ItemSet {
-    int4* d[4] = {nullptr, nullptr, nullptr, nullptr};
-    int cnt[4] = {0, 0, 0, 0};
+    int4* d[kMaxWidth] = {};
+    int cnt[kMaxWidth] = {};
     double pair_cols = 0, flops = 0, pairs1 = 0;
     bool built = false;
   } sets[4];
@@ -310,39 +320,59 @@ void check_domain(gnk_ctx* c, const gnk_domain* d, bool adjoint, bool second = f
   }
 }
 
-// Single-domain split plan: among the split counts whose waves fill whole
-// rounds of the wave slots of the pair-kernel variant best (within 1% of the
-// best fill), the fewest that give two rounds, else the most rounds; at least
-// 128 sources per workgroup, at most 64 splits. Workgroups take unequal times
-// (near source tiles cost more than far ones) and a second round lets the
-// dispatcher even that out; more rounds shorten the products a little more
-// but every split adds partial sums that the consumer has to read (measured
-// at N = 17408: 123 us per product at 15 splits, 118 us at 30, 115 us at 45,
-// with the reading growing by about 0.3 us per split).
-int64_t single_max_splits(int64_t N) { return std::max<int64_t>(1, std::min<int64_t>(64, N / 128)); }
+// Single-domain launch plan. Two targets per lane from 1024 targets on (2048 with
+// several columns): half the source loads and a reciprocal shared by more pairs,
+// against half the workgroups, which the source splits make up for (fbie solve, one
+// column, one / two targets: 1087 / 958 us at N = 4800, 616 / 559 at 1024; three
+// columns at N = 10240 2.81 / 2.27 ms; four at 1200 627 / 650 us).
+//
+// Small domains (32 splits would not fill the wave slots of the kernel variant
+// twice): as many splits as leave 64 sources each, at most 32 (8 / 16 / 32 / 64
+// splits at N = 3072: 593 / 593 / 586 / 632 us, at 6144 1002 / 944 / 916 / 996; 4 / 8 /
+// 16 at N = 512: 535 / 488 / 484), but no round of the slots that is left less than
+// half full (11 x 600 nodes, 2 columns: 29 splits 1114 us, 32 of 1.08 rounds 1186;
+// 8 columns: 19 splits 1853 us, 32 of 1.62 rounds 1784).
+//
+// Larger ones: among the split counts whose waves fill whole rounds of the slots
+// best (within 1% of the best fill), the fewest that give two rounds, else the most
+// rounds; at least 128 sources per workgroup, at most 64 splits. Workgroups take
+// unequal times (near source tiles cost more than far ones) and a second round lets
+// the dispatcher even that out; more rounds shorten the products a little more but
+// every split adds partial sums that the consumer has to read (measured at
+// N = 17408: 123 us per product at 15 splits, 118 us at 30, 115 us at 45, with the
+// reading growing by about 0.3 us per split). That rule and the two targets of full
+// slots also hold where partial sums are scarce (the fixed scratch of
+// gnk_cauchy_sum_noalloc, a workspace cap), so that what fitted there still fits,
+// and for mixed products, whose chunks are whole 256-node groups.
 // Nt targets against Ns sources (the nodes, or separate points for the Cauchy
 // integral at interior points)
 void plan_pairs(gnk_ctx* c, int64_t Nt, int64_t Ns, int align, int width, bool mixed, int* tpt, int* chunk,
                 int* splits) {
-  int t = ((Nt + 127) / 128) * 64 >= slots_of(c) ? 2 : 1;
+  const bool roomy = !mixed && !c->arena && !c->ws_limit;
+  int t = roomy ? (Nt >= (width == 1 ? 1024 : 2048) ? 2 : 1) : (((Nt + 127) / 128) * 64 >= slots_of(c) ? 2 : 1);
   if (const char* s = getenv("GNK_CAUCHY_TPT")) t = atoi(s) == 2 ? 2 : 1;
   // wave slots of the variant that runs the products (its register use sets
   // how many workgroups fit on a CU)
   const int64_t slots = (int64_t)c->num_cu * 4 * pairs_blocks_per_cu(width, t, mixed);
   const int64_t tiles = (Nt + 64 * t - 1) / (64 * t);
-  const int64_t max_s = single_max_splits(Ns);
-  std::vector<double> score((size_t)max_s + 1, 0.0), rounds((size_t)max_s + 1, 0.0);
-  double best = 0.0;
-  for (int64_t s = 1; s <= max_s; ++s) {
-    rounds[s] = (double)(tiles * s * 4) / (double)slots;
-    score[s] = rounds[s] / std::ceil(rounds[s]) * std::min(1.0, rounds[s]);
-    best = std::max(best, score[s]);
-  }
+  const int64_t few = std::max<int64_t>(1, std::min<int64_t>(32, Ns / 64));
   int64_t bs = 0;
-  for (int64_t s = 1; s <= max_s && !bs; ++s)
-    if (score[s] >= best - 0.01 && rounds[s] >= 1.9) bs = s;
-  for (int64_t s = max_s; s >= 1 && !bs; --s)
-    if (score[s] >= best - 0.01) bs = s;
+  if (roomy && (double)(tiles * few * 4) < 1.9 * (double)slots) {
+    bs = tiles * few * 4 > slots && 2 * tiles * few * 4 < 3 * slots ? slots / (4 * tiles) : few;
+  } else {
+    const int64_t max_s = std::max<int64_t>(1, std::min<int64_t>(64, Ns / 128));
+    std::vector<double> score((size_t)max_s + 1, 0.0), rounds((size_t)max_s + 1, 0.0);
+    double best = 0.0;
+    for (int64_t s = 1; s <= max_s; ++s) {
+      rounds[s] = (double)(tiles * s * 4) / (double)slots;
+      score[s] = rounds[s] / std::ceil(rounds[s]) * std::min(1.0, rounds[s]);
+      best = std::max(best, score[s]);
+    }
+    for (int64_t s = 1; s <= max_s && !bs; ++s)
+      if (score[s] >= best - 0.01 && rounds[s] >= 1.9) bs = s;
+    for (int64_t s = max_s; s >= 1 && !bs; --s)
+      if (score[s] >= best - 0.01) bs = s;
+  }
   if (const char* s = getenv("GNK_CAUCHY_SPLITS")) bs = std::max(1, atoi(s));
   int64_t ch = (Ns + bs - 1) / bs;
   ch = (ch + align - 1) / align * align;
@@ -451,7 +481,7 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
     c0 += ncols[d];
     if (ndom == 1 && shape.chunk == 0) {
       int t, ch, sp;
-      const int width = ncols[d] >= 8 ? 8 : (ncols[d] >= 4 ? 4 : (ncols[d] >= 2 ? 2 : 1));
+      const int width = mixed ? std::min(ncols[d], kMaxWidth) : group_width(ncols[d]);
       plan_single(c, D.N, align, width, mixed, &t, &ch, &sp);
       B.shape.tpt = t;
       D.chunk = ch;
@@ -544,7 +574,7 @@ void build_items(gnk_ctx* c, Batch& B, int p) {
   std::vector<int> order(B.ndom);
   for (int d = 0; d < B.ndom; ++d) order[d] = d;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return B.dom[a].N > B.dom[b].N; });
-  std::vector<int4> lists[4];
+  std::vector<int4> lists[kMaxWidth];
   S.pair_cols = S.flops = S.pairs1 = 0;
   for (int d : order) {
     const DomDev& D = B.dom[d];
@@ -558,19 +588,14 @@ void build_items(gnk_ctx* c, Batch& B, int p) {
     if (wcols == 1) S.pairs1 += pairs;
     int r0 = 0;
     while (r0 < wcols) {
-      int wi = 3;
-      for (int k = 0; k < 4; ++k)
-        if (kWidths[k] <= wcols - r0) {
-          wi = k;
-          break;
-        }
-      int w = kWidths[wi];
-      int code = r0;
-      if (p == P_GM_MIXED && wcols - r0 >= 3 && wcols - r0 < 8) {
-        // padded 8-column group of the remaining columns (width in bits 20..)
-        wi = 0;
-        w = wcols - r0;
-        code = r0 | (w << 20);
+      int w = group_width(wcols - r0);
+      int code = r0, wi = w - 1;
+      if (p == P_GM_MIXED) {
+        // groups of 8, 2 or 1 columns, 3-7 remaining ones as a padded group of 8
+        // (width in bits 20..)
+        w = std::min(wcols - r0, kMaxWidth);
+        wi = w >= 3 ? kMaxWidth - 1 : w - 1;
+        if (w >= 3 && w < kMaxWidth) code = r0 | (w << 20);
       }
       // Records larger than half an XCD's L2 (4 MB): split-major, so the
       // workgroups resident together read one source range (measured at
@@ -601,7 +626,7 @@ void build_items(gnk_ctx* c, Batch& B, int p) {
       r0 += w;
     }
   }
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < kMaxWidth; ++k) {
     S.cnt[k] = (int)lists[k].size();
     S.d[k] = upload(c, "b_items" + std::to_string(p) + "_" + std::to_string(k), lists[k]);
   }
@@ -802,9 +827,9 @@ void pairs(gnk_ctx* c, Batch& B, int p, bool mixed, const int* active) {
   }
   const bool sym = use_sym(B, p, mixed);
   if (sym) HIPCHK(c, launch_pairs_sym(B.d_dom, B.sym.items, B.sym.cnt, B.sym.plan, active, c->stream));
-  for (int k = 0; k < 4; ++k) {
+  for (int k = kMaxWidth - 1; k >= 0; --k) {
     if (sym || !S.cnt[k]) continue;
-    HIPCHK(c, launch_pairs(B.d_dom, S.d[k], S.cnt[k], kWidths[k], B.shape.tpt, kLead[p], kData[p], mixed,
+    HIPCHK(c, launch_pairs(B.d_dom, S.d[k], S.cnt[k], k + 1, B.shape.tpt, kLead[p], kData[p], mixed,
                            B.dom[0].tz != nullptr, active, c->stream));
   }
   if (c->prof) {
@@ -1178,7 +1203,7 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
     auto fp = [&](double v) { uint64_t b; memcpy(&b, &v, 8); u(b); };
     u((uint64_t)use_mixed); u((uint64_t)k);
     const Batch::ItemSet& IS = B.sets[use_mixed ? P_GM_MIXED : P_GM];
-    for (int q = 0; q < 4; ++q) { pt(IS.d[q]); u((uint64_t)IS.cnt[q]); }
+    for (int q = 0; q < kMaxWidth; ++q) { pt(IS.d[q]); u((uint64_t)IS.cnt[q]); }
     u((uint64_t)B.shape.tpt); pt(B.d_dom); pt(B.d_col); u((uint64_t)B.ndom); u((uint64_t)B.maxN);
     u((uint64_t)(B.dom[0].tz != nullptr));
     pt(B.sym.items); u((uint64_t)B.sym.cnt); u((uint64_t)B.sym.on);
@@ -2109,9 +2134,8 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
     d.eta = eta;
     d.etap = d.A = etap;
     const int wcols = 1 + nrhs;
-    const int width = wcols >= 8 ? 8 : (wcols >= 4 ? 4 : (wcols >= 2 ? 2 : 1));
     int t, ch, sp;
-    plan_pairs(c, nz, N, 16, width, false, &t, &ch, &sp);
+    plan_pairs(c, nz, N, 16, group_width(wcols), false, &t, &ch, &sp);
     // tiles of 64 points for the treecode: they cover more of the plane than as many
     // nodes of a curve, and smaller tiles meet fewer near sources (289 x 1024 nodes
     // at 200003 points: 1600 and 3070 near sources per point, 1.08 and 1.19 ms)
