@@ -73,3 +73,30 @@ def test_interior_values_of_every_width(ctx, nz, cols):
     ref = (q @ f) / den
     bound = 256 * EPS * (size @ f.abs() + ref.abs() * size.sum(1, keepdim=True)) / den.abs()
     assert bool(((got.reshape(nz, cols) - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("n", [6, 10, 70, 254, 258, 510, 514, 600, 2046, 3838, 3840, 3842, 5000, 7680, 7690])
+@pytest.mark.parametrize("cols", [1, 2])
+def test_circulant_of_other_lengths(ctx, n, cols):
+    """The direct circulant product at the ends of its tiles of 256 outputs and 3840
+    inputs, with inputs that do not fill the last four and an odd number of vectors:
+    n terms of two roundings each, 1e-13 of the largest sum of their sizes. The
+    reference's column takes its arguments on the near side, cot(pi d/n) =
+    -cot(pi (n - d)/n): beyond, rounding of pi d/n costs the dense oracle's largest
+    entries a relative n eps, 9e-14 of the sum at n = 7690."""
+    import workloads as wl
+    from paper_1308_5351_amd import gnk
+    m1 = 3
+    print(f"[circulant] n={n} cols={cols}", flush=True)
+    dom = wl.circles_unbounded(n, [0j, 3.0 + 0.5j, -2.5 + 2.0j], [1.0, 0.7, 0.5])
+    x = _columns(m1 * n, cols, n).real.contiguous()
+    y = ctx.apply(gnk.DeviceDomain.from_host(dom), gnk.OP_LHAT, x).reshape(m1 * n, cols)
+    d = np.arange(n)
+    near = np.minimum(d, n - d)
+    col = np.where(2 * d > n, -1.0, 1.0) * (-1.0) ** d / np.tan(np.pi * np.where(near == 0, 0.5 * n, near) / n) / n
+    col[[0, n // 2]] = 0.0
+    L = torch.from_numpy(col).cuda()[torch.from_numpy((d[:, None] - d[None, :]) % n).cuda()]
+    for k in range(m1):
+        blk = slice(k * n, (k + 1) * n)
+        err = (y[blk] - L @ x[blk]).abs().max() / (L.abs() @ x[blk].abs()).max()
+        assert float(err) < 1e-13, k
