@@ -10,21 +10,27 @@
 // u_i (v_i - v_j)) and z_t = c_t for fC. Grouping the terms by v (groups g with
 // vector V_g and U_g = sum_{t in g} z_t u_t, P = sum_g U_g V_g), the partial
 // derivatives of F = sum_{i != j} K_ij W_ij need only row and column sums:
-//   R1_i = sum_j K_ij W_ij = -kappa a_i [sum_g U_g,i S1(b V_g)_i - P_i S1(b)_i]
-//   R2_i = sum_j K_ij W_ij / (eta_j - eta_i) = kappa a_i [sum_g U_g,i S2(b V_g)_i - P_i S2(b)_i]
-//   T1_i = sum_g V_g,i S1(a U_g)_i - S1(a P)_i,   T2_i likewise with S2
+// and, with S1(w)_i = sum_{j != i} w_j/(eta_i - eta_j) (the matrix E of
+// eq. (e:fmm-E)), S2 the same with the square of the difference, kappa = 2/n,
+// q = 1/(eta_i - eta_j) and e_g = V_g,i - V_g,j,
+//   R1_i = sum_j K_ij W_ij = kappa a_i sum_g U_g,i F1_g,i,   F1_g,i = sum_j b_j e_g q
+//   R2_i = sum_j K_ij W_ij / (eta_j - eta_i) = -kappa a_i sum_g U_g,i F2_g,i  (q^2 for q)
+//   T1_i = sum_g V_g,i S1(a U_g)_i - S1(a P)_i = sum_j X q,  X = sum_g (a U_g)_j e_g
+//   T2_i = sum_j X q^2,
 //   dF/deta_i = R2_i - kappa b_i T2_i,  dF/deta'_i = kappa T1_i / A_i,
-//   dF/dA_i = (R1_i - kappa b_i T1_i) / A_i,
-// kappa = 2/n, S1(w)_i = sum_{j != i} w_j/(eta_i - eta_j) (the matrix E of
-// eq. (e:fmm-E)) and S2(w)_i = sum_{j != i} w_j/(eta_i - eta_j)^2. The
-// gradients returned are conj(dF/dz) = ds/dRe z + i ds/dIm z.
+//   dF/dA_i = (R1_i - kappa b_i T1_i) / A_i.
+// The gradients returned are conj(dF/dz) = ds/dRe z + i ds/dIm z.
 //
-// The first- and second-order sums share each pair's reciprocal q = 1/d
-// (q^2 costs one complex square). The kernel follows the operator pair
-// kernel: wave-uniform source records {eta_j, w_j,0..} fetched with scalar
-// loads, four wavefronts splitting the sources of a workgroup and adding
-// their sums through LDS in a fixed order, partial sums per source split
-// added in a fixed order by the epilogue (bitwise reproducible).
+// Working with the differences e_g (real) leaves 2 + 2 G complex sums per node, 44
+// FP64 operations per pair for the two groups of a solve's gradient; the sums of the
+// 2 G + 2 weights b V_g, b, a U_g, a P, each in both orders, took 65 and cancel where
+// V varies slowly. The kernel is bound by the FP64 units: two targets per lane share
+// one reciprocal and every fetched source, sources are wave-uniform records by scalar
+// loads (the next one's in flight), only the tile's own 128 sources run the masked
+// loop; four wavefronts split a workgroup's sources and add their sums through LDS in
+// a fixed order, as the epilogue adds the source splits. Groups go two per launch
+// plane (the last plane of an odd count one). N = 33792, two groups: 2.36 ms before,
+// 1.65 now, 30 of the card's 34 T FP64 operations/s.
 #include <cstdint>
 
 #include "gnk_device.h"
@@ -45,140 +51,212 @@ __device__ __forceinline__ double2 zadd(double2 a, double2 b) { return make_doub
 __device__ __forceinline__ double2 zsub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ double2 zscale(double s, double2 a) { return make_double2(s * a.x, s * a.y); }
 
-// records: rec[j*stride] = eta_j, rec[j*stride + 1 + q] = w_q,j for q < nw
-// (nw = 2G + 2 columns: b V_g, b, a U_g, a P), padded with zeros to nwpad.
+// Records of plane z (groups 2z and, if there, 2z + 1), at rec + kGeomRec N z:
+// {eta, b, a U_g, a U_g', V_g, V_g'} (10 doubles; a missing group has zeros).
+constexpr int kGeomRec = 10;
 __global__ void k_geom_weights(const double2* __restrict__ eta, const double2* __restrict__ etap,
                                const double2* __restrict__ A, int N, const GeomTerm* __restrict__ terms,
-                               const GeomGroup* __restrict__ groups, int G, int nwpad, double2* __restrict__ rec,
-                               double2* __restrict__ Ut, double2* __restrict__ P) {
+                               const GeomGroup* __restrict__ groups, int G, double* __restrict__ rec,
+                               double2* __restrict__ Ut) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= N) return;
-  const int stride = 1 + nwpad;
-  double2* r = rec + (size_t)j * stride;
   const double2 a = A[j];
   const double2 b = zdiv(etap[j], a);
-  r[0] = eta[j];
-  double2 p = make_double2(0.0, 0.0);
-  for (int g = 0; g < G; ++g) {
-    const GeomGroup gr = groups[g];
-    double2 U = make_double2(0.0, 0.0);
-    for (int t = gr.t0; t < gr.t1; ++t) U = zadd(U, zscale(terms[t].u[j], terms[t].z));
-    const double v = gr.v[j];
-    Ut[(size_t)g * N + j] = U;
-    p = zadd(p, zscale(v, U));
-    r[1 + g] = zscale(v, b);
-    r[1 + G + 1 + g] = zmul(a, U);
+  for (int g = 0; g < G; g += 2) {
+    double2* r = reinterpret_cast<double2*>(rec + ((size_t)(g >> 1) * N + j) * kGeomRec);
+    double v[2] = {0.0, 0.0};
+    r[0] = eta[j];
+    r[1] = b;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      double2 U = make_double2(0.0, 0.0);
+      if (g + h < G) {
+        const GeomGroup gr = groups[g + h];
+        for (int t = gr.t0; t < gr.t1; ++t) U = zadd(U, zscale(terms[t].u[j], terms[t].z));
+        v[h] = gr.v[j];
+        Ut[(size_t)(g + h) * N + j] = U;
+      }
+      r[2 + h] = zmul(a, U);
+    }
+    r[4] = make_double2(v[0], v[1]);
   }
-  r[1 + G] = b;
-  r[1 + 2 * G + 1] = zmul(a, p);
-  for (int q = 2 * G + 2; q < nwpad; ++q) r[1 + q] = make_double2(0.0, 0.0);
-  P[j] = p;
 }
 
-// First- and second-order sums of NR weight columns (q0 = blockIdx.z * NR) for
-// the 64 targets of blockIdx.x over the sources of split blockIdx.y:
-//   parts[((g*nw + q)*2 + o)*N + i] = sum_{j in split g, j != i} w_qj / (eta_i - eta_j)^(o+1)
-template <int NR>
-__global__ __launch_bounds__(256) void k_cauchy12(const double2* __restrict__ rec_, int stride, int N, int nw,
-                                                  int chunk, double2* __restrict__ parts_) {
-  __shared__ double red[3][4 * NR][64];
-  gptr<const double2> rec = (gptr<const double2>)rec_;
-  gptr<double2> parts = (gptr<double2>)parts_;
+struct GeomSrc {
+  double2 eta, b, x[2];
+  double v[2];
+};
+__device__ __forceinline__ GeomSrc load_src(gptr<const double2> r) {
+  const double2 v = r[4];
+  return GeomSrc{r[0], r[1], {r[2], r[3]}, {v.x, v.y}};
+}
+
+// sums of one target: T1, T2, then F1, F2 of each group
+template <int NG>
+struct GeomAcc {
+  double2 s[2 + 2 * NG];
+};
+
+// one source against the lane's two targets; MASK: a target's own node counts nothing
+template <int NG, bool MASK>
+__device__ __forceinline__ void geom_step(GeomAcc<NG> (&acc)[2], const double2 (&z)[2], const double (&vt)[2][NG],
+                                          const GeomSrc& s, bool own0, bool own1) {
+  double dx[2], dy[2], m[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    dx[t] = z[t].x - s.eta.x;
+    dy[t] = z[t].y - s.eta.y;
+    m[t] = __builtin_fma(dy[t], dy[t], dx[t] * dx[t]);
+  }
+  if (MASK) {
+    m[0] = own0 ? 1.0 : m[0];
+    m[1] = own1 ? 1.0 : m[1];
+  }
+  const double R = refine_rcp(m[0] * m[1]);
+  const double i0 = R * m[1], i1 = R * m[0];
+  m[0] = MASK && own0 ? 0.0 : i0;
+  m[1] = MASK && own1 ? 0.0 : i1;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const double qx = dx[t] * m[t], ny = dy[t] * m[t];   // q = qx - i ny
+    double2(&S)[2 + 2 * NG] = acc[t].s;
+    double e[NG];
+    double2 X;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      e[g] = vt[t][g] - s.v[g];
+      X.x = g ? __builtin_fma(s.x[g].x, e[g], X.x) : s.x[g].x * e[g];
+      X.y = g ? __builtin_fma(s.x[g].y, e[g], X.y) : s.x[g].y * e[g];
+    }
+    const double yx = __builtin_fma(X.y, ny, X.x * qx), yy = __builtin_fma(X.y, qx, -X.x * ny);
+    S[0].x += yx;
+    S[0].y += yy;
+    S[1].x = __builtin_fma(yx, qx, __builtin_fma(yy, ny, S[1].x));
+    S[1].y = __builtin_fma(yy, qx, __builtin_fma(-yx, ny, S[1].y));
+    const double bx = __builtin_fma(s.b.y, ny, s.b.x * qx), by = __builtin_fma(s.b.y, qx, -s.b.x * ny);
+    const double cx = __builtin_fma(by, ny, bx * qx), cy = __builtin_fma(by, qx, -bx * ny);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      S[2 + 2 * g].x = __builtin_fma(bx, e[g], S[2 + 2 * g].x);
+      S[2 + 2 * g].y = __builtin_fma(by, e[g], S[2 + 2 * g].y);
+      S[3 + 2 * g].x = __builtin_fma(cx, e[g], S[3 + 2 * g].x);
+      S[3 + 2 * g].y = __builtin_fma(cy, e[g], S[3 + 2 * g].y);
+    }
+  }
+}
+
+// The sums of the 128 targets of blockIdx.x over the sources of split blockIdx.y and
+// the groups of plane blockIdx.z (from `plane0` on):
+// parts[((g nz + z) 6 + k) N + i], k: T1, T2, F1, F2 (, F1', F2')
+template <int NG>
+__global__ __launch_bounds__(256) void k_geom_sums(const double* __restrict__ rec_, int N, int plane0, int nz,
+                                                   int chunk, double2* __restrict__ parts_) {
+  __shared__ double2 red[3][2][64];
+  constexpr int kStride = kGeomRec / 2;
+  const int zp = plane0 + blockIdx.z;
+  gptr<const double2> rec = (gptr<const double2>)rec_ + (size_t)zp * N * kStride;
+  gptr<double2> parts = (gptr<double2>)parts_ + ((size_t)blockIdx.y * nz + zp) * 6 * N;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int i = blockIdx.x * 64 + lane;
-  const int g = blockIdx.y;
-  const int q0 = blockIdx.z * NR;
-  const double2 ti = rec[(size_t)min(i, N - 1) * stride];
-  const int jb0 = g * chunk;
+  const int base = blockIdx.x * 128;
+  const int i0 = base + lane, i1 = i0 + 64;
+  // targets past the end repeat node N - 1, of this tile, and skip it as source
+  const int n0 = min(i0, N - 1), n1 = min(i1, N - 1);
+  double2 z[2];
+  double vt[2][NG];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const gptr<const double2> r = rec + (size_t)(t ? n1 : n0) * kStride;
+    z[t] = r[0];
+    const double2 v = r[4];
+    vt[t][0] = v.x;
+    if constexpr (NG > 1) vt[t][1] = v.y;
+  }
+  const int jb0 = blockIdx.y * chunk;
   const int jb1 = min(N, jb0 + chunk);
   const int wchunk = (chunk + 3) >> 2;
   const int j0 = min(jb1, jb0 + wv * wchunk);
   const int j1 = min(jb1, j0 + wchunk);
-  double s1x[NR], s1y[NR], s2x[NR], s2y[NR];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) s1x[r] = s1y[r] = s2x[r] = s2y[r] = 0.0;
-  for (int j = j0; j < j1; ++j) {
-    gptr<const double2> rj = rec + (size_t)j * stride;
-    const double2 e = rj[0];
-    const double dx = ti.x - e.x, dy = ti.y - e.y;
-    double m = refine_rcp(__builtin_fma(dy, dy, dx * dx));
-    m = (j == i) ? 0.0 : m;
-    const double qx = dx * m, qy = -dy * m;                        // 1/d
-    const double px = __builtin_fma(qx, qx, -qy * qy), py = 2.0 * qx * qy;   // 1/d^2
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      const double2 w = rj[1 + q0 + r];
-      s1x[r] = __builtin_fma(w.x, qx, s1x[r]);
-      s1x[r] = __builtin_fma(-w.y, qy, s1x[r]);
-      s1y[r] = __builtin_fma(w.x, qy, s1y[r]);
-      s1y[r] = __builtin_fma(w.y, qx, s1y[r]);
-      s2x[r] = __builtin_fma(w.x, px, s2x[r]);
-      s2x[r] = __builtin_fma(-w.y, py, s2x[r]);
-      s2y[r] = __builtin_fma(w.x, py, s2y[r]);
-      s2y[r] = __builtin_fma(w.y, px, s2y[r]);
+  GeomAcc<NG> acc[2] = {};
+  auto plain = [&](int ja, int jb) {
+    if (ja >= jb) return;
+    GeomSrc a = load_src(rec + (size_t)ja * kStride), b;
+    int j = ja;
+    for (; j + 1 < jb; j += 2) {
+      b = load_src(rec + (size_t)(j + 1) * kStride);
+      __builtin_amdgcn_sched_barrier(0);
+      geom_step<NG, false>(acc, z, vt, a, false, false);
+      a = load_src(rec + (size_t)min(j + 2, jb - 1) * kStride);
+      __builtin_amdgcn_sched_barrier(0);
+      geom_step<NG, false>(acc, z, vt, b, false, false);
     }
-  }
-  if (wv > 0) {
+    if (j < jb) geom_step<NG, false>(acc, z, vt, a, false, false);
+  };
+  plain(j0, min(j1, base));
+  const int ma = max(j0, base), mb = min(j1, base + 128);
+  for (int j = ma; j < mb; ++j)
+    geom_step<NG, true>(acc, z, vt, load_src(rec + (size_t)j * kStride), j == n0, j == n1);
+  plain(max(j0, base + 128), j1);
+
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      red[wv - 1][4 * r + 0][lane] = s1x[r];
-      red[wv - 1][4 * r + 1][lane] = s1y[r];
-      red[wv - 1][4 * r + 2][lane] = s2x[r];
-      red[wv - 1][4 * r + 3][lane] = s2y[r];
+  for (int k = 0; k < 2 + 2 * NG; ++k) {
+    if (wv > 0) {
+      red[wv - 1][0][lane] = acc[0].s[k];
+      red[wv - 1][1][lane] = acc[1].s[k];
     }
-  }
-  __syncthreads();
-  if (wv == 0 && i < N) {
+    __syncthreads();
+    if (wv == 0) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      double a = s1x[r], b = s1y[r], c = s2x[r], d = s2y[r];
+      for (int t = 0; t < 2; ++t) {
+        double2 s = acc[t].s[k];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        a += red[k][4 * r + 0][lane];
-        b += red[k][4 * r + 1][lane];
-        c += red[k][4 * r + 2][lane];
-        d += red[k][4 * r + 3][lane];
-      }
-      const int q = q0 + r;
-      if (q < nw) {
-        parts[(((size_t)g * nw + q) * 2 + 0) * N + i] = make_double2(a, b);
-        parts[(((size_t)g * nw + q) * 2 + 1) * N + i] = make_double2(c, d);
+        for (int w = 0; w < 3; ++w) s = zadd(s, red[w][t][lane]);
+        const int i = t ? i1 : i0;
+        if (i < N) parts[(size_t)k * N + i] = s;
       }
     }
+    __syncthreads();
   }
 }
 
-__global__ void k_geom_epilogue(const double2* __restrict__ etap, const double2* __restrict__ A, int N, int n,
-                                const GeomGroup* __restrict__ groups, int G, const double2* __restrict__ Ut,
-                                const double2* __restrict__ P, const double2* __restrict__ parts, int nw, int splits,
+__global__ void k_geom_epilogue(const double2* __restrict__ etap, const double2* __restrict__ A, int N, int n, int G,
+                                const double2* __restrict__ Ut, const double2* __restrict__ parts, int splits,
                                 double2* g_eta, double2* g_etap, double2* g_A) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
-  auto S = [&](int q, int o) {
-    double2 s = make_double2(0.0, 0.0);
-    for (int g = 0; g < splits; ++g) s = zadd(s, parts[(((size_t)g * nw + q) * 2 + o) * N + i]);
-    return s;
+  const int nz = (G + 1) / 2;
+  // the six sums of a plane over the splits, their loads in flight together
+  auto sums = [&](int z, double2 (&s)[6]) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) s[k] = make_double2(0.0, 0.0);
+    for (int g = 0; g < splits; ++g) {
+      const double2* p = parts + ((size_t)g * nz + z) * 6 * N + i;
+      double2 v[6];
+#pragma unroll
+      for (int k = 0; k < 6; ++k) v[k] = (k < 4 || 2 * z + 1 < G) ? p[(size_t)k * N] : make_double2(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) s[k] = zadd(s[k], v[k]);
+    }
   };
   const double kappa = 2.0 / (double)n;
   const double2 a = A[i];
   const double2 b = zdiv(etap[i], a);
   double2 R1 = make_double2(0.0, 0.0), R2 = R1, T1 = R1, T2 = R1;
-  for (int g = 0; g < G; ++g) {
-    const double2 U = Ut[(size_t)g * N + i];
-    const double v = groups[g].v[i];
-    R1 = zadd(R1, zmul(U, S(g, 0)));
-    R2 = zadd(R2, zmul(U, S(g, 1)));
-    T1 = zadd(T1, zscale(v, S(G + 1 + g, 0)));
-    T2 = zadd(T2, zscale(v, S(G + 1 + g, 1)));
+  for (int z = 0; z < nz; ++z) {
+    double2 s[6];
+    sums(z, s);
+    T1 = zadd(T1, s[0]);
+    T2 = zadd(T2, s[1]);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (2 * z + h < G) {
+        const double2 U = Ut[(size_t)(2 * z + h) * N + i];
+        R1 = zadd(R1, zmul(U, s[2 + 2 * h]));
+        R2 = zadd(R2, zmul(U, s[3 + 2 * h]));
+      }
   }
-  const double2 p = P[i];
-  R1 = zsub(R1, zmul(p, S(G, 0)));
-  R2 = zsub(R2, zmul(p, S(G, 1)));
-  T1 = zsub(T1, S(2 * G + 1, 0));
-  T2 = zsub(T2, S(2 * G + 1, 1));
-  R1 = zscale(-kappa, zmul(a, R1));
-  R2 = zscale(kappa, zmul(a, R2));
+  R1 = zscale(kappa, zmul(a, R1));
+  R2 = zscale(-kappa, zmul(a, R2));
   const double2 C1 = zscale(kappa, zmul(b, T1));
   const double2 C2 = zscale(-kappa, zmul(b, T2));
   const double2 de = zadd(R2, C2);
@@ -255,29 +333,28 @@ __global__ __launch_bounds__(256) void k_fourier_vjp(const double2* __restrict__
 
 }  // namespace
 
+size_t geom_rec_doubles(int N, int G) { return (size_t)((G + 1) / 2) * N * kGeomRec; }
+size_t geom_part_count(int N, int G, int splits) { return (size_t)((G + 1) / 2) * N * 6 * splits; }
+
 hipError_t launch_geom_weights(const double2* eta, const double2* etap, const double2* A, int N,
-                               const GeomTerm* terms, const GeomGroup* groups, int G, int nwpad, double2* rec,
-                               double2* Ut, double2* P, hipStream_t st) {
-  k_geom_weights<<<(unsigned)((N + 255) / 256), 256, 0, st>>>(eta, etap, A, N, terms, groups, G, nwpad, rec, Ut, P);
+                               const GeomTerm* terms, const GeomGroup* groups, int G, double* rec, double2* Ut,
+                               hipStream_t st) {
+  k_geom_weights<<<(unsigned)((N + 255) / 256), 256, 0, st>>>(eta, etap, A, N, terms, groups, G, rec, Ut);
   return hipGetLastError();
 }
 
-int geom_width(int nw) { return nw % 6 == 0 ? 6 : 2; }
-
-hipError_t launch_cauchy12(const double2* rec, int nwpad, int N, int nw, int chunk, int splits, double2* parts,
-                           hipStream_t st) {
-  const int w = geom_width(nwpad);
-  dim3 grid((unsigned)((N + 63) / 64), (unsigned)splits, (unsigned)(nwpad / w));
-  if (w == 6) k_cauchy12<6><<<grid, 256, 0, st>>>(rec, 1 + nwpad, N, nw, chunk, parts);
-  else k_cauchy12<2><<<grid, 256, 0, st>>>(rec, 1 + nwpad, N, nw, chunk, parts);
+hipError_t launch_geom_sums(const double* rec, int N, int G, int chunk, int splits, double2* parts, hipStream_t st) {
+  const int nz = (G + 1) / 2;
+  const dim3 grid((unsigned)((N + 127) / 128), (unsigned)splits, (unsigned)(G / 2));
+  if (G > 1) k_geom_sums<2><<<grid, 256, 0, st>>>(rec, N, 0, nz, chunk, parts);
+  if (G & 1) k_geom_sums<1><<<dim3(grid.x, grid.y, 1), 256, 0, st>>>(rec, N, nz - 1, nz, chunk, parts);
   return hipGetLastError();
 }
 
-hipError_t launch_geom_epilogue(const double2* etap, const double2* A, int N, int n, const GeomGroup* groups, int G,
-                                const double2* Ut, const double2* P, const double2* parts, int nw, int splits,
-                                double2* g_eta, double2* g_etap, double2* g_A, hipStream_t st) {
-  k_geom_epilogue<<<(unsigned)((N + 255) / 256), 256, 0, st>>>(etap, A, N, n, groups, G, Ut, P, parts, nw, splits,
-                                                               g_eta, g_etap, g_A);
+hipError_t launch_geom_epilogue(const double2* etap, const double2* A, int N, int n, int G, const double2* Ut,
+                                const double2* parts, int splits, double2* g_eta, double2* g_etap, double2* g_A,
+                                hipStream_t st) {
+  k_geom_epilogue<<<(unsigned)((N + 63) / 64), 64, 0, st>>>(etap, A, N, n, G, Ut, parts, splits, g_eta, g_etap, g_A);
   return hipGetLastError();
 }
 

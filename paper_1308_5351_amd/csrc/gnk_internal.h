@@ -210,18 +210,18 @@ struct GeomGroup {
   const double* v;
   int t0, t1;        // terms [t0, t1) of the group
 };
-// source records {eta, b V_g (G), b, a U_g (G), a P} with nw = 2G + 2 weights
+// sizes of the source records (doubles) and of the partial sums (complex)
+size_t geom_rec_doubles(int N, int G);
+size_t geom_part_count(int N, int G, int splits);
 hipError_t launch_geom_weights(const double2* eta, const double2* etap, const double2* A, int N,
-                               const GeomTerm* terms, const GeomGroup* groups, int G, int nw, double2* rec,
-                               double2* Ut, double2* P, hipStream_t st);
-// first- and second-order Cauchy sums of the nw weights, per source split
-hipError_t launch_cauchy12(const double2* rec, int nwpad, int N, int nw, int chunk, int splits, double2* parts,
-                           hipStream_t st);
-int geom_width(int nw);
+                               const GeomTerm* terms, const GeomGroup* groups, int G, double* rec, double2* Ut,
+                               hipStream_t st);
+// the first- and second-order sums of the G groups, per source split
+hipError_t launch_geom_sums(const double* rec, int N, int G, int chunk, int splits, double2* parts, hipStream_t st);
 // gradients with respect to eta, eta', A (any output may be null)
-hipError_t launch_geom_epilogue(const double2* etap, const double2* A, int N, int n, const GeomGroup* groups, int G,
-                                const double2* Ut, const double2* P, const double2* parts, int nw, int splits,
-                                double2* g_eta, double2* g_etap, double2* g_A, hipStream_t st);
+hipError_t launch_geom_epilogue(const double2* etap, const double2* A, int N, int n, int G, const double2* Ut,
+                                const double2* parts, int splits, double2* g_eta, double2* g_etap, double2* g_A,
+                                hipStream_t st);
 
 // Fourier boundary curves eta_j(t) = sum_k c_{j,k} e^{i sgn k t} at t_p = 2 pi p/n
 // (coef: m1 x nk, component-major) and the chain rule back to the coefficients

@@ -1765,25 +1765,23 @@ void geom_vjp(gnk_ctx* c, const gnk_domain* d, int nterms, const int* ops, const
     groups.push_back(GeomGroup{gv[g], t0, (int)terms.size()});
   }
   const int G = (int)groups.size();
-  const int nw = 2 * G + 2;
-  // enough workgroups for two rounds of the wave slots, at least 256 sources each
-  const int64_t tiles = (N + 63) / 64;
-  int64_t splits = (2 * slots_of(c) + 4 * tiles - 1) / (4 * tiles);
-  splits = std::max<int64_t>(1, std::min<int64_t>(splits, std::min<int64_t>(64, std::max<int64_t>(1, N / 256))));
+  // two rounds of the kernel's wave slots (4 per SIMD), at least 64 sources per
+  // workgroup (256 where a workspace cap counts the partial sums)
+  const int64_t tiles = (N + 127) / 128;
+  int64_t splits = (2 * 16 * (int64_t)c->num_cu + 4 * tiles - 1) / (4 * tiles);
+  splits = std::max<int64_t>(1, std::min<int64_t>(splits, std::min<int64_t>(64, N / (c->ws_limit ? 256 : 64))));
   int64_t chunk = (N + splits - 1) / splits;
   chunk = (chunk + 3) / 4 * 4;
   splits = (N + chunk - 1) / chunk;
   const GeomTerm* dterms = upload(c, "g_terms", terms);
   const GeomGroup* dgroups = upload(c, "g_groups", groups);
-  double2* rec = ws<double2>(c, "g_rec", (size_t)N * (1 + nw));
+  double* rec = ws<double>(c, "g_rec", geom_rec_doubles(N, G));
   double2* Ut = ws<double2>(c, "g_U", (size_t)G * N);
-  double2* P = ws<double2>(c, "g_P", N);
-  double2* parts = ws<double2>(c, "g_parts", (size_t)splits * nw * 2 * N);
+  double2* parts = ws<double2>(c, "g_parts", geom_part_count(N, G, (int)splits));
   const DomDev& D = B.dom[0];
-  HIPCHK(c, launch_geom_weights(D.eta, D.etap, D.A, N, dterms, dgroups, G, nw, rec, Ut, P, c->stream));
-  HIPCHK(c, launch_cauchy12(rec, nw, N, nw, (int)chunk, (int)splits, parts, c->stream));
-  HIPCHK(c, launch_geom_epilogue(D.etap, D.A, N, D.n, dgroups, G, Ut, P, parts, nw, (int)splits, g_eta, g_etap, g_A,
-                                 c->stream));
+  HIPCHK(c, launch_geom_weights(D.eta, D.etap, D.A, N, dterms, dgroups, G, rec, Ut, c->stream));
+  HIPCHK(c, launch_geom_sums(rec, N, G, (int)chunk, (int)splits, parts, c->stream));
+  HIPCHK(c, launch_geom_epilogue(D.etap, D.A, N, D.n, G, Ut, parts, (int)splits, g_eta, g_etap, g_A, c->stream));
 }
 
 std::mutex scratch_mu;
