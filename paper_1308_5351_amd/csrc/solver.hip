@@ -327,9 +327,10 @@ void check_domain(gnk_ctx* c, const gnk_domain* d, bool adjoint, bool second = f
 // columns at N = 10240 2.81 / 2.27 ms; four at 1200 627 / 650 us).
 //
 // Small domains (32 splits would not fill the wave slots of the kernel variant
-// twice): as many splits as leave 64 sources each, at most 32 (8 / 16 / 32 / 64
+// twice): as many splits as leave 64 sources each, at most 32, or 256 each, at most
+// 64 (300 points against 17408 nodes: 90 us at 64, 95 at 32). (8 / 16 / 32 / 64
 // splits at N = 3072: 593 / 593 / 586 / 632 us, at 6144 1002 / 944 / 916 / 996; 4 / 8 /
-// 16 at N = 512: 535 / 488 / 484), but no round of the slots that is left less than
+// 16 at N = 512: 535 / 488 / 484.) But no round of the slots that is left less than
 // half full (11 x 600 nodes, 2 columns: 29 splits 1114 us, 32 of 1.08 rounds 1186;
 // 8 columns: 19 splits 1853 us, 32 of 1.62 rounds 1784).
 //
@@ -355,7 +356,7 @@ void plan_pairs(gnk_ctx* c, int64_t Nt, int64_t Ns, int align, int width, bool m
   // how many workgroups fit on a CU)
   const int64_t slots = (int64_t)c->num_cu * 4 * pairs_blocks_per_cu(width, t, mixed);
   const int64_t tiles = (Nt + 64 * t - 1) / (64 * t);
-  const int64_t few = std::max<int64_t>(1, std::min<int64_t>(32, Ns / 64));
+  const int64_t few = std::max({(int64_t)1, std::min<int64_t>(32, Ns / 64), std::min<int64_t>(64, Ns / 256)});
   int64_t bs = 0;
   if (roomy && (double)(tiles * few * 4) < 1.9 * (double)slots) {
     bs = tiles * few * 4 > slots && 2 * tiles * few * 4 < 3 * slots ? slots / (4 * tiles) : few;
@@ -1048,13 +1049,17 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
   // batch's columns give more than about 8192 blocks together (each block
   // sums its column's block partials, so fewer blocks per column also means
   // less of that)
+  // (an even number: entries are taken in twos)
   const int per_blk = (int)std::max<int64_t>(
-      kT, std::min<int64_t>(kMaxChunk, std::max<int64_t>(((int64_t)B.maxN + 255) / 256, (T + 8191) / 8192)));
+      kT, std::min<int64_t>(kMaxChunk, (std::max<int64_t>(((int64_t)B.maxN + 255) / 256, (T + 8191) / 8192) + 1) / 2 * 2));
   const int nblk = (B.maxN + per_blk - 1) / per_blk;
 
   double* V = ws<double>(c, "V", (size_t)(restart + 1) * T);
   double* P1 = ws<double>(c, "gmP1", (size_t)ncol * nblk * ldp);
   double* P2 = ws<double>(c, "gmP2", (size_t)ncol * nblk * ldp);
+  // the partials of very many blocks are added up by a launch of their own
+  const bool fold = nblk > kFoldBlocks;
+  double* P3 = fold ? ws<double>(c, "gmP3", (size_t)ncol * ldp) : nullptr;
   GmresState st;
   st.ldh = restart + 1;
   st.hstride = st.ldh * restart;
@@ -1164,15 +1169,24 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
     const bool sym = use_sym(B, P_GM, use_mixed);
     // the many slots of two-sided sums shared by four groups of threads (at N =
     // 12240 the adjoint solve took 1.65 ms against 1.79 with one)
-    const int epi = sym ? kT * kEpiGroups : kT;
-    k_epilogue_dots<<<gv, epi, 0, c->stream>>>(B.d_dom, B.d_col, V, T, form.cout, form.dsel, form.a0, form.dsign,
+    const int groups = sym ? kEpiGroups : 1;
+    const double* const p1 = fold ? P3 : P1;
+    const double* const p2 = fold ? P3 : P2;
+    const int nin = fold ? 1 : nblk;
+    const dim3 gf((unsigned)((ldp + 15) / 16), (unsigned)ncol);
+    k_epilogue_dots<<<gv, kT * groups, epilogue_lds(groups, mpart ? S : 0), c->stream>>>(B.d_dom, B.d_col, V, T, form.cout, form.dsel, form.a0, form.dsign,
                                               form.cI, form.cR, mpart, S, st.active, sl.step, per_blk,
                                               sym, P1, ldp);
     LAUNCHCHK(c);
-    k_gs_update<<<gv, kT, 0, c->stream>>>(B.d_dom, B.d_col, V, T, per_blk, P1, P2, ldp, sl);
+    if (fold) k_fold_partials<<<gf, kFoldT, 0, c->stream>>>(P1, nblk, ldp, st.active, sl.step, 1, P3);
     LAUNCHCHK(c);
-    k_gs_finish<<<gv, kT, 0, c->stream>>>(B.d_dom, B.d_col, V, T, per_blk, P2, ldp, sl, next, restart, stop_tol,
-                                          host_live, host_rel, form.cw, mpart, S);
+    k_gs_update<<<gv, kT, 0, c->stream>>>(B.d_dom, B.d_col, V, T, per_blk, p1, nin, P2, ldp, sl);
+    LAUNCHCHK(c);
+    if (fold) k_fold_partials<<<gf, kFoldT, 0, c->stream>>>(P2, nblk, ldp, st.active, sl.step, 2, P3);
+    LAUNCHCHK(c);
+    k_gs_finish<<<dim3(gv.x + 1, gv.y), kT, 0, c->stream>>>(B.d_dom, B.d_col, V, T, per_blk, p2, nin, ldp, sl, next,
+                                                            restart, stop_tol, host_live, host_rel, form.cw, mpart,
+                                                            S);
     LAUNCHCHK(c);
   };
   // Every buffer the step touches exists before a capture (no allocation,
@@ -1216,7 +1230,7 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
                           (const void*)st.done})
       pt(q);
     u((uint64_t)st.ldh); u((uint64_t)st.hstride);
-    pt(V); u((uint64_t)T); u((uint64_t)per_blk); u((uint64_t)nblk); u((uint64_t)ncol); pt(P1); pt(P2);
+    pt(V); u((uint64_t)T); u((uint64_t)per_blk); u((uint64_t)nblk); u((uint64_t)ncol); pt(P1); pt(P2); pt(P3);
     u((uint64_t)ldp); pt(step_odd); u((uint64_t)restart); fp(stop_tol); pt(host_live);
     pt(host_rel);
     u((uint64_t)form.cw); u((uint64_t)form.cout); u((uint64_t)form.dsel); fp(form.a0); fp(form.dsign); fp(form.cI);

@@ -542,20 +542,100 @@ __global__ __launch_bounds__(kT) void k_col_norms(const DomDev* __restrict__ dom
 // Krylov vector l of column c: V + l*T + off_c (T = flat length of a vector set).
 // Partial sums: P[(c*nblk + blk)*ldp + l]; blocks past the column's end write 0.
 
-// Dots of the block's chunk of w with V_0..V_{nvec-1}: wavefront q takes
-// vectors l = q, q+4, ...; each lane sums its strided elements and the wave
-// reduces by shuffles.
-__device__ __forceinline__ void chunk_dots(const double* __restrict__ V, int64_t T, int64_t off, int nvec,
-                                           const double* __restrict__ w, int i0, int i1,
-                                           double* __restrict__ out) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int l = wv; l < nvec; l += nw) {
-    const double* vl = V + (size_t)l * T + off;
-    double acc = 0.0;
-    for (int i = i0 + lane; i < i1; i += 64) acc = __builtin_fma(vl[i], w[i - i0], acc);
-    acc = wave_sum(acc);
-    if (lane == 0) out[l] = acc;
+// The chunks [i0, i1) of a block and the basis are read two entries at a time (N and
+// the flat offsets are even, the basis is allocated here), eight vectors' loads in
+// flight together: with one vector after the other the three kernels of a step took
+// 13 us per 35.7 MB vector and pass at N = 4460544 (2.7 TB/s), now 7-8 (4.8). Vector indices
+// past the last repeat it (its lines are in the L1).
+constexpr int kVecW = 8;
+__device__ __forceinline__ const double2* basis2(const double* V, int64_t T, int64_t at, int l) {
+  return reinterpret_cast<const double2*>(V + (size_t)l * T + at);
+}
+
+// s[k] summed over the wave in the lanes with lane / 8 == k (every exchange halves the
+// number of values a lane carries on)
+__device__ __forceinline__ double wave_sum8(const double (&s)[8]) {
+  const int lane = threadIdx.x & 63;
+  double a[4], b[2];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const bool hi = lane & 32;
+    a[j] = (hi ? s[4 + j] : s[j]) + __shfl_xor(hi ? s[j] : s[4 + j], 32, 64);
   }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const bool hi = lane & 16;
+    b[j] = (hi ? a[2 + j] : a[j]) + __shfl_xor(hi ? a[j] : a[2 + j], 16, 64);
+  }
+  const bool hi = lane & 8;
+  double c = (hi ? b[1] : b[0]) + __shfl_xor(hi ? b[0] : b[1], 8, 64);
+#pragma unroll
+  for (int off = 4; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+  return c;
+}
+
+// Dots of the block's chunk of w (LDS) with V_0..V_{nvec-1}, eight vectors per wave at
+// a time; a chunk too short for all waves leaves groups of them to further vectors.
+template <int W>
+__device__ __forceinline__ double dots_of(const double* __restrict__ V, int64_t T, int64_t at, int q, int nvec,
+                                          const double2* w2, int i, int len2, int stride) {
+  const double2* p[W];
+#pragma unroll
+  for (int k = 0; k < W; ++k) p[k] = basis2(V, T, at, min(q + k, nvec - 1));
+  double acc[kVecW] = {};
+  for (; i < len2; i += stride) {
+    double2 v[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) v[k] = p[k][i];
+    const double2 w = w2[i];
+#pragma unroll
+    for (int k = 0; k < W; ++k) acc[k] = __builtin_fma(v[k].x, w.x, __builtin_fma(v[k].y, w.y, acc[k]));
+  }
+  return wave_sum8(acc);
+}
+__device__ __forceinline__ void chunk_dots(const double* __restrict__ V, int64_t T, int64_t off, int nvec,
+                                           const double* sw, int i0, int i1, double (*red)[kVecW],
+                                           double* __restrict__ out) {
+  const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int len2 = (i1 - i0) >> 1;
+  const int we = min(nw, (len2 + 63) >> 6), ng = nw / we;
+  const int g = wv / we, m = wv - g * we;
+  const double2* w2 = reinterpret_cast<const double2*>(sw);
+  for (int q0 = 0; q0 < nvec; q0 += kVecW * ng) {
+    const int q = q0 + kVecW * g;
+    if (g < ng && q < nvec) {
+      const int i = 64 * m + lane;
+      const double s = nvec - q <= 4 ? dots_of<4>(V, T, off + i0, q, nvec, w2, i, len2, 64 * we)
+                                     : dots_of<8>(V, T, off + i0, q, nvec, w2, i, len2, 64 * we);
+      if ((lane & 7) == 0) red[wv][lane >> 3] = s;
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < kVecW * ng && q0 + t < nvec) {
+      double s = 0.0;
+      for (int k = 0; k < we; ++k) s += red[(t >> 3) * we + k][t & 7];
+      out[q0 + t] = s;
+    }
+    __syncthreads();
+  }
+}
+
+// w - sum_l h_l V_l of the entry pair i
+__device__ __forceinline__ double2 subtract_basis(double2 w, const double* __restrict__ V, int64_t T, int64_t at,
+                                                  int nvec, const double* h, int i) {
+  for (int l = 0; l < nvec; l += kVecW) {
+    double2 v[kVecW];
+#pragma unroll
+    for (int k = 0; k < kVecW; ++k) v[k] = basis2(V, T, at, min(l + k, nvec - 1))[i];
+#pragma unroll
+    for (int k = 0; k < kVecW; ++k) {
+      const double f = l + k < nvec ? -h[l + k] : 0.0;
+      w.x = __builtin_fma(f, v[k].x, w.x);
+      w.y = __builtin_fma(f, v[k].y, w.y);
+    }
+  }
+  return w;
 }
 
 // One Arnoldi step l = *st.step of every iterating column takes four launches:
@@ -563,7 +643,7 @@ __device__ __forceinline__ void chunk_dots(const double* __restrict__ V, int64_t
 //   k_epilogue_dots  w = op(V_l) into V_{l+1}; dots of w with V_0..V_l
 //   k_gs_update      w -= V h1; dots of w with V_0..V_l and |w|^2
 //   k_gs_finish      w -= V h2, |w| = beta, V_{l+1} = w / beta and its pair
-//                    records; block 0 closes Hessenberg column l.
+//                    records; a block of its own closes Hessenberg column l.
 // (classical Gram-Schmidt with one re-orthogonalisation). Every kernel works
 // on chunks of per_blk elements of a column (grid (nblk, ncol)) and writes its
 // partial sums to (c*nblk + blk)*ldp. V is the basis (vector q at V + q*T).
@@ -618,15 +698,21 @@ __global__ __launch_bounds__(kT) void k_stage(const DomDev* __restrict__ doms, c
 // w = V_{l+1} = op(V_l) on the block's chunk from the Cauchy sums of the last
 // pair launch, then the chunk's dots of w with V_0..V_l.
 constexpr int kEpiGroups = 4;   // at most this many groups of kT threads
+inline size_t epilogue_lds(int groups, int mean_slots) {
+  return (size_t)(groups - 1) * kT * sizeof(double2) + (size_t)mean_slots * sizeof(double);
+}
 __global__ __launch_bounds__(kT * kEpiGroups) void k_epilogue_dots(const DomDev* __restrict__ doms,
                                                       const ColDev* __restrict__ cols, double* __restrict__ V,
                                                       int64_t T, int csel_out, int dsel, double a0, double dsign,
                                                       double cI, double cR, const double* __restrict__ mpart, int S,
                                                       const int* __restrict__ active, const int* __restrict__ step,
                                                       int per_blk, int sym, double* __restrict__ partial, int ldp) {
-  __shared__ double sw[kMaxChunk];
-  __shared__ double sm[kMaxMeanSlots];
-  __shared__ double2 sg[kEpiGroups - 1][kT];
+  // launched with epilogue_lds() bytes: the other groups' sums, then the means
+  extern __shared__ double2 sdyn[];
+  __shared__ __align__(16) double sw[kMaxChunk];
+  __shared__ double red[kEpiGroups * kT / 64][kVecW];
+  double2* sg = sdyn;
+  double* sm = reinterpret_cast<double*>(sdyn + (blockDim.x - kT));
   const int c = blockIdx.y, blk = blockIdx.x, nblk = gridDim.x;
   if (!active[c]) return;
   const int l = *step;
@@ -653,12 +739,12 @@ __global__ __launch_bounds__(kT * kEpiGroups) void k_epilogue_dots(const DomDev*
     double2 s = make_double2(0.0, 0.0);
     if (i < i1) s = reduce_parts(D, D.ncols, C.r, i, sym, grp, ng);
     if (ng > 1) {
-      if (grp > 0) sg[grp - 1][t] = s;
+      if (grp > 0) sg[(grp - 1) * kT + t] = s;
       __syncthreads();
       if (grp == 0)
         for (int g = 1; g < ng; ++g) {
-          s.x += sg[g - 1][t].x;
-          s.y += sg[g - 1][t].y;
+          s.x += sg[(g - 1) * kT + t].x;
+          s.y += sg[(g - 1) * kT + t].y;
         }
     }
     if (grp == 0 && i < i1) {
@@ -673,41 +759,131 @@ __global__ __launch_bounds__(kT * kEpiGroups) void k_epilogue_dots(const DomDev*
     if (ng > 1) __syncthreads();
   }
   __syncthreads();
-  chunk_dots(V, T, C.off, nvec, sw, i0, i1, out);
+  chunk_dots(V, T, C.off, nvec, sw, i0, i1, red, out);
 }
 
-// h_q = sum over blocks of the partials in[.. + q] for q = 0..nq-1 (fixed
-// order), into LDS; wavefront v takes q = v, v + 4, ...
+// h_q = sum over blocks of the partials in[.. + q] for q = 0..nq-1 (fixed order),
+// into LDS (kT threads): sixteen q at a time, the blocks in sixteen slices
 __device__ __forceinline__ void sum_partials(const double* __restrict__ in, int c, int nblk, int ldp, int nq,
                                              double* h) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int q = wv; q < nq; q += nw) {
+  __shared__ double red[kT / 64][16];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int k = threadIdx.x & 15;
+  for (int q0 = 0; q0 < nq; q0 += 16) {
+    const double* p = in + (size_t)c * nblk * ldp + min(q0 + k, nq - 1);
     double acc = 0.0;
-    for (int b = lane; b < nblk; b += 64) acc += in[((size_t)c * nblk + b) * ldp + q];
-    acc = wave_sum(acc);
-    if (lane == 0) h[q] = acc;
+#pragma unroll 8
+    for (int b = threadIdx.x >> 4; b < nblk; b += kT / 16) acc += p[(size_t)b * ldp];
+    acc += __shfl_xor(acc, 16, 64);
+    acc += __shfl_xor(acc, 32, 64);
+    if (lane < 16) red[wv][lane] = acc;
+    __syncthreads();
+    if (threadIdx.x < 16 && q0 + k < nq) {
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < kT / 64; ++w) s += red[w][k];
+      h[q0 + k] = s;
+    }
+    __syncthreads();
   }
-  __syncthreads();
 }
 
-// First pass: h1 = V^T w from the epilogue's partials, H(:, l) = h1 (block 0),
-// w -= V h1 on the chunk, then the chunk's dots of the updated w with
-// V_0..V_l (entries 0..l) and its squared norm (entry l + 1).
+// The partials of nblk blocks added up once (grid (ldp / 16 up, ncol)), for columns of
+// so many blocks that every block's own sum over all of them costs more than a launch:
+// out[c ldp + q], q < *step + extra. From kFoldBlocks blocks on: at 2178 (N = 4460544)
+// the blocks read 38 MB of partials per basis vector, as much as the vector itself.
+constexpr int kFoldBlocks = 512, kFoldT = 1024;
+__global__ __launch_bounds__(kFoldT) void k_fold_partials(const double* __restrict__ in, int nblk, int ldp,
+                                                      const int* __restrict__ active, const int* __restrict__ step,
+                                                      int extra, double* __restrict__ out) {
+  __shared__ double red[kFoldT / 64][16];
+  const int c = blockIdx.y, q0 = blockIdx.x * 16;
+  const int nq = *step + extra;
+  if (!active[c] || q0 >= nq) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, k = threadIdx.x & 15;
+  const double* p = in + (size_t)c * nblk * ldp + min(q0 + k, nq - 1);
+  double acc = 0.0;
+#pragma unroll 8
+  for (int b = threadIdx.x >> 4; b < nblk; b += kFoldT / 16) acc += p[(size_t)b * ldp];
+  acc += __shfl_xor(acc, 16, 64);
+  acc += __shfl_xor(acc, 32, 64);
+  if (lane < 16) red[wv][lane] = acc;
+  __syncthreads();
+  if (threadIdx.x < 16 && q0 + k < nq) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kFoldT / 64; ++w) s += red[w][k];
+    out[(size_t)c * ldp + q0 + k] = s;
+  }
+}
+
+// The update and the dots of nvec <= NV vectors from one read of the basis: an entry
+// pair's NV values stay in registers between the two.
+template <int NV>
+__device__ __forceinline__ double update_and_dots(const double* __restrict__ V, int64_t T, int64_t at, int nvec,
+                                                  const double* h, double2* w2, int len2, double (*red)[16],
+                                                  double* __restrict__ out) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const double2* p[NV];
+  double f[NV], acc[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    p[k] = basis2(V, T, at, min(k, nvec - 1));
+    f[k] = k < nvec ? -h[k] : 0.0;
+    acc[k] = 0.0;
+  }
+  double nrm = 0.0;
+  for (int i = threadIdx.x; i < len2; i += kT) {
+    double2 v[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = p[k][i];
+    double2 w = w2[i];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      w.x = __builtin_fma(f[k], v[k].x, w.x);
+      w.y = __builtin_fma(f[k], v[k].y, w.y);
+    }
+    w2[i] = w;
+    nrm = __builtin_fma(w.x, w.x, __builtin_fma(w.y, w.y, nrm));
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc[k] = __builtin_fma(v[k].x, w.x, __builtin_fma(v[k].y, w.y, acc[k]));
+  }
+#pragma unroll
+  for (int k = 0; k < NV; k += 8) {
+    const double s[8] = {acc[k], acc[k + 1], acc[k + 2], acc[k + 3], acc[k + 4], acc[k + 5], acc[k + 6], acc[k + 7]};
+    const double r = wave_sum8(s);
+    if ((lane & 7) == 0) red[wv][k + (lane >> 3)] = r;
+  }
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t < nvec) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kT / 64; ++w) s += red[w][t];
+    out[t] = s;
+  }
+  return nrm;
+}
+
+// First pass: h1 = V^T w from the epilogue's partials (nin rows of them), H(:, l) = h1
+// (block 0), w -= V h1 on the chunk, then the chunk's dots of the updated w with
+// V_0..V_l (entries 0..l) and its squared norm (entry l + 1). Up to 16 vectors are
+// read once, more of them twice.
 __global__ __launch_bounds__(kT) void k_gs_update(const DomDev* __restrict__ doms, const ColDev* __restrict__ cols,
                                                   double* __restrict__ V, int64_t T, int per_blk,
-                                                  const double* __restrict__ pin, double* __restrict__ pout,
-                                                  int ldp, GmresState st) {
+                                                  const double* __restrict__ pin, int nin,
+                                                  double* __restrict__ pout, int ldp, GmresState st) {
   __shared__ double h[kMaxRestart + 1];
-  __shared__ double sw[kMaxChunk];
+  __shared__ __align__(16) double sw[kMaxChunk];
   __shared__ double sh[kT / 64];
+  __shared__ double red[kT / 64][16];
   const int c = blockIdx.y, blk = blockIdx.x, nblk = gridDim.x;
   if (!st.active[c]) return;
   const int col = *st.step;
   const int nvec = col + 1;
-  double* __restrict__ w = V + (size_t)nvec * T;
   const ColDev C = cols[c];
   const int N = doms[C.d].N;
-  sum_partials(pin, c, nblk, ldp, nvec, h);
+  sum_partials(pin, c, nin, ldp, nvec, h);
   if (blk == 0) {
     double* Hr = st.H + (size_t)c * st.hstride + (size_t)col * st.ldh;
     for (int l = threadIdx.x; l < nvec; l += blockDim.x) Hr[l] = h[l];
@@ -718,17 +894,24 @@ __global__ __launch_bounds__(kT) void k_gs_update(const DomDev* __restrict__ dom
     for (int l = threadIdx.x; l <= nvec; l += blockDim.x) out[l] = 0.0;
     return;
   }
-  double* wr = w + C.off;
+  const int64_t at = C.off + i0;
+  const int len2 = (i1 - i0) >> 1;
+  double2* w2 = reinterpret_cast<double2*>(V + (size_t)nvec * T + at);
   double nrm = 0.0;
-  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-    double v = wr[i];
-    for (int l = 0; l < nvec; ++l) v = __builtin_fma(-h[l], V[(size_t)l * T + C.off + i], v);
-    wr[i] = v;
-    sw[i - i0] = v;
-    nrm = __builtin_fma(v, v, nrm);
+  if (nvec <= 8) {
+    nrm = update_and_dots<8>(V, T, at, nvec, h, w2, len2, red, out);
+  } else if (nvec <= 16) {
+    nrm = update_and_dots<16>(V, T, at, nvec, h, w2, len2, red, out);
+  } else {
+    for (int i = threadIdx.x; i < len2; i += kT) {
+      const double2 v = subtract_basis(w2[i], V, T, at, nvec, h, i);
+      w2[i] = v;
+      reinterpret_cast<double2*>(sw)[i] = v;
+      nrm = __builtin_fma(v.x, v.x, __builtin_fma(v.y, v.y, nrm));
+    }
+    __syncthreads();
+    chunk_dots(V, T, C.off, nvec, sw, i0, i1, reinterpret_cast<double(*)[kVecW]>(red), out);
   }
-  __syncthreads();
-  chunk_dots(V, T, C.off, nvec, sw, i0, i1, out);
   const double t = block_sum(nrm, sh);
   if (threadIdx.x == 0) out[nvec] = t;
 }
@@ -874,60 +1057,60 @@ __device__ void arnoldi_close(GmresState st, int c, int col, const double* h2, d
 // the updated w, |w|^2 - |h2|^2 is its squared norm beta^2 (the first pass has
 // already removed all but rounding-size components along V, so no
 // cancellation occurs short of a breakdown); V_{l+1} = w / beta, its pair
-// records and component sums. Block 0 of each column then closes Hessenberg
-// column l. Those blocks count themselves in *st.done (after a device-scope
-// fence); the last publishes the number of iterating columns to host_live[l]
+// records and component sums. The last block of each column has no chunk and
+// closes Hessenberg column l meanwhile (its chain of rotations and the store
+// to the host took the chunk's block 3 us longer than the others). Those
+// blocks count themselves in *st.done (after a device-scope fence); the last publishes the number of iterating columns to host_live[l]
 // and, when given, the residual estimates to host_rel[l*ncol ..] (host-mapped
 // memory the host reads after an event) and sets *step_next = l + 1. The
 // step index is double-buffered (st.step is read by all of this step's
 // launches, step_next by the next step's), so no block can read an index
-// that another has already advanced. A block of a column that block 0 has
-// just stopped may still write V_{l+1} and its records: no later step or the
+// that another has already advanced. A block of a column that has just
+// been stopped may still write V_{l+1} and its records: no later step or the
 // solution update reads them.
 __global__ __launch_bounds__(kT) void k_gs_finish(const DomDev* __restrict__ doms, const ColDev* __restrict__ cols,
                                                   double* __restrict__ V, int64_t T, int per_blk,
-                                                  const double* __restrict__ pin, int ldp, GmresState st,
-                                                  int* __restrict__ step_next, int restart, double tol,
-                                                  int* host_live, double* host_rel, int csel,
+                                                  const double* __restrict__ pin, int nin, int ldp,
+                                                  GmresState st, int* __restrict__ step_next, int restart,
+                                                  double tol, int* host_live, double* host_rel, int csel,
                                                   double* __restrict__ mpart, int S) {
   __shared__ double h[kMaxRestart + 2];
-  __shared__ double sq[kMaxChunk];
+  __shared__ __align__(16) double sq[kMaxChunk];
   __shared__ double hc[kMaxRestart + 2];
   __shared__ double cs_[kMaxRestart], sn_[kMaxRestart];
   __shared__ int last;
-  const int c = blockIdx.y, blk = blockIdx.x, nblk = gridDim.x, ncol = gridDim.y;
+  const int c = blockIdx.y, blk = blockIdx.x, nblk = gridDim.x - 1, ncol = gridDim.y;
   const bool act = st.active[c] != 0;
-  if (!act && blk != 0) return;
+  if (!act && blk != nblk) return;
   const int col = *st.step;
   const int nvec = col + 1;
   double beta = 0.0;
   if (act) {
-    sum_partials(pin, c, nblk, ldp, nvec + 1, h);
+    sum_partials(pin, c, nin, ldp, nvec + 1, h);
     double hh = 0.0;
     for (int l = 0; l < nvec; ++l) hh = __builtin_fma(h[l], h[l], hh);
     const double b2 = h[nvec] - hh;
     beta = b2 > 0.0 ? sqrt(b2) : 0.0;
+  }
+  if (blk != nblk) {
     const double inv = beta > 0.0 ? 1.0 / beta : 0.0;
     const ColDev C = cols[c];
     const DomDev& D = doms[C.d];
     const int i0 = blk * per_blk, i1 = min(D.N, i0 + per_blk);
-    if (i0 < D.N) {
-      double* wr = V + (size_t)nvec * T + C.off;
-      for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-        double v = wr[i];
-        for (int l = 0; l < nvec; ++l) v = __builtin_fma(-h[l], V[(size_t)l * T + C.off + i], v);
-        const double q = v * inv;
-        wr[i] = q;
-        sq[i - i0] = q;
-        stage_weight(D, csel, C.r, i, q, false);
-      }
-      if (mpart) {
-        __syncthreads();
-        chunk_component_sums(sq, i0, i1, D.n, mpart + ((size_t)c * nblk + blk) * S);
-      }
+    if (i0 >= D.N) return;
+    const int64_t at = C.off + i0;
+    double2* w2 = reinterpret_cast<double2*>(V + (size_t)nvec * T + at);
+    for (int i = threadIdx.x; 2 * i < i1 - i0; i += kT) {
+      const double2 v = subtract_basis(w2[i], V, T, at, nvec, h, i);
+      const double2 q = make_double2(v.x * inv, v.y * inv);
+      w2[i] = q;
+      reinterpret_cast<double2*>(sq)[i] = q;
     }
+    __syncthreads();
+    for (int i = i0 + threadIdx.x; i < i1; i += kT) stage_weight(D, csel, C.r, i, sq[i - i0], false);
+    if (mpart) chunk_component_sums(sq, i0, i1, D.n, mpart + ((size_t)c * nblk + blk) * S);
+    return;
   }
-  if (blk != 0) return;
   if (act) arnoldi_close(st, c, col, h, beta, restart, tol, hc, cs_, sn_);
   __syncthreads();
   if (threadIdx.x == 0) {
