@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kT) void k_weights(const DomDev* __restrict__ doms,
     acc += v;
     if (D.w1 && wcols == 1) {
       D.w1[j] = w;
-      continue;
+      if (!D.rec32) continue;   // mixed products take the records
     }
     const double2 ep = record_offset(D, j);
     put_weight(D, wcols, j, lead + C.r, w, ep);

@@ -104,3 +104,25 @@ def test_solves_of_one_and_three_columns_agree(gk, prec):
             assert float((a - b).abs().max() / x.abs().max()) <= 1e-10
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("m1,n", [(6, 1364), (9, 1024), (17, 1024)])
+def test_mixed_product_of_one_column(gk, m1, n):
+    """A mixed product of one column, at sizes whose FP64 products are two-sided: it
+    takes the node records, not the compact weights. 1e-5 as for the other mixed
+    products (FP32 far tiles, about 1e-7)."""
+    import workloads as wl
+    print(f"[sym] mixed {m1} x {n}", flush=True)
+    dom = gk.DeviceDomain.from_host(wl.circles_unbounded(n, [2.6 * (k % 5) + 2.6j * (k // 5) for k in range(m1)], [1.0] * m1))
+    g = torch.Generator().manual_seed(n)
+    x = torch.randn(dom.N, 2, generator=g, dtype=torch.float64).cuda()
+    for op in (gk.OP_FB, gk.OP_FB_T):
+        ctx = gk.Context(0)
+        try:
+            y = ctx.apply(dom, op, x[:, 0].contiguous(), prec=gk.MIXED)   # the context's first product
+            two = ctx.apply(dom, op, x)
+            again = ctx.apply(dom, op, x[:, 0].contiguous(), prec=gk.MIXED)
+            for v in (y, again):
+                assert float((v - two[:, 0]).abs().max() / two[:, 0].abs().max()) < 1e-5
+        finally:
+            ctx.close()
