@@ -106,7 +106,8 @@ typedef struct {
  *   tol        : relative residual ||b - A x||_2 / ||b||_2 per right-hand side
  *   prec       : GNK_FP64, or GNK_MIXED: the Arnoldi products switch to FP32
  *                for well-separated 64-node tiles (FP64 for all other pairs,
- *                the epilogues, the orthogonalisation) once every column's
+ *                the epilogues, the orthogonalisation), or in large domains
+ *                to the treecode, in FP64 with far_tol 1e-9, once every column's
  *                residual estimate is below inner_tol; the residual starting
  *                each restart cycle is recomputed with FP64 products, so
  *                restarts act as FP64 iterative refinement and the same tol
@@ -160,8 +161,8 @@ typedef struct {
  *                 inner_it: total Arnoldi steps
  *   relres      : GMRES residual estimate at exit
  *   true_relres : ||b - A x|| / ||b|| recomputed with an FP64 product
- *   mixed_steps : Arnoldi steps whose product used FP32 far tiles (GNK_MIXED); at most
- *                 inner_it, and in a solve that switches to mixed products part-way it
+ *   mixed_steps : Arnoldi steps whose product used FP32 far tiles or, in place of
+ *                 them, the treecode at 1e-9 (GNK_MIXED); at most inner_it, and in a solve that switches to mixed products part-way it
  *                 may include up to seven speculative steps after the column stopped
  *   refine_steps: GNK_MIXED: restart cycles of this column that took mixed products,
  *                 each followed by an FP64 residual (refinement steps); 0 for GNK_FP64
@@ -193,6 +194,8 @@ typedef struct {
  *   GNK_MIXED_THETA=t    separation factor of the far-tile test (default 1): a
  *                        source tile is far from a target tile when their
  *                        bounding circles are (1 + t)(r_t + r_s) apart
+ *                        (with this or the override above mixed solves keep to
+ *                        the pair kernels)
  *   GNK_TREE_SPLITS=s    override the treecode's splits per target tile
  * The overrides change launch shapes and the near/far split (in mixed precision,
  * which pairs are summed in FP32), never which pairs are summed. */
@@ -210,7 +213,8 @@ GNK_API const char* gnk_version(void);
  *   flops             : N(N-1) * (16 + 8 (columns - 1)) summed (16 flops per
  *                       pair and column 1, 8 per further column sharing it)
  *   launches1, ms1, pairs1 : the single-column FP64 launches alone
- *   *_mixed           : the mixed-precision launches (also in the totals)
+ *   *_mixed           : the mixed products (also in the totals; flops as of the
+ *                       direct sum where a treecode stands in for it)
  *   *_tree            : the treecode products (also in the totals; their flops
  *                       field counts the direct sum they replace): launches,
  *                       time, and the work their interaction lists imply,

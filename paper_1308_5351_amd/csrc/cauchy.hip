@@ -926,6 +926,7 @@ __global__ void k_records32(const DomDev* __restrict__ doms, int lead, int data)
   // 8 where the matrix-core sources are kept, so that the consecutive lanes of
   // a wave read and write consecutive fields
   const DomDev& D = doms[blockIdx.y];
+  if (D.treeslots) return;   // mixed products by the treecode
   const int wcols = lead + data * D.ncols;
   const int Q = D.far32 != nullptr ? (wcols + 7) / 8 * 8 : wcols;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -75,10 +75,16 @@ struct DomDev {
   int c0;            // first global column index
   int splits;        // source splits
   int symslots;      // partial-sum slots of the two-sided one-column launch (0: none)
+  int treeslots;     // splits of the treecode in mixed products (0: pair kernels)
   int chunk;         // sources per split
   int c;             // +1 bounded, -1 unbounded
   int slim;          // records are the treecode's slim ones
 };
+
+// where an epilogue finds a product's partial sums: in the splits of the pair kernels,
+// the slots of the two-sided launch, or (mixed products) the treecode's splits in the
+// domains that have it
+enum PartsOf : int { P_SPLITS = 0, P_SYM = 1, P_TREE = 2 };
 
 struct ColDev {
   int d;             // domain
@@ -156,15 +162,15 @@ hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* faroff, int64_t* nea
                             hipStream_t st);
 // multipole moments (p per box, column c at mom + c colstride) of ncols record
 // weight fields from wo on: leaves directly, then every level from its children;
-// level_off/level_nb: host arrays; active: null, or a flag on the device (0: skip)
+// level_off/level_nb: host arrays; active: null, or a flag per column (0: skip)
 hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols, int N, const double4* bounds,
                                const int* perm, const int* level_off, const int* level_nb, int levels, int p,
                                double2* mom, size_t colstride, const int* active, hipStream_t st);
 // C(k + l, l), kTreeMaxP x kTreeMaxP
 std::vector<double> tree_binomials();
 // The tiles' local expansions (loc: kTreeMaxP per tile and column, terms: per tile)
-// and the sums of weight columns col .. col + ncols - 1 (ncols 1 or 2) of doms[0];
-// flag: as `active` of launch_tree_moments, for the expansions
+// and the sums of weight columns col .. col + ncols - 1 of doms[0] (whose moments lie
+// at mom in that order); flag: as `active` of launch_tree_moments, for the expansions
 struct TreeEvalArgs {
   const double4* tb;
   const int64_t* faroff;

@@ -287,6 +287,7 @@ struct Batch {
     int* perm = nullptr;  // level-0 slot -> leaf (device)
     bool ext = false;     // targets are the points tz (no j != i window), not the nodes
   } tree;
+  std::vector<Tree> mtree;   // the domains' treecodes for mixed products (empty: none)
 };
 
 void check_domain(gnk_ctx* c, const gnk_domain* d, bool adjoint, bool second = false) {
@@ -587,6 +588,7 @@ void build_items(gnk_ctx* c, Batch& B, int p) {
     S.pair_cols += pairs * wcols;
     S.flops += pairs * (16.0 + 8.0 * (wcols - 1));
     if (wcols == 1) S.pairs1 += pairs;
+    if (p == P_GM_MIXED && D.treeslots > 0) continue;   // no items: a treecode's domain
     int r0 = 0;
     while (r0 < wcols) {
       int w = group_width(wcols - r0);
@@ -663,14 +665,12 @@ int tree_terms(double far_tol) {
   return std::max(4, std::min(kTreeMaxP, p));
 }
 
-void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
-  if (B.ndom != 1 || B.mixed) {
-    set_err(c, "the treecode takes one domain in FP64");
-    throw Fail{GNK_ERR_ARG};
-  }
-  DomDev& D = B.dom[0];
-  auto& T = B.tree;
-  const int N = D.N, tpt = B.shape.tpt, kt = 64 * tpt;
+// The boxes, lists and buffers of domain D's treecode for mcols weight columns at a
+// time, buffers named by `tag`. spare: scratch that they may take first (moments and
+// the tiles' expansions). capacity: most splits (0: any).
+void plan_tree(gnk_ctx* c, Batch::Tree& T, const DomDev& D, int tpt, double far_tol, bool ext, int mcols,
+               const std::string& tag, double2* spare, size_t spare_len, int capacity) {
+  const int N = D.N, kt = 64 * tpt;
   const int NT = ext ? D.Nt : N;   // targets
   T = Batch::Tree{};
   T.ext = ext;
@@ -684,15 +684,9 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   }
   T.levels = (int)T.nb.size();
   T.nbox = total;
-  double4* bounds = ws<double4>(c, "t_bounds", total);
-  // moments of up to two weight columns at a time
-  const int mcols = std::min(2, D.ncols + 1);
-  // (in the rest of the record buffer, which the slim records leave free, where
-  // they fit: below 37 terms; likewise the tiles' expansions)
-  double2* spare = D.rec + (size_t)N * slim_stride(D.ncols + 1);
-  size_t spare_len = (size_t)N * (rec_stride(D.ncols + 1) - slim_stride(D.ncols + 1));
-  auto carve = [&](const char* name, size_t n) {
-    if (n > spare_len) return ws<double2>(c, name, n);
+  double4* bounds = ws<double4>(c, "t_bounds" + tag, total);
+  auto carve = [&](const std::string& name, size_t n) {
+    if (n > spare_len) return ws<double2>(c, name + tag, n);
     double2* q = spare;
     spare += n;
     spare_len -= n;
@@ -707,7 +701,7 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   const int nleaf = T.nb[0];
   double4* lbox = ws<double4>(c, "t_lbox", nleaf);
   HIPCHK(c, launch_leaf_boxes(D.eta, N, nleaf, lbox, c->stream));
-  int* perm = ws<int>(c, "t_perm", nleaf);
+  int* perm = ws<int>(c, "t_perm" + tag, nleaf);
   // the sort's scratch: the moments' buffer, not yet in use, where it suffices
   const size_t hb = hilbert_scratch(nleaf);
   void* hs = hb <= sizeof(double2) * total * T.p ? (void*)T.mom : (void*)ws<char>(c, "t_hilbert", hb);
@@ -717,14 +711,15 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
                               c->stream));
   T.tiles = (NT + kt - 1) / kt;
   // about two rounds of resident workgroups
-  const int64_t resident = (int64_t)c->num_cu * 5;
-  int S = (int)std::max<int64_t>(1, std::min<int64_t>(16, (2 * resident + T.tiles - 1) / T.tiles));
+  const int64_t resident = (int64_t)c->num_cu * 5, work_items = (int64_t)T.tiles * ((mcols + 1) / 2);
+  int S = (int)std::max<int64_t>(1, std::min<int64_t>(16, (2 * resident + work_items - 1) / work_items));
   if (const char* e = getenv("GNK_TREE_SPLITS")) S = std::max(1, atoi(e));
+  if (capacity > 0) S = std::min(S, capacity);
   T.splits = S;
   const TreeListArgs la{bounds, D.tb, T.perm, T.off.data(), T.nb.data(), far_tol, kTreeTheta,
                         T.levels, T.p, N, NT, kt, T.tiles, ext};
-  int64_t* faroff = ws<int64_t>(c, "t_faroff", (size_t)T.tiles + 1);
-  int64_t* nearoff = ws<int64_t>(c, "t_nearoff", (size_t)T.tiles + 1);
+  int64_t* faroff = ws<int64_t>(c, "t_faroff" + tag, (size_t)T.tiles + 1);
+  int64_t* nearoff = ws<int64_t>(c, "t_nearoff" + tag, (size_t)T.tiles + 1);
   double* work = ws<double>(c, "t_work", T.tiles);
   volatile int64_t* len = reinterpret_cast<int64_t*>(hostio(c, 2 * sizeof(int64_t)));
   HIPCHK(c, launch_tree_count(la, faroff, nearoff, work, hostio_dev(c, const_cast<int64_t*>(len)), c->stream));
@@ -735,14 +730,14 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
   }
   // an eighth more than needed when a list's buffer grows, so that the lists of
   // other domains of the same size, a little longer, find room
-  auto room = [&](const char* name, size_t n, size_t item) {
+  auto room = [&](const std::string& name, size_t n, size_t item) {
     return !c->ws_limit && c->bufs[name].bytes < n * item ? n + n / 8 : n;
   };
-  int2* far = ws<int2>(c, "t_far", room("t_far", (size_t)len[0], sizeof(int2)));
-  int* near = ws<int>(c, "t_near", room("t_near", (size_t)len[1], sizeof(int)));
+  int2* far = ws<int2>(c, "t_far" + tag, room("t_far" + tag, (size_t)len[0], sizeof(int2)));
+  int* near = ws<int>(c, "t_near" + tag, room("t_near" + tag, (size_t)len[1], sizeof(int)));
   HIPCHK(c, launch_tree_fill(la, faroff, nearoff, far, near, c->stream));
   double2* loc = carve("t_loc", (size_t)mcols * T.tiles * kTreeMaxP);
-  int* terms = ws<int>(c, "t_terms", T.tiles);
+  int* terms = ws<int>(c, "t_terms" + tag, T.tiles);
   T.ev = TreeEvalArgs{D.tb, faroff, far, nearoff, near, bounds, T.mom, (size_t)total * T.p, T.p,
                       upload(c, "t_binom", tree_binomials()), loc, terms};
   T.flops = 0.0;
@@ -752,15 +747,77 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     for (double x : hw) T.flops += x;
   }
-  D.splits = S;
-  D.chunk = N;
+  T.on = true;
+}
+
+void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
+  if (B.ndom != 1 || B.mixed) {
+    set_err(c, "the treecode takes one domain in FP64");
+    throw Fail{GNK_ERR_ARG};
+  }
+  DomDev& D = B.dom[0];
+  // moments of up to two weight columns at a time, in the rest of the record buffer,
+  // which the slim records leave free, where they fit (below 37 terms; likewise the
+  // tiles' expansions)
+  plan_tree(c, B.tree, D, B.shape.tpt, far_tol, ext, std::min(2, D.ncols + 1), "",
+            D.rec + (size_t)D.N * slim_stride(D.ncols + 1),
+            (size_t)D.N * (rec_stride(D.ncols + 1) - slim_stride(D.ncols + 1)), 0);
+  D.splits = B.tree.splits;
+  D.chunk = D.N;
   B.sym.on = false;
   D.symslots = 0;
   D.w1 = nullptr;
   D.slim = 1;
-  D.parts = ws<double2>(c, "t_parts", (size_t)S * (D.ncols + 1) * NT);
+  D.parts = ws<double2>(c, "t_parts", (size_t)D.splits * (D.ncols + 1) * (ext ? D.Nt : D.N));
   B.d_dom = upload(c, "b_dom", B.dom);
-  T.on = true;
+}
+
+// Treecodes for the mixed products of a solve: the near field and the expansions in
+// FP64, truncated at 1e-9 of the sum of the term sizes, where FP32 far tiles leave
+// about 1e-7; the refinement by FP64 products is as it was. A domain takes it from as
+// many (node pairs x columns) as its launches are worth: with one domain 4e8 (one
+// column, a whole solve with / without: N = 16384 6.0 / 5.8 ms, 24576 11.2 / 12.7,
+// 51200 39 / 61; 8192 nodes and 4 columns 2.2 / 2.4, 16 columns 3.1 / 4.0), in a batch,
+// whose other items share one launch, 1e9 (six domains of 1e8 to 4e8 each: 5.2 ms,
+// with them from 1.5e8 on 5.7; eight of 1e9 to 2e11: 213 ms from 1e9 or 4e8 on, 224
+// from 2e9, 645 without). Not under a workspace cap, whose callers count on the pair
+// kernels' buffers, nor with the overrides of those kernels.
+constexpr double kMixedTreeTol = 1e-9;
+constexpr int kMixedTreeMinN = 4096;
+constexpr double kMixedTreePairs = 4e8, kMixedTreePairsOfMany = 1e9;
+void build_mixed_trees(gnk_ctx* c, Batch& B) {
+  if (c->ws_limit || c->arena) return;
+  for (const char* e : {"GNK_MIXED_THETA", "GNK_CAUCHY_TPT", "GNK_CAUCHY_SPLITS"})
+    if (getenv(e)) return;
+  bool any = false;
+  std::vector<Batch::Tree> trees(B.ndom);
+  for (int d = 0; d < B.ndom; ++d) {
+    DomDev& D = B.dom[d];
+    const double work = (double)D.N * (double)D.N * D.ncols;
+    if (D.N < kMixedTreeMinN || work < (B.ndom == 1 ? kMixedTreePairs : kMixedTreePairsOfMany)) continue;
+    plan_tree(c, trees[d], D, B.shape.tpt, kMixedTreeTol, false, D.ncols, "_m" + std::to_string(d), nullptr, 0,
+              D.splits);
+    D.treeslots = trees[d].splits;
+    any = true;
+  }
+  if (!any) return;
+  B.mtree = std::move(trees);
+  B.sets[P_GM_MIXED] = Batch::ItemSet{};
+  B.d_dom = upload(c, "b_dom", B.dom);
+}
+
+// the mixed products of the domains that have a treecode: all columns at a time
+void mixed_tree_pairs(gnk_ctx* c, Batch& B, const int* active) {
+  for (int d = 0; d < B.ndom; ++d) {
+    const Batch::Tree& T = B.mtree[d];
+    if (!T.on) continue;
+    const DomDev& D = B.dom[d];
+    const int* flag = active ? active + D.c0 : nullptr;
+    HIPCHK(c, launch_tree_moments(D.rec, rec_stride(D.ncols), kRecHead, D.ncols, D.N, T.ev.bounds, T.perm,
+                                  T.off.data(), T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, flag, c->stream));
+    HIPCHK(c, launch_tree_eval(B.d_dom + d, T.tiles, B.shape.tpt, T.ev, D.ncols, T.splits, 0, D.ncols, active, 0,
+                               false, flag, c->stream));
+  }
 }
 
 // the Cauchy sums of one pattern by the treecode, one weight column at a time
@@ -819,13 +876,17 @@ void pairs(gnk_ctx* c, Batch& B, int p, bool mixed, const int* active) {
   if (mixed && p == P_GM) p = P_GM_MIXED;
   build_items(c, B, p);
   auto& S = B.sets[p];
-  if (mixed) HIPCHK(c, launch_records32(B.d_dom, B.ndom, records32_threads(B, p), kLead[p], kData[p], c->stream));
+  const bool trees = p == P_GM_MIXED && !B.mtree.empty();
+  int items = 0;
+  for (int n : S.cnt) items += n;
+  if (mixed && items) HIPCHK(c, launch_records32(B.d_dom, B.ndom, records32_threads(B, p), kLead[p], kData[p], c->stream));
   gnk_ctx::ProfRec pr{};
   if (c->prof) {
     pr = gnk_ctx::ProfRec{pool_event(c), pool_event(c), S.pair_cols, S.flops, S.pairs1, mixed,
                           S.pairs1 > 0 && S.pairs1 == S.pair_cols};
     HIPCHK(c, hipEventRecord(pr.a, c->stream));
   }
+  if (trees) mixed_tree_pairs(c, B, active);
   const bool sym = use_sym(B, p, mixed);
   if (sym) HIPCHK(c, launch_pairs_sym(B.d_dom, B.sym.items, B.sym.cnt, B.sym.plan, active, c->stream));
   for (int k = kMaxWidth - 1; k >= 0; --k) {
@@ -1176,7 +1237,8 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
     const dim3 gf((unsigned)((ldp + 15) / 16), (unsigned)ncol);
     k_epilogue_dots<<<gv, kT * groups, epilogue_lds(groups, mpart ? S : 0), c->stream>>>(B.d_dom, B.d_col, V, T, form.cout, form.dsel, form.a0, form.dsign,
                                               form.cI, form.cR, mpart, S, st.active, sl.step, per_blk,
-                                              sym, P1, ldp);
+                                              sym ? P_SYM : (use_mixed && !B.mtree.empty() ? P_TREE : P_SPLITS), P1,
+                                              ldp);
     LAUNCHCHK(c);
     if (fold) k_fold_partials<<<gf, kFoldT, 0, c->stream>>>(P1, nblk, ldp, st.active, sl.step, 1, P3);
     LAUNCHCHK(c);
@@ -1192,6 +1254,7 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
   // Every buffer the step touches exists before a capture (no allocation,
   // upload or event record may happen inside it). Profiling times each pair
   // launch with events and so runs the steps without a graph.
+  if (mixed) build_mixed_trees(c, B);
   build_items(c, B, P_GM);
   if (mixed) build_items(c, B, P_GM_MIXED);
   const bool use_graph = c->graphs && !c->prof;
@@ -1243,7 +1306,7 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
     hipGraphExec_t& ge = c->step_exec[m];
     if (!fresh[m]) {
       std::vector<uint64_t> sig;
-      if (!B.tree.on) sig = step_signature(use_mixed, k);
+      if (!B.tree.on && !(use_mixed && !B.mtree.empty())) sig = step_signature(use_mixed, k);
       if (ge && !sig.empty() && c->step_sig[m] == sig) {
         fresh[m] = true;
         return ge;

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(64) void k_leaf_moments(const double2* __restrict__
                                                      const double4* __restrict__ bounds, const int* __restrict__ perm,
                                                      int nleaf, int p, double2* __restrict__ mom, size_t colstride,
                                                      const int* __restrict__ active) {
-  if (active != nullptr && *active == 0) return;
+  if (active != nullptr && active[blockIdx.y] == 0) return;
   const int b = blockIdx.x * 16 + (threadIdx.x >> 2), q = threadIdx.x & 3;
   if (b >= nleaf) return;
   const double4 c = bounds[b];
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(64) void k_m2m_levels(const double4* __restrict__ b
                                                    const int* __restrict__ active) {
   constexpr int H = P / 2;
   __shared__ double2 child[64 * (H + 1)];   // half the terms of 64 boxes at a time
-  if (active != nullptr && *active == 0) return;
+  if (active != nullptr && active[blockIdx.y] == 0) return;
   const int lane = threadIdx.x;
   const int b0 = blockIdx.x * 64 + lane;
   mom += blockIdx.y * colstride;
@@ -389,7 +389,15 @@ __global__ __launch_bounds__(256) void k_tile_locals(const double4* __restrict__
                                                      const double* __restrict__ binom, double2* __restrict__ loc,
                                                      int* __restrict__ terms, const int* __restrict__ active) {
   __shared__ double tab[kLoc * kLoc];
-  if (active != nullptr && *active == 0) return;
+  if (active != nullptr) {
+    bool any = false;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) any = any || active[blockIdx.y * NC + c] != 0;
+    if (!any) return;
+  }
+  // the launch's NC-column groups by blockIdx.y
+  mom += (size_t)blockIdx.y * NC * colstride;
+  loc += (size_t)blockIdx.y * NC * tiles * kLoc;
   for (int i = threadIdx.x; i < kLoc * kLoc; i += 256) tab[i] = binom[i];
   __syncthreads();
   const int lane = threadIdx.x & 63, row = lane >> 4, j = lane & 15;
@@ -508,10 +516,12 @@ template <int TPT, int NC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 8 : 6))) void k_tree(
     const DomDev* __restrict__ doms, const int64_t* __restrict__ nearoff, const int* __restrict__ near_,
     const double4* __restrict__ tb, const double2* __restrict__ loc, const int* __restrict__ terms, int items,
-    int splits, int col, int wcols, const int* __restrict__ active, int lead, int ext) {
+    int tiles, int splits, int col, int wcols, const int* __restrict__ active, int lead, int ext) {
   __shared__ double red[4][TPT][NC][2][64];
   constexpr int kTile = 64 * TPT;
   const DomDev& D = doms[0];
+  col += NC * blockIdx.y;
+  loc += (size_t)blockIdx.y * NC * tiles * kLoc;
   if (active != nullptr) {
     bool any = false;
 #pragma unroll
@@ -526,8 +536,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 8
   const int base = tile * kTile;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int stride = slim_stride(wcols);
-  const int wo = 1 + col;
+  const int stride = D.slim ? slim_stride(wcols) : rec_stride(wcols);
+  const int wo = (D.slim ? 1 : kRecHead) + col;
   const gptr<const double2> rec = (gptr<const double2>)D.rec;
   const cptr<int64_t> off = (cptr<int64_t>)nearoff + tile;
   const int n0 = (int)off[0];
@@ -1110,18 +1120,24 @@ hipError_t launch_tree_eval(const DomDev* doms, int tiles, int tpt, const TreeEv
   const int groups = ((tiles + 3) / 4 + 7) & ~7, items = tiles * splits;
   const unsigned lg = (unsigned)std::min(groups, 4096), grid = (unsigned)((items + 7) & ~7);
   const int e = ext ? 1 : 0;
-  if (ncols == 2)
-    k_tile_locals<2><<<lg, 256, 0, st>>>(A.tb, tiles, A.faroff, A.far, A.bounds, A.mom, A.colstride, A.p, A.binom,
-                                         A.loc, A.terms, nullptr);
-  else
-    k_tile_locals<1><<<lg, 256, 0, st>>>(A.tb, tiles, A.faroff, A.far, A.bounds, A.mom, A.colstride, A.p, A.binom,
-                                         A.loc, A.terms, flag);
-  auto run = [&](auto kern) {
-    kern<<<grid, 256, 0, st>>>(doms, A.nearoff, A.near, A.tb, A.loc, A.terms, items, splits, col, wcols, active, lead,
-                               e);
+  // the columns in twos, the last of an odd number alone
+  const int pairs = ncols / 2;
+  auto run = [&](auto two, int c0, int ny) {
+    constexpr int NC = decltype(two)::value;
+    const double2* mom = A.mom + c0 * A.colstride;
+    double2* loc = A.loc + (size_t)c0 * tiles * kLoc;
+    k_tile_locals<NC><<<dim3(lg, (unsigned)ny), 256, 0, st>>>(A.tb, tiles, A.faroff, A.far, A.bounds, mom, A.colstride,
+                                                              A.p, A.binom, loc, A.terms,
+                                                              flag ? flag + c0 : nullptr);
+    auto eval = [&](auto kern) {
+      kern<<<dim3(grid, (unsigned)ny), 256, 0, st>>>(doms, A.nearoff, A.near, A.tb, loc, A.terms, items, tiles, splits,
+                                                     col + c0, wcols, active, lead, e);
+    };
+    if (tpt == 2) eval(k_tree<2, NC>);
+    else eval(k_tree<1, NC>);
   };
-  if (tpt == 2) ncols == 2 ? run(k_tree<2, 2>) : run(k_tree<2, 1>);
-  else ncols == 2 ? run(k_tree<1, 2>) : run(k_tree<1, 1>);
+  if (pairs > 0) run(std::integral_constant<int, 2>{}, 0, pairs);
+  if (ncols & 1) run(std::integral_constant<int, 1>{}, ncols - 1, 1);
   return hipGetLastError();
 }
 

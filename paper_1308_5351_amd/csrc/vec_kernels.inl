@@ -148,14 +148,13 @@ __global__ void k_rho(const DomDev* __restrict__ doms) {
 
 // sum over the splits of weight column q (of wcols) of a domain's partial
 // sums (those with index = g0 mod gstep), added in split order; the loads go out
-// eight at a time. sym: the sums come from the two-sided one-column launch
-// (its slots in place of the splits)
+// eight at a time. sym: where the sums come from (PartsOf)
 __device__ __forceinline__ double2 reduce_parts(const DomDev& D, int wcols, int q, int i, int sym, int g0 = 0,
                                                 int gstep = 1) {
   constexpr int kG = 8;
   const gptr<const double2> p = (gptr<const double2>)D.parts + (size_t)q * D.N + i;
   const size_t gs = (size_t)wcols * D.N;
-  const int splits = sym ? D.symslots : D.splits;
+  const int splits = sym == P_SYM ? D.symslots : (sym == P_TREE && D.treeslots ? D.treeslots : D.splits);
   double2 s = make_double2(0.0, 0.0);
   for (int g = g0; g < splits; g += kG * gstep) {
     double2 v[kG];
