@@ -329,7 +329,7 @@ void check_domain(gnk_ctx* c, const gnk_domain* d, bool adjoint, bool second = f
 //
 // Small domains (32 splits would not fill the wave slots of the kernel variant
 // twice): as many splits as leave 64 sources each, at most 32, or 256 each, at most
-// 64 (300 points against 17408 nodes: 90 us at 64, 95 at 32). (8 / 16 / 32 / 64
+// 64 (300 points against 17408 nodes: 67 us at 64, 76 at 32). (8 / 16 / 32 / 64
 // splits at N = 3072: 593 / 593 / 586 / 632 us, at 6144 1002 / 944 / 916 / 996; 4 / 8 /
 // 16 at N = 512: 535 / 488 / 484.) But no round of the slots that is left less than
 // half full (11 x 600 nodes, 2 columns: 29 splits 1114 us, 32 of 1.08 rounds 1186;
@@ -2240,8 +2240,11 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
     }
     D.tb = ws<double4>(c, "f_tb", (size_t)((nz + 63) / 64));
     B.d_dom = upload(c, "b_dom", B.dom);
-    HIPCHK(c, launch_tile_bounds(B.d_dom, 1, (int)nz, 64 * B.shape.tpt, 3, c->stream));
-    if (far_tol > 0.0) build_tree(c, B, far_tol, true);
+    // (the direct sums, of two columns at least, have no far form for separate points)
+    if (far_tol > 0.0) {
+      HIPCHK(c, launch_tile_bounds(B.d_dom, 1, (int)nz, 64 * B.shape.tpt, 3, c->stream));
+      build_tree(c, B, far_tol, true);
+    }
     k_fcau_records<<<nblocks(N), kT, 0, c->stream>>>(B.d_dom, static_cast<const double2*>(f), nrhs);
     LAUNCHCHK(c);
     pairs(c, B, P_SETUP, false, nullptr);
@@ -2250,7 +2253,7 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
       const double2* h = static_cast<const double2*>(finf);
       fi = upload(c, "f_finf", std::vector<double2>(h, h + nrhs));
     }
-    k_fcau_epilogue<<<dim3(nblocks(nz), (unsigned)nrhs), kT, 0, c->stream>>>(
+    k_fcau_epilogue<<<dim3(nblocks(nz, 64), (unsigned)nrhs), 64, 0, c->stream>>>(
         B.d_dom, static_cast<const double2*>(f), nrhs, fi, (double)n, tperm, static_cast<double2*>(fz));
     LAUNCHCHK(c);
     HIPCHK(c, hipStreamSynchronize(c->stream));

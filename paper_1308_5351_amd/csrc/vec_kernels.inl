@@ -451,13 +451,27 @@ __global__ void k_fcau_epilogue(const DomDev* __restrict__ doms, const double2* 
   if (i >= Nt) return;
   const int wcols = 1 + nrhs;
   double2 p1 = make_double2(0.0, 0.0), pf = make_double2(0.0, 0.0);
-  for (int g = 0; g < D.splits; ++g) {
-    const double2 a = D.parts[((size_t)g * wcols) * Nt + i];
-    const double2 b = D.parts[((size_t)g * wcols + 1 + q) * Nt + i];
-    p1.x += a.x;
-    p1.y += a.y;
-    pf.x += b.x;
-    pf.y += b.y;
+  // the splits in order, the loads of eight at a time in flight (300 points and 17408
+  // nodes, 64 splits: the call took 90 us, now 67)
+  constexpr int kG = 8;
+  const gptr<const double2> p = (gptr<const double2>)D.parts + i;
+  const size_t gs = (size_t)wcols * Nt, fq = (size_t)(1 + q) * Nt;
+  for (int g = 0; g < D.splits; g += kG) {
+    double2 a[kG], b[kG];
+#pragma unroll
+    for (int k = 0; k < kG; ++k)
+      if (g + k < D.splits) {
+        a[k] = p[(size_t)(g + k) * gs];
+        b[k] = p[(size_t)(g + k) * gs + fq];
+      }
+#pragma unroll
+    for (int k = 0; k < kG; ++k)
+      if (g + k < D.splits) {
+        p1.x += a[k].x;
+        p1.y += a[k].y;
+        pf.x += b[k].x;
+        pf.y += b[k].y;
+      }
   }
   double2 r;
   if (finf == nullptr) {
