@@ -162,10 +162,12 @@ hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* faroff, int64_t* nea
                             hipStream_t st);
 // multipole moments (p per box, column c at mom + c colstride) of ncols record
 // weight fields from wo on: leaves directly, then every level from its children;
-// level_off/level_nb: host arrays; active: null, or a flag per column (0: skip)
+// level_off/level_nb: host arrays; binom: tree_binomials(); active: null, or a flag per
+// column (0: skip)
 hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols, int N, const double4* bounds,
                                const int* perm, const int* level_off, const int* level_nb, int levels, int p,
-                               double2* mom, size_t colstride, const int* active, hipStream_t st);
+                               double2* mom, size_t colstride, const double* binom, const int* active,
+                               hipStream_t st);
 // C(k + l, l), kTreeMaxP x kTreeMaxP
 std::vector<double> tree_binomials();
 // The tiles' local expansions (loc: kTreeMaxP per tile and column, terms: per tile)

@@ -814,7 +814,8 @@ void mixed_tree_pairs(gnk_ctx* c, Batch& B, const int* active) {
     const DomDev& D = B.dom[d];
     const int* flag = active ? active + D.c0 : nullptr;
     HIPCHK(c, launch_tree_moments(D.rec, rec_stride(D.ncols), kRecHead, D.ncols, D.N, T.ev.bounds, T.perm,
-                                  T.off.data(), T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, flag, c->stream));
+                                  T.off.data(), T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, T.ev.binom, flag,
+                                  c->stream));
     HIPCHK(c, launch_tree_eval(B.d_dom + d, T.tiles, B.shape.tpt, T.ev, D.ncols, T.splits, 0, D.ncols, active, 0,
                                false, flag, c->stream));
   }
@@ -840,7 +841,7 @@ void tree_pairs(gnk_ctx* c, Batch& B, int p, const int* active) {
     // the flag of a single data column, whose masked steps skip the expansions too
     const int* act = active && nc == 1 && col >= lead ? active + D.c0 + col - lead : nullptr;
     HIPCHK(c, launch_tree_moments(D.rec, slim_stride(wcols), 1 + col, nc, D.N, T.ev.bounds, T.perm, T.off.data(),
-                                  T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, act, c->stream));
+                                  T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, T.ev.binom, act, c->stream));
     HIPCHK(c, launch_tree_eval(B.d_dom, T.tiles, B.shape.tpt, T.ev, nc, T.splits, col, wcols, active, lead, T.ext, act,
                                c->stream));
     col += nc;

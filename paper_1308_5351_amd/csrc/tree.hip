@@ -28,6 +28,7 @@
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "gnk_device.h"
@@ -212,85 +213,6 @@ __global__ __launch_bounds__(64) void k_leaf_moments(const double2* __restrict__
     if (CH * q + k < p) o[k] = make_double2(ax[k], ay[k]);
 }
 
-// Moments of levels l0 + 1 .. l0 + nlev from those of level l0, one wavefront per
-// 64 boxes of level l0, a lane per box with its moments in registers (P >= p of
-// them): a_k of a child in its parent's terms, scaled by (r_child/r_parent)^k and
-// shifted by e = (c_child - c_parent)/r_parent,
-//   sum_{q <= k} C(k, q) e^(k - q) a_q,
-// as repeated a_k += e a_(k-1) (p^2/2 complex products, no binomials), then added
-// to its sibling's (the lane whose box index differs in that level's bit): after
-// step s every lane of 2^s holds its common ancestor. The children come in through
-// LDS, as the 64 boxes' moments are contiguous. Bound by the arithmetic of one
-// wave (2100 products of p = 33 per level), six levels a launch.
-constexpr int kM2MLevels = 6;
-template <int P>
-__global__ __launch_bounds__(64) void k_m2m_levels(const double4* __restrict__ bounds, LevelTable lt, int l0, int nlev,
-                                                   int p, double2* __restrict__ mom, size_t colstride,
-                                                   const int* __restrict__ active) {
-  constexpr int H = P / 2;
-  __shared__ double2 child[64 * (H + 1)];   // half the terms of 64 boxes at a time
-  if (active != nullptr && active[blockIdx.y] == 0) return;
-  const int lane = threadIdx.x;
-  const int b0 = blockIdx.x * 64 + lane;
-  mom += blockIdx.y * colstride;
-  double ax[P], ay[P];
-  const bool has = b0 < lt.nb[l0];
-  {
-    const int first = blockIdx.x * 64, cnt = min(64, lt.nb[l0] - first) * H;
-    const double2* m = mom + (size_t)(lt.off[l0] + first) * p;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll 6
-      for (int i = lane; i < cnt; i += 64) {
-        const int q = i / H, k = i - q * H;
-        if (h * H + k < p) child[q * (H + 1) + k] = m[(size_t)q * p + h * H + k];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < H; ++k) {
-        const double2 v = has && h * H + k < p ? child[lane * (H + 1) + k] : make_double2(0.0, 0.0);
-        ax[h * H + k] = v.x;
-        ay[h * H + k] = v.y;
-      }
-      __syncthreads();
-    }
-  }
-  for (int s = 1; s <= nlev; ++s) {
-    const int l = l0 + s, cb = b0 >> (s - 1), pb = b0 >> s;
-    const bool live = cb < lt.nb[l - 1];
-    const double4 cc = bounds[lt.off[l - 1] + (live ? cb : 0)], cp = bounds[lt.off[l] + (live ? pb : 0)];
-    const double inv = 1.0 / cp.z;
-    const double ratio = live ? cc.z * inv : 0.0;
-    const double ex = live ? (cc.x - cp.x) * inv : 0.0, ey = live ? (cc.y - cp.y) * inv : 0.0;
-    double f = ratio;
-#pragma unroll
-    for (int k = 1; k < P; ++k) {
-      ax[k] *= f;
-      ay[k] *= f;
-      f *= ratio;
-    }
-#pragma unroll
-    for (int i = 1; i < P; ++i)
-#pragma unroll
-      for (int k = P - 1; k >= i; --k) {
-        ax[k] = __builtin_fma(ex, ax[k - 1], __builtin_fma(-ey, ay[k - 1], ax[k]));
-        ay[k] = __builtin_fma(ex, ay[k - 1], __builtin_fma(ey, ax[k - 1], ay[k]));
-      }
-    const int bit = 1 << (s - 1);
-#pragma unroll
-    for (int k = 0; k < P; ++k) {
-      ax[k] += __shfl_xor(ax[k], bit, 64);
-      ay[k] += __shfl_xor(ay[k], bit, 64);
-    }
-    if ((lane & (2 * bit - 1)) == 0 && pb < lt.nb[l]) {
-      double2* o = mom + (size_t)(lt.off[l] + pb) * p;
-#pragma unroll
-      for (int k = 0; k < P; ++k)
-        if (k < p) o[k] = make_double2(ax[k], ay[k]);
-    }
-  }
-}
-
 // ---------------------------------------------------- local expansions of tiles
 // Workgroups go to the eight XCDs in turn: with this order each takes a contiguous
 // run of the n items (n a multiple of 8), whose boxes and records its L2 shares.
@@ -323,6 +245,138 @@ __device__ __forceinline__ double row_lane(double v) {
   const long long zero = 0, p = __builtin_bit_cast(long long, v);
   const long long q = __builtin_amdgcn_update_dpp(zero, p, 0x150 + K, 0xf, 0xf, true);   // row_newbcast:K
   return __builtin_bit_cast(double, q);
+}
+
+// Moments of levels l0 + 1 .. l0 + nlev from those of level l0. a_k of a child in its
+// parent's terms, scaled by (r_child/r_parent)^k and shifted by e = (c_child -
+// c_parent)/r_parent, is
+//   sum_{q <= k} C(k, q) e^(k - q) a_q,
+// formed as Horner's rule in e over q, the a_q broadcast by DPP: a row of 16 lanes per
+// child, lane j of it the terms k = j, j + 16, j + 32 (P >= p in all). A workgroup
+// takes 64 boxes of level l0, 32 rows at a time, up to their common ancestor six levels
+// on; siblings lie in neighbouring rows, and parents pass on through LDS. Bound by
+// these chains, P complex steps per level and row (a lane per box with its moments in
+// registers and a_k += e a_(k-1), p^2/2 products a level in one chain, took 35-44 us a
+// launch at 33 terms; at N = 4460544 95, 50 and 40 us, now 85, 23 and 20; at 614400
+// 34.5, now 18).
+constexpr int kM2MLevels = 6;
+
+// the table's entries C(k, q) of the four q from 4 G on
+template <int NCH, int P, int G>
+__device__ __forceinline__ void m2m_table(double (&t)[4][NCH], const double* tab, int j) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int ch = G / 4; ch < NCH; ++ch)
+      t[i][ch] = tab[(4 * G + i) * P + max(16 * ch + j - (4 * G + i), 0)];
+}
+template <int NCH, int P, int Q>
+__device__ __forceinline__ void m2m_step(double2 (&s)[NCH], const double2 (&b)[NCH], double ex, double ey,
+                                         const double (&t)[NCH], int j) {
+  constexpr int QC = Q / 16, QI = Q % 16;
+  const double bx = row_lane<QI>(b[QC].x), by = row_lane<QI>(b[QC].y);
+#pragma unroll
+  for (int ch = QC; ch < NCH; ++ch) {
+    const double nx = __builtin_fma(ex, s[ch].x, __builtin_fma(-ey, s[ch].y, t[ch] * bx));
+    const double ny = __builtin_fma(ex, s[ch].y, __builtin_fma(ey, s[ch].x, t[ch] * by));
+    const bool on = ch > QC || j >= QI;
+    s[ch].x = on ? nx : s[ch].x;
+    s[ch].y = on ? ny : s[ch].y;
+  }
+}
+// the steps of four q, the next four's entries loading meanwhile (the barriers keep the
+// broadcasts and reads of all steps from going first, past the registers)
+template <int NCH, int P, int G>
+__device__ __forceinline__ void m2m_group(double2 (&s)[NCH], const double2 (&b)[NCH], double ex, double ey,
+                                          double (&t)[2][4][NCH], const double* tab, int j) {
+  if constexpr (4 * G + 4 < P) m2m_table<NCH, P, G + 1>(t[(G + 1) & 1], tab, j);
+  __builtin_amdgcn_sched_barrier(0);
+  m2m_step<NCH, P, 4 * G>(s, b, ex, ey, t[G & 1][0], j);
+  m2m_step<NCH, P, 4 * G + 1>(s, b, ex, ey, t[G & 1][1], j);
+  m2m_step<NCH, P, 4 * G + 2>(s, b, ex, ey, t[G & 1][2], j);
+  m2m_step<NCH, P, 4 * G + 3>(s, b, ex, ey, t[G & 1][3], j);
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <int NCH, int P, int... G>
+__device__ __forceinline__ void m2m_groups(double2 (&s)[NCH], const double2 (&b)[NCH], double ex, double ey,
+                                           const double* tab, int j, std::integer_sequence<int, G...>) {
+  double t[2][4][NCH];
+  m2m_table<NCH, P, 0>(t[0], tab, j);
+  (m2m_group<NCH, P, G>(s, b, ex, ey, t, tab, j), ...);
+}
+
+constexpr int kM2MT = 512;   // 32 rows
+template <int P>
+__global__ __launch_bounds__(kM2MT) void k_m2m_levels(const double4* __restrict__ bounds, LevelTable lt, int l0,
+                                                    int nlev, int p, double2* __restrict__ mom, size_t colstride,
+                                                    const double* __restrict__ binom, const int* __restrict__ active) {
+  constexpr int NCH = (P + 15) / 16;
+  __shared__ double tab[P * P];              // tab[q][d] = C(q + d, q)
+  __shared__ double2 even[32 * P], odd[16 * P];   // parents after odd and even steps
+  __shared__ double4 box[128];               // {c, r, 1/r}: level l0 + s from 128 - (128 >> s) on
+  if (active != nullptr && active[blockIdx.y] == 0) return;
+  for (int i = threadIdx.x; i < P * P; i += kM2MT) tab[i] = binom[(i / P) * kTreeMaxP + i % P];
+  if (threadIdx.x < 127) {
+    const int s = 6 - (31 - __clz(127 - threadIdx.x));
+    const int b = blockIdx.x * (64 >> s) + threadIdx.x - (128 - (128 >> s));
+    if (s <= nlev && b < lt.nb[l0 + s]) {
+      const double4 v = bounds[lt.off[l0 + s] + b];
+      box[threadIdx.x] = make_double4(v.x, v.y, v.z, 1.0 / v.z);
+    }
+  }
+  __syncthreads();
+  mom += blockIdx.y * colstride;
+  const int row = threadIdx.x >> 4, j = threadIdx.x & 15;
+  for (int s = 1; s <= nlev; ++s) {
+    const int l = l0 + s, nc = 64 >> (s - 1), first = blockIdx.x * nc;
+    const double2* src = (s & 1) ? odd : even;
+    double2* dst = (s & 1) ? even : odd;
+    for (int r0 = 0; r0 + (row & ~3) < nc; r0 += kM2MT / 16) {   // (whole waves)
+      const int lc = r0 + row, cb = first + lc;
+      const bool live = lc < nc && cb < lt.nb[l - 1];
+      double2 b[NCH], a[NCH];
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        const int k = 16 * ch + j;
+        b[ch] = a[ch] = make_double2(0.0, 0.0);
+        if (live && k < p) b[ch] = s == 1 ? mom[(size_t)(lt.off[l - 1] + cb) * p + k] : src[lc * P + k];
+      }
+      const int at = live ? lc : 0;
+      const double4 cc = box[128 - (256 >> s) + at], cp = box[128 - (128 >> s) + (at >> 1)];
+      const double ratio = live ? cc.z * cp.w : 0.0;
+      const double ex = live ? (cc.x - cp.x) * cp.w : 0.0, ey = live ? (cc.y - cp.y) * cp.w : 0.0;
+      const double f2 = ratio * ratio, f4 = f2 * f2, f8 = f4 * f4, f16 = f8 * f8;
+      double f = (j & 1) ? ratio : 1.0;
+      f *= (j & 2) ? f2 : 1.0;
+      f *= (j & 4) ? f4 : 1.0;
+      f *= (j & 8) ? f8 : 1.0;
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        b[ch].x *= f;
+        b[ch].y *= f;
+        f *= f16;
+      }
+      m2m_groups<NCH, P>(a, b, ex, ey, tab, j, std::make_integer_sequence<int, P / 4>{});
+      // the sibling's, of the neighbouring row
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        a[ch].x += __shfl_xor(a[ch].x, 16, 64);
+        a[ch].y += __shfl_xor(a[ch].y, 16, 64);
+      }
+      if (live && (row & 1) == 0) {
+        double2* o = mom + (size_t)(lt.off[l] + (cb >> 1)) * p;
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+          const int k = 16 * ch + j;
+          if (k < p) {
+            dst[(lc >> 1) * P + k] = a[ch];
+            o[k] = a[ch];
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
 }
 
 // s[ch] += sum over the four k from 4 G on (of the lane's chunk of 16) of
@@ -1079,7 +1133,8 @@ hipError_t launch_box_bounds(const double2* eta, int N, const int* level_off, co
 
 hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols, int N, const double4* bounds,
                                const int* perm, const int* level_off, const int* level_nb, int levels, int p,
-                               double2* mom, size_t colstride, const int* active, hipStream_t st) {
+                               double2* mom, size_t colstride, const double* binom, const int* active,
+                               hipStream_t st) {
   if (levels > 32 || p > kTreeMaxP) return hipErrorInvalidValue;
   LevelTable lt{};
   for (int l = 0; l < levels; ++l) {
@@ -1095,7 +1150,7 @@ hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols
     for (int l = 0; l + 1 < levels;) {
       const int nlev = std::min(kM2MLevels, levels - 1 - l);
       const dim3 g((unsigned)((level_nb[l] + 63) / 64), (unsigned)ncols);
-      k_m2m_levels<P><<<g, 64, 0, st>>>(bounds, lt, l, nlev, p, mom, colstride, active);
+      k_m2m_levels<P><<<g, kM2MT, 0, st>>>(bounds, lt, l, nlev, p, mom, colstride, binom, active);
       l += nlev;
     }
   };
