@@ -874,36 +874,13 @@ __global__ __launch_bounds__(256) void k_far(const DomDev* __restrict__ doms, co
 // `tile` consecutive nodes (which 0, 1, 2: of the nodes into sb, tb, sbf;
 // 3: of the target points into tb); one wavefront per (tile, domain)
 __device__ __forceinline__ void tile_bounds(const DomDev& D, int tile, int which, int b) {
-  const int lane = threadIdx.x;
   const double2* pts = which == 3 ? D.tz : D.eta;
   const int np = which == 3 ? D.Nt : D.N;
   const int i0 = b * tile;
   if (i0 >= np) return;
-  const int i1 = min(np, i0 + tile);
-  double xmin = 1e300, xmax = -1e300, ymin = 1e300, ymax = -1e300;
-  for (int i = i0 + lane; i < i1; i += 64) {
-    const double2 e = pts[i];
-    xmin = fmin(xmin, e.x); xmax = fmax(xmax, e.x);
-    ymin = fmin(ymin, e.y); ymax = fmax(ymax, e.y);
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    xmin = fmin(xmin, __shfl_xor(xmin, off, 64));
-    xmax = fmax(xmax, __shfl_xor(xmax, off, 64));
-    ymin = fmin(ymin, __shfl_xor(ymin, off, 64));
-    ymax = fmax(ymax, __shfl_xor(ymax, off, 64));
-  }
-  const double cx = 0.5 * (xmin + xmax), cy = 0.5 * (ymin + ymax);
-  double r = 0.0;
-  for (int i = i0 + lane; i < i1; i += 64) {
-    const double2 e = pts[i];
-    r = fmax(r, sqrt((e.x - cx) * (e.x - cx) + (e.y - cy) * (e.y - cy)));
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) r = fmax(r, __shfl_xor(r, off, 64));
-  // widen by a relative margin so rounding of the centre cannot hide a node
+  const double4 v = wave_circle(pts, i0, min(np, i0 + tile));
   double4* out = (which == 1 || which == 3) ? D.tb : (which == 2 ? D.sbf : D.sb);
-  if (lane == 0) out[b] = make_double4(cx, cy, r * (1.0 + 1e-12) + 1e-300, 0.0);
+  if (threadIdx.x == 0) out[b] = v;
 }
 
 __global__ __launch_bounds__(64) void k_tile_bounds(const DomDev* __restrict__ doms, int tile, int which) {

@@ -26,4 +26,33 @@ __device__ __forceinline__ double refine_rcp(double d) {
   return __builtin_fma(r, e, r);
 }
 
+// bounding circle {cx, cy, r, 0} of pts[i0, i1) by one wavefront: the centre of the
+// bounding box, the radius widened by a relative margin so that rounding of the centre
+// cannot hide a point
+__device__ __forceinline__ double4 wave_circle(const double2* pts, int i0, int i1) {
+  const int lane = threadIdx.x & 63;
+  double xmin = 1e300, xmax = -1e300, ymin = 1e300, ymax = -1e300;
+  for (int i = i0 + lane; i < i1; i += 64) {
+    const double2 e = pts[i];
+    xmin = fmin(xmin, e.x); xmax = fmax(xmax, e.x);
+    ymin = fmin(ymin, e.y); ymax = fmax(ymax, e.y);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    xmin = fmin(xmin, __shfl_xor(xmin, off, 64));
+    xmax = fmax(xmax, __shfl_xor(xmax, off, 64));
+    ymin = fmin(ymin, __shfl_xor(ymin, off, 64));
+    ymax = fmax(ymax, __shfl_xor(ymax, off, 64));
+  }
+  const double cx = 0.5 * (xmin + xmax), cy = 0.5 * (ymin + ymax);
+  double r = 0.0;
+  for (int i = i0 + lane; i < i1; i += 64) {
+    const double2 e = pts[i];
+    r = fmax(r, sqrt((e.x - cx) * (e.x - cx) + (e.y - cy) * (e.y - cy)));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) r = fmax(r, __shfl_xor(r, off, 64));
+  return make_double4(cx, cy, r * (1.0 + 1e-12) + 1e-300, 0.0);
+}
+
 }  // namespace gnk

@@ -126,24 +126,36 @@ hipError_t launch_node_tile_bounds(const DomDev* doms, int ndom, int maxN, int t
 // Treecode (csrc/tree.hip): boxes of kLeaf << l nodes at level l
 constexpr int kLeaf = 64;
 constexpr int kTreeMaxP = 48;   // terms of a box's and of a tile's expansion
+// Runs of n consecutive entries cut into `per` pieces of `size` each, the last one of a
+// run shorter: piece b holds entries [first, last) of the N
+struct Pieces {
+  int n, per, size;
+  __host__ __device__ int first(int b) const { return b / per * n + b % per * size; }
+  __host__ __device__ int last(int b, int N) const {
+    const int run = b / per * n, e = run + (b % per + 1) * size;
+    return e < run + n ? (e < N ? e : N) : (run + n < N ? run + n : N);
+  }
+};
 // bounding circles of the boxes of every level (at out + level_off[l]): level
 // 0 holds the leaves in slot order (perm: slot -> leaf), box b of level l the
 // slots [b 2^l, (b + 1) 2^l); leafbox: the leaves' bounding boxes; bbox and
 // rbits: scratch of one entry per box
-hipError_t launch_box_bounds(const double2* eta, int N, const int* level_off, const int* level_nb, int levels,
-                             const double4* leafbox, const int* perm, double4* bbox, unsigned long long* rbits,
+hipError_t launch_box_bounds(const double2* eta, int N, Pieces leaves, const int* level_off, const int* level_nb,
+                             int levels, const double4* leafbox, const int* perm, double4* bbox, unsigned long long* rbits,
                              double4* out, hipStream_t st);
-// bounding boxes {xmin, xmax, ymin, ymax} of the leaves (kLeaf consecutive nodes)
-hipError_t launch_leaf_boxes(const double2* eta, int N, int nleaf, double4* leafbox, hipStream_t st);
+// bounding boxes {xmin, xmax, ymin, ymax} of the leaves (up to kLeaf consecutive nodes)
+hipError_t launch_leaf_boxes(const double2* eta, int N, Pieces leaves, int nleaf, double4* leafbox, hipStream_t st);
+// bounding circles {cx, cy, r, 0} of the tiles of consecutive nodes
+hipError_t launch_piece_circles(const double2* eta, int N, Pieces tiles, int count, double4* out, hipStream_t st);
 // perm: the n points (pts, or the centres of boxes when pts is null) in the
 // order of their positions along a Hilbert curve; scratch of hilbert_scratch(n)
 // bytes
 size_t hilbert_scratch(int64_t n);
 hipError_t launch_hilbert_order(const double2* pts, const double4* boxes, int n, void* scratch, int* perm,
                                 hipStream_t st);
-// Interaction lists of `tiles` target tiles (kt targets each, bounds tb) against
-// the boxes: far entries {box, p_e | chunks of 16 tile terms << 8} and near blocks
-// (64-node indices). Count: offsets of every tile into the two lists (tiles + 1
+// Interaction lists of the target tiles (bounds tb) against
+// the boxes: far entries {box, p_e | chunks of 16 tile terms << 8} and near leaves (first
+// node, complemented where the leaf has fewer than kLeaf nodes). Count: offsets of every tile into the two lists (tiles + 1
 // each), its work (flops: 64 p_e per chunk of a far entry, 8 kTreeMaxP per target,
 // 16 per near pair) and the lists' lengths at total[0..1] (host-mapped).
 struct TreeListArgs {
@@ -153,8 +165,8 @@ struct TreeListArgs {
   const int* level_off;   // host
   const int* level_nb;    // host
   double far_tol, theta;
-  int levels, p, N, NT, kt, tiles;
-  bool ext;
+  int levels, p, N, NT, tiles;
+  Pieces leaves, cut;   // of the nodes into leaves, of the targets into tiles
 };
 hipError_t launch_tree_count(const TreeListArgs& A, int64_t* faroff, int64_t* nearoff, double* work, int64_t* total,
                              hipStream_t st);
@@ -164,7 +176,8 @@ hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* faroff, int64_t* nea
 // weight fields from wo on: leaves directly, then every level from its children;
 // level_off/level_nb: host arrays; binom: tree_binomials(); active: null, or a flag per
 // column (0: skip)
-hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols, int N, const double4* bounds,
+hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols, int N, Pieces leaves,
+                               const double4* bounds,
                                const int* perm, const int* level_off, const int* level_nb, int levels, int p,
                                double2* mom, size_t colstride, const double* binom, const int* active,
                                hipStream_t st);
@@ -186,6 +199,7 @@ struct TreeEvalArgs {
   const double* binom;
   double2* loc;
   int* terms;
+  Pieces leaves, cut;
 };
 hipError_t launch_tree_eval(const DomDev* doms, int tiles, int tpt, const TreeEvalArgs& A, int ncols, int splits,
                             int col, int wcols, const int* active, int lead, bool ext, const int* flag,

@@ -281,6 +281,7 @@ struct Batch {
     bool on = false;
     int p = 0, levels = 0, nbox = 0, splits = 0, tiles = 0;
     std::vector<int> off, nb;
+    Pieces leaves{}, cut{};   // of the nodes, of the targets
     TreeEvalArgs ev{};
     double2* mom = nullptr;
     double flops = 0.0;   // per column (see TreeListArgs)
@@ -675,8 +676,20 @@ void plan_tree(gnk_ctx* c, Batch::Tree& T, const DomDev& D, int tpt, double far_
   T = Batch::Tree{};
   T.ext = ext;
   T.p = tree_terms(far_tol);
+  // Leaves and tiles end with their curve, where curves hold a leaf at least: one that
+  // joins the end of a curve and the start of the next is as wide as the gap, and near
+  // to all around it (70 curves of 600 nodes: the near field of a product took 158 us,
+  // now 24; a solve on 400 x 258 nodes 26 ms, now 4.0, on 100 x 1500 52 and 3.5). A cap
+  // keeps to the fewer leaves of the run of all nodes.
+  const bool curves = D.m1 > 1 && D.n >= kLeaf && (int64_t)D.m1 * D.n == N && !c->ws_limit;
+  auto cut = [&](int64_t count, bool by_curve, int size) {
+    const int64_t n = by_curve ? D.n : count;
+    return Pieces{(int)n, (int)((n + size - 1) / size), size};
+  };
+  T.leaves = cut(N, curves, kLeaf);
+  T.cut = cut(NT, curves && !ext, kt);
   int total = 0;
-  for (int nb = (N + kLeaf - 1) / kLeaf;; nb = (nb + 1) / 2) {
+  for (int nb = curves ? D.m1 * T.leaves.per : T.leaves.per;; nb = (nb + 1) / 2) {
     T.off.push_back(total);
     T.nb.push_back(nb);
     total += nb;
@@ -700,24 +713,29 @@ void plan_tree(gnk_ctx* c, Batch::Tree& T, const DomDev& D, int tpt, double far_
   // box could join boundary pieces far apart, and few boxes would be far).
   const int nleaf = T.nb[0];
   double4* lbox = ws<double4>(c, "t_lbox", nleaf);
-  HIPCHK(c, launch_leaf_boxes(D.eta, N, nleaf, lbox, c->stream));
+  HIPCHK(c, launch_leaf_boxes(D.eta, N, T.leaves, nleaf, lbox, c->stream));
   int* perm = ws<int>(c, "t_perm" + tag, nleaf);
   // the sort's scratch: the moments' buffer, not yet in use, where it suffices
   const size_t hb = hilbert_scratch(nleaf);
   void* hs = hb <= sizeof(double2) * total * T.p ? (void*)T.mom : (void*)ws<char>(c, "t_hilbert", hb);
   HIPCHK(c, launch_hilbert_order(nullptr, lbox, nleaf, hs, perm, c->stream));
   T.perm = perm;
-  HIPCHK(c, launch_box_bounds(D.eta, N, T.off.data(), T.nb.data(), T.levels, lbox, T.perm, bbox, rbits, bounds,
-                              c->stream));
-  T.tiles = (NT + kt - 1) / kt;
+  HIPCHK(c, launch_box_bounds(D.eta, N, T.leaves, T.off.data(), T.nb.data(), T.levels, lbox, T.perm, bbox, rbits,
+                              bounds, c->stream));
+  T.tiles = T.cut.n == NT ? T.cut.per : D.m1 * T.cut.per;
+  double4* tb = D.tb;   // (of tiles of kt consecutive targets, whatever the curves)
+  if (T.cut.n != NT && D.n % kt) {
+    tb = ws<double4>(c, "t_tb" + tag, T.tiles);
+    HIPCHK(c, launch_piece_circles(D.eta, N, T.cut, T.tiles, tb, c->stream));
+  }
   // about two rounds of resident workgroups
   const int64_t resident = (int64_t)c->num_cu * 5, work_items = (int64_t)T.tiles * ((mcols + 1) / 2);
   int S = (int)std::max<int64_t>(1, std::min<int64_t>(16, (2 * resident + work_items - 1) / work_items));
   if (const char* e = getenv("GNK_TREE_SPLITS")) S = std::max(1, atoi(e));
   if (capacity > 0) S = std::min(S, capacity);
   T.splits = S;
-  const TreeListArgs la{bounds, D.tb, T.perm, T.off.data(), T.nb.data(), far_tol, kTreeTheta,
-                        T.levels, T.p, N, NT, kt, T.tiles, ext};
+  const TreeListArgs la{bounds, tb, T.perm, T.off.data(), T.nb.data(), far_tol, kTreeTheta,
+                        T.levels, T.p, N, NT, T.tiles, T.leaves, T.cut};
   int64_t* faroff = ws<int64_t>(c, "t_faroff" + tag, (size_t)T.tiles + 1);
   int64_t* nearoff = ws<int64_t>(c, "t_nearoff" + tag, (size_t)T.tiles + 1);
   double* work = ws<double>(c, "t_work", T.tiles);
@@ -738,8 +756,8 @@ void plan_tree(gnk_ctx* c, Batch::Tree& T, const DomDev& D, int tpt, double far_
   HIPCHK(c, launch_tree_fill(la, faroff, nearoff, far, near, c->stream));
   double2* loc = carve("t_loc", (size_t)mcols * T.tiles * kTreeMaxP);
   int* terms = ws<int>(c, "t_terms" + tag, T.tiles);
-  T.ev = TreeEvalArgs{D.tb, faroff, far, nearoff, near, bounds, T.mom, (size_t)total * T.p, T.p,
-                      upload(c, "t_binom", tree_binomials()), loc, terms};
+  T.ev = TreeEvalArgs{tb, faroff, far, nearoff, near, bounds, T.mom, (size_t)total * T.p, T.p,
+                      upload(c, "t_binom", tree_binomials()), loc, terms, T.leaves, T.cut};
   T.flops = 0.0;
   if (c->prof) {
     std::vector<double> hw((size_t)T.tiles);
@@ -813,7 +831,7 @@ void mixed_tree_pairs(gnk_ctx* c, Batch& B, const int* active) {
     if (!T.on) continue;
     const DomDev& D = B.dom[d];
     const int* flag = active ? active + D.c0 : nullptr;
-    HIPCHK(c, launch_tree_moments(D.rec, rec_stride(D.ncols), kRecHead, D.ncols, D.N, T.ev.bounds, T.perm,
+    HIPCHK(c, launch_tree_moments(D.rec, rec_stride(D.ncols), kRecHead, D.ncols, D.N, T.leaves, T.ev.bounds, T.perm,
                                   T.off.data(), T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, T.ev.binom, flag,
                                   c->stream));
     HIPCHK(c, launch_tree_eval(B.d_dom + d, T.tiles, B.shape.tpt, T.ev, D.ncols, T.splits, 0, D.ncols, active, 0,
@@ -840,7 +858,7 @@ void tree_pairs(gnk_ctx* c, Batch& B, int p, const int* active) {
     const int nc = std::min(2, wcols - col);
     // the flag of a single data column, whose masked steps skip the expansions too
     const int* act = active && nc == 1 && col >= lead ? active + D.c0 + col - lead : nullptr;
-    HIPCHK(c, launch_tree_moments(D.rec, slim_stride(wcols), 1 + col, nc, D.N, T.ev.bounds, T.perm, T.off.data(),
+    HIPCHK(c, launch_tree_moments(D.rec, slim_stride(wcols), 1 + col, nc, D.N, T.leaves, T.ev.bounds, T.perm, T.off.data(),
                                   T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, T.ev.binom, act, c->stream));
     HIPCHK(c, launch_tree_eval(B.d_dom, T.tiles, B.shape.tpt, T.ev, nc, T.splits, col, wcols, active, lead, T.ext, act,
                                c->stream));
@@ -2243,6 +2261,8 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
     B.d_dom = upload(c, "b_dom", B.dom);
     // (the direct sums, of two columns at least, have no far form for separate points)
     if (far_tol > 0.0) {
+      D.m1 = (int)m1;
+      D.n = (int)n;
       HIPCHK(c, launch_tile_bounds(B.d_dom, 1, (int)nz, 64 * B.shape.tpt, 3, c->stream));
       build_tree(c, B, far_tol, true);
     }

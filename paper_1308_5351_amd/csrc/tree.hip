@@ -49,12 +49,10 @@ namespace {
 // (exact: min and max), and the radii of all levels from one pass over the
 // nodes (maxima over the waves, then an atomic maximum on the radius's bit
 // pattern, which orders non-negative doubles as unsigned integers).
-__global__ __launch_bounds__(64) void k_leaf_bbox(const double2* __restrict__ eta, int N,
+__global__ __launch_bounds__(64) void k_leaf_bbox(const double2* __restrict__ eta, int N, Pieces leaves,
                                                   double4* __restrict__ bbox) {
   const int b = blockIdx.x, lane = threadIdx.x;
-  const int i0 = b * kLeaf;
-  if (i0 >= N) return;
-  const int i1 = min(N, i0 + kLeaf);
+  const int i0 = leaves.first(b), i1 = leaves.last(b, N);
   double xmin = 1e300, xmax = -1e300, ymin = 1e300, ymax = -1e300;
   for (int i = i0 + lane; i < i1; i += 64) {
     const double2 e = eta[i];
@@ -71,6 +69,13 @@ __global__ __launch_bounds__(64) void k_leaf_bbox(const double2* __restrict__ et
     ymax = fmax(ymax, __shfl_xor(ymax, off, 64));
   }
   if (lane == 0) bbox[b] = make_double4(xmin, xmax, ymin, ymax);
+}
+
+__global__ __launch_bounds__(64) void k_piece_circles(const double2* __restrict__ eta, int N, Pieces tiles,
+                                                      double4* __restrict__ out) {
+  const int b = blockIdx.x;
+  const double4 v = wave_circle(eta, tiles.first(b), tiles.last(b, N));
+  if (threadIdx.x == 0) out[b] = v;
 }
 
 __global__ void k_bbox_gather(const double4* __restrict__ leafbox, const int* __restrict__ perm, int nleaf,
@@ -109,8 +114,8 @@ struct LevelTable {
 // lie in one box, whose maximum the block forms before its atomic (one atomic a
 // leaf would queue 70000 of them on the top box of 4460544 nodes).
 constexpr int kRadiiWaves = 16;
-__global__ __launch_bounds__(64 * kRadiiWaves) void k_box_radii(const double2* __restrict__ eta, int N, LevelTable lv,
-                                                                int levels, int nleaf, const int* __restrict__ perm,
+__global__ __launch_bounds__(64 * kRadiiWaves) void k_box_radii(const double2* __restrict__ eta, int N,
+                                                                Pieces leaves, LevelTable lv, int levels, int nleaf, const int* __restrict__ perm,
                                                                 const double4* __restrict__ out,
                                                                 unsigned long long* __restrict__ rbits) {
   static_assert(kLeaf == 64, "one node per lane");
@@ -118,8 +123,8 @@ __global__ __launch_bounds__(64 * kRadiiWaves) void k_box_radii(const double2* _
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int slot = blockIdx.x * kRadiiWaves + wv;
   const bool has = slot < nleaf;
-  const int i = has ? perm[slot] * kLeaf + lane : N;
-  const bool in = i < N;
+  const int i = has ? leaves.first(perm[slot]) + lane : N;
+  const bool in = has && i < leaves.last(perm[slot], N);
   const double2 e = in ? eta[i] : make_double2(0.0, 0.0);
   for (int l = 0; l < levels; ++l) {
     const double4 c = out[lv.off[l] + (has ? slot >> l : 0)];
@@ -158,7 +163,7 @@ __global__ void k_box_finish(const unsigned long long* __restrict__ rbits, int n
 // loads (32 bytes a node with one column).
 template <int CH>
 __global__ __launch_bounds__(64) void k_leaf_moments(const double2* __restrict__ rec, int stride, int wo, int N,
-                                                     const double4* __restrict__ bounds, const int* __restrict__ perm,
+                                                     Pieces leaves, const double4* __restrict__ bounds, const int* __restrict__ perm,
                                                      int nleaf, int p, double2* __restrict__ mom, size_t colstride,
                                                      const int* __restrict__ active) {
   if (active != nullptr && active[blockIdx.y] == 0) return;
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(64) void k_leaf_moments(const double2* __restrict__
   if (b >= nleaf) return;
   const double4 c = bounds[b];
   const double inv = 1.0 / c.z;
-  const int j0 = perm[b] * kLeaf, j1 = min(N, j0 + kLeaf);
+  const int j0 = leaves.first(perm[b]), j1 = leaves.last(perm[b], N);
   const int w0 = wo + blockIdx.y;
   double ax[CH], ay[CH];
 #pragma unroll
@@ -555,7 +560,7 @@ __global__ __launch_bounds__(256) void k_tile_locals(const double4* __restrict__
 
 // One workgroup per (target tile, split), weight columns col .. col + NC - 1: wave
 // wv takes the range 4 split + wv of 4 splits equal ranges (in fours) of the
-// tile's near sources, 64-node blocks summed directly. In the first split wave t
+// tile's near sources, leaf by leaf, summed directly. In the first split wave t
 // adds the tile's local expansion at the targets of the lanes' t-th set. Partial
 // sums go to slot split, like the direct kernels'.
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -570,9 +575,9 @@ template <int TPT, int NC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 8 : 6))) void k_tree(
     const DomDev* __restrict__ doms, const int64_t* __restrict__ nearoff, const int* __restrict__ near_,
     const double4* __restrict__ tb, const double2* __restrict__ loc, const int* __restrict__ terms, int items,
-    int tiles, int splits, int col, int wcols, const int* __restrict__ active, int lead, int ext) {
+    int tiles, int splits, int col, int wcols, const int* __restrict__ active, int lead, int ext, int curve,
+    Pieces cut) {
   __shared__ double red[4][TPT][NC][2][64];
-  constexpr int kTile = 64 * TPT;
   const DomDev& D = doms[0];
   col += NC * blockIdx.y;
   loc += (size_t)blockIdx.y * NC * tiles * kLoc;
@@ -587,7 +592,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 8
   const int item = xcd_order(blockIdx.x, gridDim.x);
   if (item >= items) return;
   const int tile = item / splits, g = item - tile * splits;
-  const int base = tile * kTile;
+  const int base = cut.first(tile), end = cut.last(tile, NT);
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int stride = D.slim ? slim_stride(wcols) : rec_stride(wcols);
@@ -603,7 +608,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 8
 #pragma unroll
   for (int t = 0; t < TPT; ++t) {
     ti[t] = base + t * 64 + lane;
-    tg[t] = ext ? D.tz[min(ti[t], NT - 1)] : D.eta[min(ti[t], N - 1)];
+    tg[t] = ext ? D.tz[min(ti[t], end - 1)] : D.eta[min(ti[t], end - 1)];
   }
   Acc<NC, TPT> acc;
 #pragma unroll
@@ -627,17 +632,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 8
   const cptr<int> nl = (cptr<int>)near_ + n0;
   for (int u = u0; u < u1;) {
     const int ue = min(u1, (u | 63) + 1);
-    const int blk = nl[u >> 6] * 64;
-    const int ja = blk + (u & 63), jb = min(N, blk + ((ue - 1) & 63) + 1);
+    // (a short leaf ends its curve)
+    const int v = nl[u >> 6], blk = v < 0 ? ~v : v;
+    const int bend = v < 0 ? min(N, (blk / curve + 1) * curve) : blk + kLeaf;
+    const int ja = min(bend, blk + (u & 63)), jb = min(bend, blk + ((ue - 1) & 63) + 1);
     u = ue;
     if (ext) {
       plain(ja, jb);
       continue;
     }
     plain(ja, min(jb, base));
-    const int ma = max(ja, base), mb = min(jb, base + kTile);
+    const int ma = max(ja, base), mb = min(jb, end);
     for (int j = ma; j < mb; ++j) single_step<NC, TPT>(acc, tg, ti, rec + (size_t)j * stride, wo, j, true);
-    plain(max(ja, base + kTile), jb);
+    plain(max(ja, end), jb);
   }
 #pragma unroll
   for (int t = 0; t < TPT; ++t)
@@ -680,7 +687,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 8
       x += red[q][wv][c][0][lane];
       y += red[q][wv][c][1][lane];
     }
-    if (i < NT) D.parts[((size_t)g * wcols + col + c) * NT + i] = make_double2(x, y);
+    if (i < end) D.parts[((size_t)g * wcols + col + c) * NT + i] = make_double2(x, y);
   }
 }
 
@@ -923,7 +930,8 @@ struct TreeWalk {
   double thr[kTreeMaxP + 1];   // far_tol^(1/k)
   double qthr[2];              // (far_tol/64)^(1/16), ^(1/32)
   double f2;                   // (1 + theta)^2
-  int levels, p, N, NT, kt, tiles, ext;
+  int levels, p, N, NT, tiles;
+  Pieces leaves, cut;
 };
 
 __device__ __forceinline__ int wave_prefix(int v, int lane, int* total) {
@@ -952,7 +960,7 @@ __global__ __launch_bounds__(256) void k_tree_lists(TreeWalk W, int64_t* __restr
   int* st = stk + wv * 128 * W.levels;
   int* cnt = left[wv];
   const double4 tt = W.tb[t];
-  const double nt = (double)min(W.kt, W.NT - t * W.kt);
+  const double nt = (double)(W.cut.last(t, W.NT) - W.cut.first(t));
   int64_t f = FILL ? nfar[t] : 0, n = FILL ? nnear[t] : 0;
   double wk = 0.0;
   int l = W.levels - 1, sp = 1;   // level of the stack's top, boxes on it
@@ -984,7 +992,7 @@ __global__ __launch_bounds__(256) void k_tree_lists(TreeWalk W, int64_t* __restr
         if (!FILL) wk += 64.0 * pe * nq;
       } else if (l == 0) {
         is_near = true;
-        if (!FILL) wk += 16.0 * nt * min(kLeaf, W.N - W.perm[b] * kLeaf);
+        if (!FILL) wk += 16.0 * nt * (W.leaves.last(W.perm[b], W.N) - W.leaves.first(W.perm[b]));
       } else {
         nch = 2 * b + 1 < W.nb[l - 1] ? 2 : 1;
       }
@@ -992,7 +1000,10 @@ __global__ __launch_bounds__(256) void k_tree_lists(TreeWalk W, int64_t* __restr
     const unsigned long long below = (1ull << lane) - 1ull, mf = __ballot(is_far), mn = __ballot(is_near);
     if (FILL) {
       if (is_far) far[f + __popcll(mf & below)] = make_int2(g, pe | (nq << 8));
-      if (is_near) near_[n + __popcll(mn & below)] = W.perm[b];
+      if (is_near) {
+        const int a = W.leaves.first(W.perm[b]);
+        near_[n + __popcll(mn & below)] = W.leaves.last(W.perm[b], W.N) - a < kLeaf ? ~a : a;
+      }
     }
     f += __popcll(mf);
     n += __popcll(mn);
@@ -1082,9 +1093,9 @@ static TreeWalk tree_walk(const TreeListArgs& A) {
   W.p = A.p;
   W.N = A.N;
   W.NT = A.NT;
-  W.kt = A.kt;
   W.tiles = A.tiles;
-  W.ext = A.ext ? 1 : 0;
+  W.leaves = A.leaves;
+  W.cut = A.cut;
   return W;
 }
 
@@ -1102,13 +1113,18 @@ hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* nfar, int64_t* nnear
   return hipGetLastError();
 }
 
-hipError_t launch_leaf_boxes(const double2* eta, int N, int nleaf, double4* leafbox, hipStream_t st) {
-  k_leaf_bbox<<<nleaf, 64, 0, st>>>(eta, N, leafbox);
+hipError_t launch_leaf_boxes(const double2* eta, int N, Pieces leaves, int nleaf, double4* leafbox, hipStream_t st) {
+  k_leaf_bbox<<<nleaf, 64, 0, st>>>(eta, N, leaves, leafbox);
   return hipGetLastError();
 }
 
-hipError_t launch_box_bounds(const double2* eta, int N, const int* level_off, const int* level_nb, int levels,
-                             const double4* leafbox, const int* perm, double4* bbox, unsigned long long* rbits,
+hipError_t launch_piece_circles(const double2* eta, int N, Pieces tiles, int count, double4* out, hipStream_t st) {
+  k_piece_circles<<<count, 64, 0, st>>>(eta, N, tiles, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_box_bounds(const double2* eta, int N, Pieces leaves, const int* level_off, const int* level_nb,
+                             int levels, const double4* leafbox, const int* perm, double4* bbox, unsigned long long* rbits,
                              double4* out, hipStream_t st) {
   if (levels < 1 || levels > 32) return hipErrorInvalidValue;
   k_bbox_gather<<<(level_nb[0] + 255) / 256, 256, 0, st>>>(leafbox, perm, level_nb[0], bbox);
@@ -1124,14 +1140,15 @@ hipError_t launch_box_bounds(const double2* eta, int N, const int* level_off, co
   if ((e = hipGetLastError()) != hipSuccess) return e;
   LevelTable lv{};
   for (int l = 0; l < levels; ++l) lv.off[l] = level_off[l];
-  k_box_radii<<<(level_nb[0] + kRadiiWaves - 1) / kRadiiWaves, 64 * kRadiiWaves, 0, st>>>(eta, N, lv, levels,
-                                                                                         level_nb[0], perm, out, rbits);
+  k_box_radii<<<(level_nb[0] + kRadiiWaves - 1) / kRadiiWaves, 64 * kRadiiWaves, 0, st>>>(
+      eta, N, leaves, lv, levels, level_nb[0], perm, out, rbits);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   k_box_finish<<<(nbox + 255) / 256, 256, 0, st>>>(rbits, nbox, out);
   return hipGetLastError();
 }
 
-hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols, int N, const double4* bounds,
+hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols, int N, Pieces leaves,
+                               const double4* bounds,
                                const int* perm, const int* level_off, const int* level_nb, int levels, int p,
                                double2* mom, size_t colstride, const double* binom, const int* active,
                                hipStream_t st) {
@@ -1145,7 +1162,7 @@ hipError_t launch_tree_moments(const double2* rec, int stride, int wo, int ncols
   auto run = [&](auto terms) {
     constexpr int P = decltype(terms)::value;
     const dim3 grid((unsigned)((level_nb[0] + 15) / 16), (unsigned)ncols);
-    k_leaf_moments<P / 4><<<grid, 64, 0, st>>>(rec, stride, wo, N, bounds, perm, level_nb[0], p, mom, colstride,
+    k_leaf_moments<P / 4><<<grid, 64, 0, st>>>(rec, stride, wo, N, leaves, bounds, perm, level_nb[0], p, mom, colstride,
                                                active);
     for (int l = 0; l + 1 < levels;) {
       const int nlev = std::min(kM2MLevels, levels - 1 - l);
@@ -1186,7 +1203,7 @@ hipError_t launch_tree_eval(const DomDev* doms, int tiles, int tpt, const TreeEv
                                                               flag ? flag + c0 : nullptr);
     auto eval = [&](auto kern) {
       kern<<<dim3(grid, (unsigned)ny), 256, 0, st>>>(doms, A.nearoff, A.near, A.tb, loc, A.terms, items, tiles, splits,
-                                                     col + c0, wcols, active, lead, e);
+                                                     col + c0, wcols, active, lead, e, A.leaves.n, A.cut);
     };
     if (tpt == 2) eval(k_tree<2, NC>);
     else eval(k_tree<1, NC>);
