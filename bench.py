@@ -45,9 +45,9 @@ FLOPS_PER_PAIR = 16.0            # one column: 2 sub, |d|^2 (3), reciprocal (1),
 # size, from two rocprofv3 --pmc runs (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000
 # KiB, the factors from a 256 MiB copy of known size; profiles/*_hbm_counters.md).
 # Valid only for that N and the kernel sources they were taken on (hash below), else null.
-PAIR_TRAFFIC = {"sources": ("cauchy.hip", "pair_steps.inl", "gnk_device.h", "gnk_internal.h"),
-                "sha256": "ee869c570c521e57036ff54079c03cab365223db8583a3842d9b03f430a3ae44",
-                "N": 264192, "bytes_per_launch": 518457089}
+PAIR_TRAFFIC = {"sources": ("pairs_sym.hip", "gnk_device.h", "gnk_internal.h"),
+                "sha256": "ad79ea4be3d5d9a3f8f8c5738301587c2e656db3200f92e00ca9a2c559e3948e",
+                "N": 264192, "bytes_per_launch": 5961104169}
 
 
 def pair_traffic(N):
@@ -709,7 +709,7 @@ def main():
                                "each), n=2048, N=264192, A=1, gamma=Re(eta^2); step = FBIE in FP64 (right-hand "
                                "side, GMRES restart 60 to tol 1e-13, h), every pair summed directly",
                    "N": dom.N, "m1": dom.m1, "n": dom.n, "precision": "fp64"},
-        "matvec": {"kernel": "k_pairs<1, TPT, M_FP64> (FP64, one column)", "avg_ms": round(avg1_ms, 4),
+        "matvec": {"kernel": "k_pairs_sym<8> (FP64, one column, every unordered pair once)", "avg_ms": round(avg1_ms, 4),
                    "gpair_s": round(pairs1 / (avg1_ms * 1e-3) / 1e9, 2),
                    "frac_fp64_peak": round(achieved / FP64_PEAK_TFLOPS, 4),
                    "launches_per_step": prof["launches"] / args.steps,

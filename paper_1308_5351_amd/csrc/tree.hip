@@ -1,9 +1,9 @@
 // Far-field compression of the Cauchy sums S_i = sum_{j != i} w_j/(eta_i - eta_j)
 // for large N (the paper evaluates these sums with a fast multipole method;
 // this is a treecode on the GPU, FP64 throughout):
-//   * boxes: level 0 holds the leaves of kLeaf = 64 consecutive nodes (the
-//     node order follows the boundary curves, so a range of nodes is compact),
-//     level l + 1 pairs the boxes of level l; each box has a bounding circle;
+//   * boxes: level 0 holds the leaves of up to kLeaf = 64 consecutive nodes of a
+//     curve (of fewer than 64 nodes a curve: across curves), level l + 1 pairs the
+//     boxes of level l; each box has a bounding circle;
 //   * multipole moments of box b about its centre c_b in units of its radius r_b,
 //     for one weight column: a_k = sum_{j in b} w_j ((eta_j - c_b)/r_b)^k, k < p;
 //     leaves from their nodes, parents from their children by the binomial shift;
@@ -13,7 +13,7 @@
 //     truncated on the box's side with error below (r_b/(|D| - r_t))^p_e and on
 //     the tile's side below (r_t/(|D| - r_b))^q_e, each times a factor of at most
 //     2.4 and sum |w_j|/|z - eta_j|; the expansion is evaluated once per target;
-//   * every other source is summed directly, in blocks of 64 nodes, by the
+//   * every other source is summed directly, leaf by leaf, by the
 //     FP64 pair loops (j != i excluded);
 //   * the order of the leaves (and of separate targets) along a Hilbert curve
 //     and the interaction lists (far boxes and near blocks per target tile) are
@@ -24,7 +24,7 @@
 // Local expansions instead of evaluating every far box at every target (4 p_e +
 // 14 operations each), and leaves of 64 nodes instead of 256: at 1089 x 4096 nodes
 // a target meets 506 near sources and 145 boxes instead of 1020 and 115, and a
-// product took 2.6 ms instead of 5.3 (near sums 1.2, expansions 1.1, moments 0.3).
+// product took 2.6 ms instead of 5.3; now 2.2 (near sums 1.05, expansions 0.9, moments 0.2).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -42,7 +42,7 @@ namespace {
 
 // Bounding circles {cx, cy, r, 0} of the boxes of every level: the centre of
 // the box's bounding box and the largest distance of its nodes from it. The
-// leaves (kLeaf consecutive nodes) take the slots of level 0 in an order chosen
+// leaves (up to kLeaf consecutive nodes) take the slots of level 0 in an order chosen
 // by their centres (perm: slot -> leaf); the box of slots
 // [b 2^l, (b + 1) 2^l) is box b of level l. Leaf bounding boxes come from
 // their nodes (one wavefront per leaf), a parent's from its two children
