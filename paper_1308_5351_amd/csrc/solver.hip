@@ -813,8 +813,26 @@ void build_mixed_trees(gnk_ctx* c, Batch& B) {
     DomDev& D = B.dom[d];
     const double work = (double)D.N * (double)D.N * D.ncols;
     if (D.N < kMixedTreeMinN || work < (B.ndom == 1 ? kMixedTreePairs : kMixedTreePairsOfMany)) continue;
-    plan_tree(c, trees[d], D, B.shape.tpt, kMixedTreeTol, false, D.ncols, "_m" + std::to_string(d), nullptr, 0,
-              D.splits);
+    const std::string tag = "_m" + std::to_string(d);
+    try {
+      plan_tree(c, trees[d], D, B.shape.tpt, kMixedTreeTol, false, D.ncols, tag, nullptr, 0, D.splits);
+    } catch (const Fail& f) {
+      // no memory left for it: the pair kernels take the domain, as they would have
+      if (f.st != GNK_ERR_OOM) throw;
+      HIPCHK(c, hipStreamSynchronize(c->stream));
+      for (const char* n : {"t_bounds", "t_mom", "t_perm", "t_faroff", "t_nearoff", "t_far", "t_near", "t_loc",
+                            "t_terms", "t_tb"}) {
+        auto it = c->bufs.find(n + tag);
+        if (it == c->bufs.end()) continue;
+        if (it->second.p) {
+          HIPCHK(c, hipFree(it->second.p));
+          c->ws_bytes -= it->second.bytes;
+        }
+        c->bufs.erase(it);
+      }
+      trees[d] = Batch::Tree{};
+      continue;
+    }
     D.treeslots = trees[d].splits;
     any = true;
   }
