@@ -349,9 +349,13 @@ void check_domain(gnk_ctx* c, const gnk_domain* d, bool adjoint, bool second = f
 // and for mixed products, whose chunks are whole 256-node groups.
 // Nt targets against Ns sources (the nodes, or separate points for the Cauchy
 // integral at interior points)
-void plan_pairs(gnk_ctx* c, int64_t Nt, int64_t Ns, int align, int width, bool mixed, int* tpt, int* chunk,
+void plan_pairs(gnk_ctx* c, int64_t Nt, int64_t Ns, int align, int cols, bool mixed, int* tpt, int* chunk,
                 int* splits) {
-  const bool roomy = !mixed && !c->arena && !c->ws_limit;
+  const bool scarce = c->arena || c->ws_limit, roomy = !mixed && !scarce;
+  // the column group whose variant sets the wave slots (scarce: of 8, 4, 2 or 1, so
+  // that no column count takes more splits than it did)
+  const int width = scarce ? (cols >= 8 ? 8 : (cols >= 4 ? 4 : (cols >= 2 ? 2 : 1)))
+                           : (mixed ? std::min(cols, kMaxWidth) : group_width(cols));
   int t = roomy ? (Nt >= (width == 1 ? 1024 : 2048) ? 2 : 1) : (((Nt + 127) / 128) * 64 >= slots_of(c) ? 2 : 1);
   if (const char* s = getenv("GNK_CAUCHY_TPT")) t = atoi(s) == 2 ? 2 : 1;
   // wave slots of the variant that runs the products (its register use sets
@@ -383,8 +387,8 @@ void plan_pairs(gnk_ctx* c, int64_t Nt, int64_t Ns, int align, int width, bool m
   *chunk = (int)ch;
   *splits = (int)((Ns + ch - 1) / ch);
 }
-void plan_single(gnk_ctx* c, int64_t N, int align, int width, bool mixed, int* tpt, int* chunk, int* splits) {
-  plan_pairs(c, N, N, align, width, mixed, tpt, chunk, splits);
+void plan_single(gnk_ctx* c, int64_t N, int align, int cols, bool mixed, int* tpt, int* chunk, int* splits) {
+  plan_pairs(c, N, N, align, cols, mixed, tpt, chunk, splits);
 }
 
 // Two-sided one-column sums (csrc/pairs_sym.hip): the plan of N nodes and its
@@ -484,8 +488,7 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
     c0 += ncols[d];
     if (ndom == 1 && shape.chunk == 0) {
       int t, ch, sp;
-      const int width = mixed ? std::min(ncols[d], kMaxWidth) : group_width(ncols[d]);
-      plan_single(c, D.N, align, width, mixed, &t, &ch, &sp);
+      plan_single(c, D.N, align, ncols[d], mixed, &t, &ch, &sp);
       B.shape.tpt = t;
       D.chunk = ch;
       D.splits = sp;
@@ -2247,7 +2250,7 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
     d.etap = d.A = etap;
     const int wcols = 1 + nrhs;
     int t, ch, sp;
-    plan_pairs(c, nz, N, 16, group_width(wcols), false, &t, &ch, &sp);
+    plan_pairs(c, nz, N, 16, wcols, false, &t, &ch, &sp);
     // tiles of 64 points for the treecode: they cover more of the plane than as many
     // nodes of a curve, and smaller tiles meet fewer near sources (289 x 1024 nodes
     // at 200003 points: 1600 and 3070 near sources per point, 1.08 and 1.19 ms)
