@@ -365,7 +365,8 @@ void plan_pairs(gnk_ctx* c, int64_t Nt, int64_t Ns, int align, int cols, bool mi
   const int64_t few = std::max({(int64_t)1, std::min<int64_t>(32, Ns / 64), std::min<int64_t>(64, Ns / 256)});
   int64_t bs = 0;
   if (roomy && (double)(tiles * few * 4) < 1.9 * (double)slots) {
-    bs = tiles * few * 4 > slots && 2 * tiles * few * 4 < 3 * slots ? slots / (4 * tiles) : few;
+    // (a single split of few sources may by itself overfill a round)
+    bs = tiles * few * 4 > slots && 2 * tiles * few * 4 < 3 * slots ? std::max<int64_t>(1, slots / (4 * tiles)) : few;
   } else {
     const int64_t max_s = std::max<int64_t>(1, std::min<int64_t>(64, Ns / 128));
     std::vector<double> score((size_t)max_s + 1, 0.0), rounds((size_t)max_s + 1, 0.0);
