@@ -515,9 +515,10 @@ __device__ __forceinline__ void pair_item(gptr<const double2> rec, gptr<const fl
         quad_step<NR, TPT>(acc, tg, r, r + stride, r + 2 * stride, r + 3 * stride, wo);
       } else {
         // four wide records would not fit in scalar registers together
-        if constexpr (NR != 4 && TPT % 2 == 0) {
+        if constexpr (!EXT && NR != 4 && TPT % 2 == 0) {
           // one reciprocal for two sources and two targets (4 columns: the
-          // extra registers cost a wave per SIMD)
+          // extra registers cost a wave per SIMD; separate points: one on a node,
+          // which takes the node's value in the end, must not spoil the lane's other)
           pair_step_t2<NR, TPT>(acc, tg, r, r + stride, wo);
           pair_step_t2<NR, TPT>(acc, tg, r + 2 * stride, r + 3 * stride, wo);
         } else {
