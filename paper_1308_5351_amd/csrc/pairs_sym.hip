@@ -307,8 +307,8 @@ __global__ __launch_bounds__(256, T == 8 ? 2 : 3) void k_pairs_sym(const DomDev*
       c -= c >= nchunk ? nchunk : 0;
       int d = c / (4 * T) - it.x;
       d += d < 0 ? P.nb : 0;
-      // (a wave past the last node holds zero weights on the last node's place)
-      xch[wv][lane] = chunk_pair<T>(g, L, sb, far2, own0, c, nchunk);
+      // (a wave past the last node has no tile whose distance would tell far from near)
+      xch[wv][lane] = own0 < N ? chunk_pair<T>(g, L, sb, far2, own0, c, nchunk) : make_double2(0.0, 0.0);
       __syncthreads();
       if (wv == (q & 3)) {
         const double2 a0 = xch[0][lane], a1 = xch[1][lane], a2 = xch[2][lane], a3 = xch[3][lane];
