@@ -36,6 +36,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 #include <vector>
 
 #include "gnk_device.h"
@@ -497,13 +498,20 @@ __device__ __forceinline__ void pair_item(gptr<const double2> rec, gptr<const fl
     tg[t] = pts[min(ti[t], NT - 1)];
   }
   Acc<NR, TPT> acc;
+  auto clear = [&] {
 #pragma unroll
-  for (int t = 0; t < TPT; ++t)
+    for (int t = 0; t < TPT; ++t)
 #pragma unroll
-    for (int r = 0; r < NR; ++r) { acc.x[t][r] = 0.0; acc.y[t][r] = 0.0; }
+      for (int r = 0; r < NR; ++r) { acc.x[t][r] = 0.0; acc.y[t][r] = 0.0; }
+  };
+  clear();
+  // one reciprocal for two sources and two targets (4 columns: the extra registers cost
+  // a wave per SIMD; separate points: one on a node, which takes the node's value in the
+  // end, must not spoil the lane's other)
+  constexpr bool kPairedTargets = MODE == M_FP64 && NR > 2 && NR != 4 && TPT % 2 == 0;
 
   // sources outside the tile's own window need no j != i test
-  auto plain = [&](int ja, int jb) {
+  auto plain = [&](int ja, int jb, auto paired) {
     if constexpr (MODE == M_NEAR && NR >= 8 && TPT % 2 == 0) {
       stream_range<NR, TPT>(acc, tg, rec, stride, wo, ja, jb);
       return;
@@ -515,10 +523,7 @@ __device__ __forceinline__ void pair_item(gptr<const double2> rec, gptr<const fl
         quad_step<NR, TPT>(acc, tg, r, r + stride, r + 2 * stride, r + 3 * stride, wo);
       } else {
         // four wide records would not fit in scalar registers together
-        if constexpr (!EXT && NR != 4 && TPT % 2 == 0) {
-          // one reciprocal for two sources and two targets (4 columns: the
-          // extra registers cost a wave per SIMD; separate points: one on a node,
-          // which takes the node's value in the end, must not spoil the lane's other)
+        if constexpr (decltype(paired)::value) {
           pair_step_t2<NR, TPT>(acc, tg, r, r + stride, wo);
           pair_step_t2<NR, TPT>(acc, tg, r + 2 * stride, r + 3 * stride, wo);
         } else {
@@ -533,16 +538,17 @@ __device__ __forceinline__ void pair_item(gptr<const double2> rec, gptr<const fl
     }
     if (j < jb) single_step<NR, TPT>(acc, tg, ti, rec + (size_t)j * stride, wo, j, false);
   };
-  auto fp64_range = [&](int ja, int jb) {
+  auto range_by = [&](int ja, int jb, auto paired) {
     if constexpr (EXT) {
-      plain(ja, jb);
+      plain(ja, jb, paired);
       return;
     }
-    plain(ja, min(jb, base));
+    plain(ja, min(jb, base), paired);
     const int ma = max(ja, base), mb = min(jb, base + kTile);
     for (int j = ma; j < mb; ++j) single_step<NR, TPT>(acc, tg, ti, rec + (size_t)j * stride, wo, j, true);
-    plain(max(ja, base + kTile), jb);
+    plain(max(ja, base + kTile), jb, paired);
   };
+  auto fp64_range = [&](int ja, int jb) { range_by(ja, jb, std::false_type{}); };
 
   bool any_near = false;
   if constexpr (!MIXED && (NR == 1 || (NR == 2 && !EXT))) {
@@ -594,6 +600,21 @@ __device__ __forceinline__ void pair_item(gptr<const double2> rec, gptr<const fl
         fp64_range(ts, te);
       }
       ts = te;
+    }
+  } else if constexpr (kPairedTargets) {
+    range_by(j0, j1, std::true_type{});
+    // a node in the place of a target spoils the lane's two targets: a range that leaves
+    // a sum non-finite is taken again with reciprocals of their own, which keeps that to
+    // the one
+    double all = 0.0;
+#pragma unroll
+    for (int t = 0; t < TPT; ++t)
+      if (ti[t] < NT)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) all += acc.x[t][r] + acc.y[t][r];
+    if (__any(!isfinite(all))) {
+      clear();
+      fp64_range(j0, j1);
     }
   } else if (!MIXED) {
     fp64_range(j0, j1);

@@ -78,6 +78,12 @@ __device__ __forceinline__ void inverse4(const double (&d)[4], double (&m)[4]) {
   m[3] = r1 * d[2];
 }
 
+// the same with a reciprocal for each: one zero distance leaves the others' inverses
+__device__ __forceinline__ void inverse4_apart(const double (&d)[4], double (&m)[4]) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) m[v] = refine_rcp(d[v]);
+}
+
 __device__ __forceinline__ double2 zmul_conj(double2 a, double2 b) {   // a conj(b)
   return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
@@ -181,33 +187,14 @@ __device__ __forceinline__ double2 chunk_far(const SymNodes& g, SymLds<T>& L, in
   return out;
 }
 
-// The same in the plain form. SELF: the chunk lies in the wave's own tile; one
+// The 64 steps of the plain form: adds to the owned nodes' sums sx, sy and returns
+// the sum of the lane's stream node. SELF: the chunk lies in the wave's own tile; one
 // side only, and pairs of equal (clamped) node indices are left out.
-template <int T, bool SELF>
-__device__ __forceinline__ double2 chunk_near(const SymNodes& g, SymLds<T>& L, int own0, int chunk) {
+template <int T, bool SELF, bool APART>
+__device__ __forceinline__ double2 near_steps(const SymNodes& g, const SymLds<T>& L, int own0, int chunk,
+                                              const double (&zx)[T], const double (&zy)[T], const double (&wx)[T],
+                                              const double (&wy)[T], double (&sx)[T], double (&sy)[T]) {
   const int lane = threadIdx.x & 63;
-  const int j = chunk * 64 + lane;
-  {
-    const double2 e = node_at(g, min(j, g.N - 1));
-    const double2 wj = j < g.N ? weight_at(g, j) : make_double2(0.0, 0.0);
-    L.u[lane] = L.u[lane + 64] = e;
-    L.w[lane] = L.w[lane + 64] = wj;
-  }
-  double zx[T], zy[T], wx[T], wy[T], sx[T], sy[T];
-#pragma unroll
-  for (int t = 0; t < T; ++t) {
-    const int i = own0 + t * 64 + lane;
-    const double2 z = node_at(g, min(i, g.N - 1));
-    const double2 w = i < g.N ? weight_at(g, i) : make_double2(0.0, 0.0);
-    const double2 s = L.s[t * 64 + lane];
-    zx[t] = z.x;
-    zy[t] = z.y;
-    wx[t] = w.x;
-    wy[t] = w.y;
-    sx[t] = s.x;
-    sy[t] = s.y;
-  }
-  wave_fence();
   double2 e = L.u[lane], w = L.w[lane];
   double2 ra = make_double2(0.0, 0.0);
 #pragma unroll 2
@@ -226,7 +213,8 @@ __device__ __forceinline__ double2 chunk_near(const SymNodes& g, SymLds<T>& L, i
         // equal nodes: q = 0 from dx = dy = 0 and a finite m
         if constexpr (SELF) d[v] = (min(own0 + (t + v) * 64 + lane, g.N - 1) == jk) ? 1.0 : d[v];
       }
-      inverse4(d, m);
+      if constexpr (APART) inverse4_apart(d, m);
+      else inverse4(d, m);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const double qx = dx[v] * m[v], qy = -dy[v] * m[v];
@@ -245,6 +233,52 @@ __device__ __forceinline__ double2 chunk_near(const SymNodes& g, SymLds<T>& L, i
     if constexpr (!SELF) ra = from_next_lane(ra);
     e = en;
     w = wn;
+  }
+  return ra;
+}
+
+// The chunk's 64 nodes against the wave's 64 T in the plain form. Two nodes in one
+// place spoil the reciprocal that four of a lane's nodes share: a chunk that leaves a
+// sum non-finite is taken again with a reciprocal for each pair, which keeps that to
+// the two nodes' own sums.
+template <int T, bool SELF>
+__device__ __forceinline__ double2 chunk_near(const SymNodes& g, SymLds<T>& L, int own0, int chunk) {
+  const int lane = threadIdx.x & 63;
+  const int j = chunk * 64 + lane;
+  {
+    const double2 e = node_at(g, min(j, g.N - 1));
+    const double2 wj = j < g.N ? weight_at(g, j) : make_double2(0.0, 0.0);
+    L.u[lane] = L.u[lane + 64] = e;
+    L.w[lane] = L.w[lane + 64] = wj;
+  }
+  double zx[T], zy[T], wx[T], wy[T], sx[T], sy[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int i = own0 + t * 64 + lane;
+    const double2 z = node_at(g, min(i, g.N - 1));
+    const double2 w = i < g.N ? weight_at(g, i) : make_double2(0.0, 0.0);
+    zx[t] = z.x;
+    zy[t] = z.y;
+    wx[t] = w.x;
+    wy[t] = w.y;
+  }
+  auto start = [&] {
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const double2 s = L.s[t * 64 + lane];
+      sx[t] = s.x;
+      sy[t] = s.y;
+    }
+  };
+  start();
+  wave_fence();
+  double2 ra = near_steps<T, SELF, false>(g, L, own0, chunk, zx, zy, wx, wy, sx, sy);
+  double all = ra.x + ra.y;
+#pragma unroll
+  for (int t = 0; t < T; ++t) all += sx[t] + sy[t];
+  if (__any(!isfinite(all))) {
+    start();
+    ra = near_steps<T, SELF, true>(g, L, own0, chunk, zx, zy, wx, wy, sx, sy);
   }
 #pragma unroll
   for (int t = 0; t < T; ++t) L.s[t * 64 + lane] = make_double2(sx[t], sy[t]);
