@@ -32,6 +32,7 @@
 // plane (the last plane of an odd count one). N = 33792, two groups: 2.36 ms before,
 // 1.65 now, 30 of the card's 34 T FP64 operations/s.
 #include <cstdint>
+#include <type_traits>
 
 #include "gnk_device.h"
 #include "gnk_internal.h"
@@ -97,8 +98,9 @@ struct GeomAcc {
   double2 s[2 + 2 * NG];
 };
 
-// one source against the lane's two targets; MASK: a target's own node counts nothing
-template <int NG, bool MASK>
+// one source against the lane's two targets; MASK: a target's own node counts nothing;
+// APART: a reciprocal for each target
+template <int NG, bool MASK, bool APART>
 __device__ __forceinline__ void geom_step(GeomAcc<NG> (&acc)[2], const double2 (&z)[2], const double (&vt)[2][NG],
                                           const GeomSrc& s, bool own0, bool own1) {
   double dx[2], dy[2], m[2];
@@ -112,8 +114,15 @@ __device__ __forceinline__ void geom_step(GeomAcc<NG> (&acc)[2], const double2 (
     m[0] = own0 ? 1.0 : m[0];
     m[1] = own1 ? 1.0 : m[1];
   }
-  const double R = refine_rcp(m[0] * m[1]);
-  const double i0 = R * m[1], i1 = R * m[0];
+  double i0, i1;
+  if (APART) {
+    i0 = refine_rcp(m[0]);
+    i1 = refine_rcp(m[1]);
+  } else {
+    const double R = refine_rcp(m[0] * m[1]);
+    i0 = R * m[1];
+    i1 = R * m[0];
+  }
   m[0] = MASK && own0 ? 0.0 : i0;
   m[1] = MASK && own1 ? 0.0 : i1;
 #pragma unroll
@@ -178,25 +187,41 @@ __global__ __launch_bounds__(256) void k_geom_sums(const double* __restrict__ re
   const int j0 = min(jb1, jb0 + wv * wchunk);
   const int j1 = min(jb1, j0 + wchunk);
   GeomAcc<NG> acc[2] = {};
-  auto plain = [&](int ja, int jb) {
-    if (ja >= jb) return;
-    GeomSrc a = load_src(rec + (size_t)ja * kStride), b;
-    int j = ja;
-    for (; j + 1 < jb; j += 2) {
-      b = load_src(rec + (size_t)(j + 1) * kStride);
-      __builtin_amdgcn_sched_barrier(0);
-      geom_step<NG, false>(acc, z, vt, a, false, false);
-      a = load_src(rec + (size_t)min(j + 2, jb - 1) * kStride);
-      __builtin_amdgcn_sched_barrier(0);
-      geom_step<NG, false>(acc, z, vt, b, false, false);
-    }
-    if (j < jb) geom_step<NG, false>(acc, z, vt, a, false, false);
+  auto sums = [&](auto apart) {
+    constexpr bool APART = decltype(apart)::value;
+    auto plain = [&](int ja, int jb) {
+      if (ja >= jb) return;
+      GeomSrc a = load_src(rec + (size_t)ja * kStride), b;
+      int j = ja;
+      for (; j + 1 < jb; j += 2) {
+        b = load_src(rec + (size_t)(j + 1) * kStride);
+        __builtin_amdgcn_sched_barrier(0);
+        geom_step<NG, false, APART>(acc, z, vt, a, false, false);
+        a = load_src(rec + (size_t)min(j + 2, jb - 1) * kStride);
+        __builtin_amdgcn_sched_barrier(0);
+        geom_step<NG, false, APART>(acc, z, vt, b, false, false);
+      }
+      if (j < jb) geom_step<NG, false, APART>(acc, z, vt, a, false, false);
+    };
+    plain(j0, min(j1, base));
+    const int ma = max(j0, base), mb = min(j1, base + 128);
+    for (int j = ma; j < mb; ++j)
+      geom_step<NG, true, APART>(acc, z, vt, load_src(rec + (size_t)j * kStride), j == n0, j == n1);
+    plain(max(j0, base + 128), j1);
   };
-  plain(j0, min(j1, base));
-  const int ma = max(j0, base), mb = min(j1, base + 128);
-  for (int j = ma; j < mb; ++j)
-    geom_step<NG, true>(acc, z, vt, load_src(rec + (size_t)j * kStride), j == n0, j == n1);
-  plain(max(j0, base + 128), j1);
+  sums(std::false_type{});
+  // a node in the place of a target, or squared distances whose product leaves the
+  // range, spoil the lane's two targets: sums left non-finite are formed again with a
+  // reciprocal for each
+  double all = 0.0;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int k = 0; k < 2 + 2 * NG; ++k) all += acc[t].s[k].x + acc[t].s[k].y;
+  if (__any(!isfinite(all))) {
+    acc[0] = acc[1] = GeomAcc<NG>{};
+    sums(std::true_type{});
+  }
 
 #pragma unroll
   for (int k = 0; k < 2 + 2 * NG; ++k) {
