@@ -454,12 +454,19 @@ bool plan_sym(gnk_ctx* c, int64_t N, int64_t part_cols, SymPlan* P, std::vector<
   return true;
 }
 
+// What a call takes from the direct kernels, which sets the partial sums that are
+// reserved and the plans that are made: no product at all (treecode, separate points,
+// geometric derivative: up to 2.1 KB per node and 100 us of host work at 73728 nodes
+// for nothing), products of several columns only, or one-column ones as well (of the
+// one column, or of the leading column that diagonals are made from).
+enum class Direct { none, columns, single };
+
 // Builds the batch tables and workspace. doms: host array; ncols: columns per
 // domain; col_off: flat offset of column 0 of each domain (the columns of a
 // domain are contiguous, N_d apart).
 void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const int* ncols,
-                 const std::vector<int64_t>& col_off, int64_t T, bool adjoint, bool mixed, const PairShape& shape,
-                 int64_t force_N = 0) {
+                 const std::vector<int64_t>& col_off, int64_t T, bool adjoint, bool mixed, Direct direct,
+                 const PairShape& shape, int64_t force_N = 0) {
   B = Batch();
   B.ndom = ndom;
   B.T = T;
@@ -494,7 +501,7 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
       D.chunk = ch;
       D.splits = sp;
       std::vector<int4> items;
-      if (plan_sym(c, D.N, (int64_t)sp * (ncols[d] + 1), &B.sym.plan, &items)) {
+      if (direct == Direct::single && plan_sym(c, D.N, (int64_t)sp * (ncols[d] + 1), &B.sym.plan, &items)) {
         B.sym.on = true;
         B.sym.cnt = (int)items.size();
         B.sym.items = upload(c, "b_sym", items);
@@ -515,7 +522,7 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
     rec_total += (int64_t)D.N * rec_stride(D.ncols + 1);   // head, w.., b.. with a lead column
     rec32_total += (int64_t)D.N * rec32_stride(D.ncols + 1);
     far32_total += far32_size(D.N, D.ncols + 1);
-    part_total += std::max<int64_t>((int64_t)D.splits * (D.ncols + 1), D.symslots) * D.N;
+    if (direct != Direct::none) part_total += std::max<int64_t>((int64_t)D.splits * (D.ncols + 1), D.symslots) * D.N;
     sb_total += (D.N + 63) / 64;
     tb_total += (D.N + 63) / 64;
     sbf_total += (D.N + kFarTile - 1) / kFarTile;
@@ -529,7 +536,7 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
   double2* rec = ws<double2>(c, "b_rec", rec_total);
   float2* rec32 = mixed ? ws<float2>(c, "b_rec32", rec32_total) : nullptr;
   float2* far32 = mixed ? ws<float2>(c, "b_far32", far32_total) : nullptr;
-  double2* parts = ws<double2>(c, "b_parts", part_total);
+  double2* parts = part_total ? ws<double2>(c, "b_parts", part_total) : nullptr;
   // tile bounds: far-tile classification (both precisions) and tile-relative records
   double4* sb = ws<double4>(c, "b_sb", sb_total);
   double4* tb = ws<double4>(c, "b_tb", tb_total);
@@ -547,7 +554,7 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
     D.rec = rec + orc;
     D.rec32 = rec32 ? rec32 + orc32 : nullptr;
     D.far32 = far32 ? far32 + ofar : nullptr;
-    D.parts = parts + op;
+    D.parts = parts ? parts + op : nullptr;
     D.sb = sb ? sb + osb : nullptr;
     D.tb = tb ? tb + otb : nullptr;
     D.sbf = sbf + osbf;
@@ -572,8 +579,14 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
   HIPCHK(c, launch_node_tile_bounds(B.d_dom, ndom, B.maxN, B.shape.tpt, c->stream));
 }
 
+// Whether the sums of pattern p come from the two-sided one-column launch.
+bool use_sym(const Batch& B, int p, bool mixed) {
+  return B.sym.on && !B.tree.on && !mixed && kLead[p] + kData[p] * B.dom[0].ncols == 1;
+}
+
 // Work items of a pattern: every domain (largest first), column group, target
-// tile and source split; grouped by column-group width.
+// tile and source split; grouped by column-group width (none for a pattern that the
+// treecode or the two-sided launch takes, which have lists of their own).
 void build_items(gnk_ctx* c, Batch& B, int p) {
   auto& S = B.sets[p];
   if (S.built) return;
@@ -582,6 +595,7 @@ void build_items(gnk_ctx* c, Batch& B, int p) {
   for (int d = 0; d < B.ndom; ++d) order[d] = d;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return B.dom[a].N > B.dom[b].N; });
   std::vector<int4> lists[kMaxWidth];
+  const bool own_lists = B.tree.on || use_sym(B, p, p == P_GM_MIXED);
   S.pair_cols = S.flops = S.pairs1 = 0;
   for (int d : order) {
     const DomDev& D = B.dom[d];
@@ -593,7 +607,7 @@ void build_items(gnk_ctx* c, Batch& B, int p) {
     S.pair_cols += pairs * wcols;
     S.flops += pairs * (16.0 + 8.0 * (wcols - 1));
     if (wcols == 1) S.pairs1 += pairs;
-    if (p == P_GM_MIXED && D.treeslots > 0) continue;   // no items: a treecode's domain
+    if (own_lists || (p == P_GM_MIXED && D.treeslots > 0)) continue;
     int r0 = 0;
     while (r0 < wcols) {
       int w = group_width(wcols - r0);
@@ -636,7 +650,7 @@ void build_items(gnk_ctx* c, Batch& B, int p) {
   }
   for (int k = 0; k < kMaxWidth; ++k) {
     S.cnt[k] = (int)lists[k].size();
-    S.d[k] = upload(c, "b_items" + std::to_string(p) + "_" + std::to_string(k), lists[k]);
+    S.d[k] = lists[k].empty() ? nullptr : upload(c, "b_items" + std::to_string(p) + "_" + std::to_string(k), lists[k]);
   }
   S.built = true;
 }
@@ -901,11 +915,6 @@ int64_t records32_threads(const Batch& B, int p) {
     t = std::max(t, (int64_t)D.N * ((wc + 7) / 8 * 8));
   }
   return t;
-}
-
-// Whether the sums of pattern p come from the two-sided one-column launch.
-bool use_sym(const Batch& B, int p, bool mixed) {
-  return B.sym.on && !B.tree.on && !mixed && kLead[p] + kData[p] * B.dom[0].ncols == 1;
 }
 
 // All Cauchy sums of a pattern for the batch (one launch per column-group width).
@@ -1674,7 +1683,7 @@ PairShape tuned_shape(gnk_ctx* c, int ndom, const gnk_domain* doms, const int* n
   c->prof = false;
   for (const PairShape& p : cand) {
     Batch B;
-    build_batch(c, B, ndom, doms, ncols, col_off, T, false, mixed, p);
+    build_batch(c, B, ndom, doms, ncols, col_off, T, false, mixed, Direct::columns, p);
     k_rho<<<node_grid(B), kT, 0, c->stream>>>(B.d_dom);
     LAUNCHCHK(c);
     k_weights<<<dim3((unsigned)B.maxm1, (unsigned)B.ncol), kT, 0, c->stream>>>(
@@ -1786,11 +1795,11 @@ gnk_status guarded(gnk_ctx* c, F&& f) {
 }
 
 // Batch of one domain whose flat vectors are the caller's N x nrhs arrays.
-void single_batch(gnk_ctx* c, Batch& B, const gnk_domain* d, int nrhs, bool adjoint, bool mixed,
+void single_batch(gnk_ctx* c, Batch& B, const gnk_domain* d, int nrhs, bool adjoint, bool mixed, Direct direct,
                   bool second = false) {
   check_domain(c, d, adjoint, second);
   std::vector<int64_t> off{0};
-  build_batch(c, B, 1, d, &nrhs, off, d->m1 * d->n * (int64_t)nrhs, adjoint, mixed, PairShape{});
+  build_batch(c, B, 1, d, &nrhs, off, d->m1 * d->n * (int64_t)nrhs, adjoint, mixed, direct, PairShape{});
   B.second = second || adjoint;
 }
 
@@ -1835,7 +1844,7 @@ GmresOut fbie_adjoint_batch(gnk_ctx* c, Batch& B, const double* g_mu, const doub
 void geom_vjp(gnk_ctx* c, const gnk_domain* d, int nterms, const int* ops, const double* coef,
               const double* const* u, const double* const* v, double2* g_eta, double2* g_etap, double2* g_A) {
   Batch B;
-  single_batch(c, B, d, 1, false, false);
+  single_batch(c, B, d, 1, false, false, Direct::none);
   const int N = B.dom[0].N;
   {
     // finiteness of the domain data and of every term vector
@@ -1948,7 +1957,8 @@ void cauchy_sum(gnk_ctx* c, int64_t N, const void* eta, const void* w, int nrhs,
   d.eta = d.etap = d.A = eta;
   Batch B;
   std::vector<int64_t> off{0};
-  build_batch(c, B, 1, &d, &nrhs, off, N * (int64_t)nrhs, false, false, PairShape{}, N);
+  build_batch(c, B, 1, &d, &nrhs, off, N * (int64_t)nrhs, false, false,
+              nrhs == 1 ? Direct::single : Direct::columns, PairShape{}, N);
   k_pack_records<<<nblocks(N), kT, 0, c->stream>>>(B.d_dom, static_cast<const double2*>(w), nrhs);
   LAUNCHCHK(c);
   pairs(c, B, P_GM, false, nullptr);
@@ -2166,7 +2176,7 @@ static gnk_status slit_map(gnk_ctx* c, const char* name, int64_t m1, int64_t n, 
   d.etap = etap;
   d.A = A;
   Batch B;
-  single_batch(c, B, &d, 1, false, o.prec == GNK_MIXED);
+  single_batch(c, B, &d, 1, false, o.prec == GNK_MIXED, o.far_tol > 0.0 ? Direct::none : Direct::single);
   if (o.far_tol > 0.0) build_tree(c, B, o.far_tol);
   GmresOut g = fbie_batch(c, B, gam, o, mu, h);
   k_comp_means<<<(unsigned)m1, kT, 0, c->stream>>>(h, (int)n, hbar);
@@ -2217,7 +2227,7 @@ gnk_status gnk_cauchy_sum_tree(gnk_ctx* c, int64_t N, const void* eta, const voi
     d.eta = d.etap = d.A = eta;
     Batch B;
     std::vector<int64_t> off{0};
-    build_batch(c, B, 1, &d, &nrhs, off, N * (int64_t)nrhs, false, false, PairShape{}, N);
+    build_batch(c, B, 1, &d, &nrhs, off, N * (int64_t)nrhs, false, false, Direct::none, PairShape{}, N);
     build_tree(c, B, far_tol);
     k_pack_records<<<nblocks(N), kT, 0, c->stream>>>(B.d_dom, static_cast<const double2*>(w), nrhs);
     LAUNCHCHK(c);
@@ -2258,20 +2268,18 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
     if (far_tol > 0.0) t = 1;
     Batch B;
     std::vector<int64_t> off{0};
-    build_batch(c, B, 1, &d, &nrhs, off, N * (int64_t)nrhs, false, false, PairShape{t, ch}, N);
+    build_batch(c, B, 1, &d, &nrhs, off, N * (int64_t)nrhs, false, false, Direct::none, PairShape{t, ch}, N);
     DomDev& D = B.dom[0];
     D.tz = static_cast<const double2*>(z);
     D.Nt = (int)nz;
-    D.parts = ws<double2>(c, "f_parts", (size_t)D.splits * wcols * nz);
+    if (far_tol == 0.0) D.parts = ws<double2>(c, "f_parts", (size_t)D.splits * wcols * nz);
     // treecode: the points in the Hilbert order of their positions, so that a
     // tile of consecutive targets is a compact cluster (results go back to the
     // caller's order in the epilogue)
     const int* tperm = nullptr;
     if (far_tol > 0.0) {
       int* perm = ws<int>(c, "f_tperm", nz);
-      // the sort's scratch: the partial sums' buffer, not yet in use, where it suffices
-      const size_t hb = hilbert_scratch(nz);
-      void* hs = hb <= sizeof(double2) * D.splits * wcols * nz ? (void*)D.parts : (void*)ws<char>(c, "f_hilbert", hb);
+      char* hs = ws<char>(c, "f_hilbert", hilbert_scratch(nz));
       HIPCHK(c, launch_hilbert_order(static_cast<const double2*>(z), nullptr, (int)nz, hs, perm, c->stream));
       tperm = perm;
       double2* zp = ws<double2>(c, "f_zp", (size_t)nz);
@@ -2332,7 +2340,7 @@ gnk_status gnk_apply(gnk_ctx* c, const gnk_domain* d, int op, int prec, const do
     }
     Batch B;
     const bool mixed = prec == GNK_MIXED && op != GNK_OP_LHAT;
-    single_batch(c, B, d, nrhs, adj, mixed, unsub);
+    single_batch(c, B, d, nrhs, adj, mixed, op == GNK_OP_LHAT ? Direct::none : Direct::single, unsub);
     validate(c, B, x, B.T);
     if (op != GNK_OP_LHAT) {
       setup_diag(c, B);
@@ -2356,7 +2364,9 @@ gnk_status gnk_fbie(gnk_ctx* c, const gnk_domain* d, const double* gam, int nrhs
     }
     gnk_opts o = resolve_opts(c, opts);
     Batch B;
-    single_batch(c, B, d, nrhs, false, o.prec == GNK_MIXED, o.no_subtraction != 0);
+    single_batch(c, B, d, nrhs, false, o.prec == GNK_MIXED,
+                 o.far_tol > 0.0 ? Direct::none : (nrhs == 1 ? Direct::single : Direct::columns),
+                 o.no_subtraction != 0);
     if (o.far_tol > 0.0) build_tree(c, B, o.far_tol);
     GmresOut g = fbie_batch(c, B, gam, o, mu, h);
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -2375,7 +2385,7 @@ gnk_status gnk_fbie_ad(gnk_ctx* c, const gnk_domain* d, const double* gam, int n
     }
     gnk_opts o = resolve_opts(c, opts);
     Batch B;
-    single_batch(c, B, d, nrhs, true, o.prec == GNK_MIXED);
+    single_batch(c, B, d, nrhs, true, o.prec == GNK_MIXED, o.far_tol > 0.0 ? Direct::none : Direct::single);
     if (o.far_tol > 0.0) build_tree(c, B, o.far_tol);
     GmresOut g = fbiead_batch(c, B, gam, o, mu);
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -2424,7 +2434,7 @@ gnk_status gnk_fbie_batched(gnk_ctx* c, int ndom, const gnk_domain* doms, const 
     const bool mixed = o.prec == GNK_MIXED;
     const PairShape p = tuned_shape(c, ndom, doms, nrhs, mixed, g, off, T);
     Batch B;
-    build_batch(c, B, ndom, doms, nrhs, off, T, false, mixed, p);
+    build_batch(c, B, ndom, doms, nrhs, off, T, false, mixed, Direct::columns, p);
     GmresOut go = fbie_batch(c, B, g, o, m, hh);
     for (int d = 0; d < ndom; ++d) {
       const size_t bytes = sizeof(double) * doms[d].m1 * doms[d].n * nrhs[d];
@@ -2452,7 +2462,7 @@ gnk_status gnk_fbie_adjoint(gnk_ctx* c, const gnk_domain* d, const double* g_mu,
       throw Fail{GNK_ERR_ARG};
     }
     Batch B;
-    single_batch(c, B, d, nrhs, false, o.prec == GNK_MIXED);
+    single_batch(c, B, d, nrhs, false, o.prec == GNK_MIXED, Direct::single);
     GmresOut g = fbie_adjoint_batch(c, B, g_mu, g_h, o, lam, g_gam);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (info)
