@@ -75,14 +75,19 @@ __device__ __forceinline__ void put_head(const DomDev& D, int wcols, int j, doub
   if (D.slim) D.rec[(size_t)j * slim_stride(wcols)] = D.eta[j];
   else record_head(D.rec + (size_t)j * rec_stride(wcols), D.eta[j], ep);
 }
-__device__ __forceinline__ void put_weight(const DomDev& D, int wcols, int j, int q, double2 w, double2 ep) {
-  if (D.slim) {
-    D.rec[(size_t)j * slim_stride(wcols) + 1 + q] = w;
-  } else {
-    double2* rj = D.rec + (size_t)j * rec_stride(wcols) + kRecHead + q;
-    rj[0] = w;
-    rj[wcols] = cmul_conj(w, ep);
-  }
+// where node j's weights lie and, relative to them, their products (0: none kept); taken
+// once for all columns, since every store could change the domain's table
+struct RecordAt {
+  double2* w;
+  int prod;
+};
+__device__ __forceinline__ RecordAt record_at(const DomDev& D, int wcols, int j) {
+  return D.slim ? RecordAt{D.rec + (size_t)j * slim_stride(wcols) + 1, 0}
+                : RecordAt{D.rec + (size_t)j * rec_stride(wcols) + kRecHead, wcols};
+}
+__device__ __forceinline__ void put_weight(const RecordAt& r, int q, double2 w, double2 ep) {
+  r.w[q] = w;
+  if (r.prod) r.w[r.prod + q] = cmul_conj(w, ep);
 }
 __device__ __forceinline__ double diagv(const DomDev& D, int sel, int i) {
   return sel == D_B ? D.dB[i] : (sel == D_D ? D.dD[i] : (sel == D_E ? D.e[i] : (sel == D_BU ? D.bu[i] : 0.0)));
@@ -247,10 +252,11 @@ __global__ __launch_bounds__(kT) void k_weights(const DomDev* __restrict__ doms,
       if (!D.rec32) continue;   // mixed products take the records
     }
     const double2 ep = record_offset(D, j);
-    put_weight(D, wcols, j, lead + C.r, w, ep);
+    const RecordAt r = record_at(D, wcols, j);
+    put_weight(r, lead + C.r, w, ep);
     if (C.r == 0) {
       put_head(D, wcols, j, ep);
-      if (lead) put_weight(D, wcols, j, 0, cf, ep);
+      if (lead) put_weight(r, 0, cf, ep);
     }
   }
   if (mean) {
@@ -270,7 +276,7 @@ __device__ __forceinline__ void stage_weight(const DomDev& D, int csel, int r, i
     if (!D.rec32) return;   // mixed products take the records
   }
   const double2 ep = record_offset(D, j);
-  put_weight(D, wcols, j, r, w, ep);
+  put_weight(record_at(D, wcols, j), r, w, ep);
   if (head) put_head(D, wcols, j, ep);
 }
 
@@ -302,7 +308,7 @@ __global__ void k_lead_records(const DomDev* __restrict__ doms, int csel) {
   }
   const double2 ep = record_offset(D, j);
   put_head(D, 1, j, ep);
-  put_weight(D, 1, j, 0, cf, ep);
+  put_weight(record_at(D, 1, j), 0, cf, ep);
 }
 
 // records of one domain from column-major complex weights w (N x ncols)
@@ -316,7 +322,9 @@ __global__ void k_pack_records(const DomDev* __restrict__ doms, const double2* _
   }
   const double2 ep = record_offset(D, j);
   put_head(D, ncols, j, ep);
-  for (int r = 0; r < ncols; ++r) put_weight(D, ncols, j, r, w[(size_t)r * D.N + j], ep);
+  const RecordAt rj = record_at(D, ncols, j);
+  const int N = D.N;
+  for (int r = 0; r < ncols; ++r) put_weight(rj, r, w[(size_t)r * N + j], ep);
 }
 
 // ------------------------------- conformal maps onto the disc with slits
@@ -421,8 +429,10 @@ __global__ void k_fcau_records(const DomDev* __restrict__ doms, const double2* _
   const double2 ep = record_offset(D, j);
   const double2 p = D.etap[j];
   put_head(D, wcols, j, ep);
-  put_weight(D, wcols, j, 0, p, ep);
-  for (int q = 0; q < nrhs; ++q) put_weight(D, wcols, j, 1 + q, cmul(f[(size_t)q * D.N + j], p), ep);
+  const RecordAt rj = record_at(D, wcols, j);
+  const int N = D.N;
+  put_weight(rj, 0, p, ep);
+  for (int q = 0; q < nrhs; ++q) put_weight(rj, 1 + q, cmul(f[(size_t)q * N + j], p), ep);
 }
 
 // a / b without overflow of |b|^2 (scaled division)
