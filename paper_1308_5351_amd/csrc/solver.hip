@@ -229,12 +229,22 @@ constexpr int kLead[4] = {0, 1, 1, 0};
 constexpr int kData[4] = {1, 1, 0, 1};
 constexpr int kMaxWidth = 8;   // widest column group of the pair kernels (lists are kept by width - 1)
 
-// Width of the next column group of an FP64 product with `left` columns to go:
-// the fewest groups of at most 8 columns, of nearly equal widths, since the
-// distances and the reciprocal of a pair are formed once per group (11 x 600
-// nodes, 5 columns: one launch 43 us, groups of 4 and 1 41 + 22 us; the solve
-// 1.95 and 1.54 ms, with 7 columns 2.51 and 1.75).
-int group_width(int left) {
+// Width of the next column group of an FP64 product with `left` columns to go: the
+// fewest groups of at most 8 columns, of nearly equal widths, since the distances and
+// the reciprocal of a pair are formed once per group (11 x 600 nodes, 5 columns: one
+// launch 43 us, groups of 4 and 1 41 + 22 us; the solve 1.95 and 1.54 ms, with 7
+// columns 2.51 and 1.75). One column over full groups of 8 goes alone from 5000
+// targets on: its far form saves more than equal widths do (9 columns, 8 + 1 / 5 + 4,
+// one cycle of ten steps: 17 x 1024 nodes 6.98 / 7.13 ms, 9000 nodes 2.51 / 2.56, 4800
+// 1.16 / 1.15; 8 right-hand sides at 65536 points 2.08 / 2.11 ms). Two columns, whose
+// far form (nodes only) saves less, go so over one group of 8 from 32000 nodes on (10
+// columns, 8 + 2 / 5 + 5: 33 x 1024 nodes 24.6 / 25.2 ms, 30 x 1000 20.1 / 19.9).
+constexpr int64_t kLoneMinN = 5000, kLonePairMinN = 32000;
+bool lone_column(int left, int64_t targets) {
+  return left > kMaxWidth && left % kMaxWidth == 1 && targets >= kLoneMinN;
+}
+int group_width(int left, int64_t targets, bool nodes) {
+  if (lone_column(left, targets) || (nodes && left == kMaxWidth + 2 && targets >= kLonePairMinN)) return kMaxWidth;
   const int groups = (left + kMaxWidth - 1) / kMaxWidth;
   return (left + groups - 1) / groups;
 }
@@ -355,7 +365,7 @@ void plan_pairs(gnk_ctx* c, int64_t Nt, int64_t Ns, int align, int cols, bool mi
   // the column group whose variant sets the wave slots (scarce: of 8, 4, 2 or 1, so
   // that no column count takes more splits than it did)
   const int width = scarce ? (cols >= 8 ? 8 : (cols >= 4 ? 4 : (cols >= 2 ? 2 : 1)))
-                           : (mixed ? std::min(cols, kMaxWidth) : group_width(cols));
+                           : (mixed ? std::min(cols, kMaxWidth) : group_width(cols, Nt, true));
   int t = roomy ? (Nt >= (width == 1 ? 1024 : 2048) ? 2 : 1) : (((Nt + 127) / 128) * 64 >= slots_of(c) ? 2 : 1);
   if (const char* s = getenv("GNK_CAUCHY_TPT")) t = atoi(s) == 2 ? 2 : 1;
   // wave slots of the variant that runs the products (its register use sets
@@ -610,7 +620,7 @@ void build_items(gnk_ctx* c, Batch& B, int p) {
     if (own_lists || (p == P_GM_MIXED && D.treeslots > 0)) continue;
     int r0 = 0;
     while (r0 < wcols) {
-      int w = group_width(wcols - r0);
+      int w = group_width(wcols - r0, NT, !D.tz);
       int code = r0, wi = w - 1;
       if (p == P_GM_MIXED) {
         // groups of 8, 2 or 1 columns, 3-7 remaining ones as a padded group of 8
@@ -2289,11 +2299,12 @@ static gnk_status fcau(gnk_ctx* c, const char* name, int64_t m1, int64_t n, cons
     }
     D.tb = ws<double4>(c, "f_tb", (size_t)((nz + 63) / 64));
     B.d_dom = upload(c, "b_dom", B.dom);
-    // (the direct sums, of two columns at least, have no far form for separate points)
+    // (for separate points only groups of one column have a far form)
+    if (far_tol > 0.0 || lone_column(wcols, nz))
+      HIPCHK(c, launch_tile_bounds(B.d_dom, 1, (int)nz, 64 * B.shape.tpt, 3, c->stream));
     if (far_tol > 0.0) {
       D.m1 = (int)m1;
       D.n = (int)n;
-      HIPCHK(c, launch_tile_bounds(B.d_dom, 1, (int)nz, 64 * B.shape.tpt, 3, c->stream));
       build_tree(c, B, far_tol, true);
     }
     k_fcau_records<<<nblocks(N), kT, 0, c->stream>>>(B.d_dom, static_cast<const double2*>(f), nrhs);
