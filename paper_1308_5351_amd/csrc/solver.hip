@@ -412,16 +412,17 @@ void plan_single(gnk_ctx* c, int64_t N, int align, int cols, bool mixed, int* tp
 //     (1.5 GB there; 2.6 times that at 1e6).
 //   * Eight nodes per lane from 40000 on (537/550 us at N = 45000, 1415/1450 at
 //     73729), four below, whose items are half as long (109.5/100.8 at 17408).
-//   * Not in the fixed scratch of gnk_cauchy_sum_noalloc, nor where its partial
-//     sums would pass those of the one-sided launch under a workspace cap, nor
-//     with the launch-shape overrides, which are the one-sided kernel's.
+//   * Not in the fixed scratch of gnk_cauchy_sum_noalloc nor under a workspace cap
+//     (its slots, items and weights come on top of what the right-hand side's two
+//     columns need, and what fitted by the one-sided kernel has to fit), nor with the
+//     launch-shape overrides, which are the one-sided kernel's.
 // A block's stream is cut into F pieces, the same fractions for every block:
 // each layer of nb pieces takes 1/(2 resident workgroups) of the work left per
 // workgroup, but at least two chunks (every piece is a slot that the consumer
 // reads; at N = 17408 a piece is two or three chunks).
 constexpr int64_t kSymMinN = 8000, kSymMaxN = 600000, kSymWideN = 40000;
-bool plan_sym(gnk_ctx* c, int64_t N, int64_t part_cols, SymPlan* P, std::vector<int4>* items) {
-  if (N < kSymMinN || N > kSymMaxN || c->arena || getenv("GNK_CAUCHY_TPT") || getenv("GNK_CAUCHY_SPLITS")) return false;
+bool plan_sym(gnk_ctx* c, int64_t N, SymPlan* P, std::vector<int4>* items) {
+  if (N < kSymMinN || N > kSymMaxN || c->arena || c->ws_limit || getenv("GNK_CAUCHY_TPT") || getenv("GNK_CAUCHY_SPLITS")) return false;
   const int T = N >= kSymWideN ? 8 : 4;
   const int nb = (int)((N + 256 * T - 1) / (256 * T));
   const int nc = (int)((N + 63) / 64), per = 4 * T;
@@ -449,7 +450,6 @@ bool plan_sym(gnk_ctx* c, int64_t N, int64_t part_cols, SymPlan* P, std::vector<
   P->H = nb / 2;
   P->F = (int)cut.size() - 1;
   P->P = 3 * T;
-  if (c->ws_limit && P->slots() >= part_cols) return false;
   std::vector<std::pair<int, int4>> v;   // chunks, item
   for (int I = 0; I < nb; ++I) {
     const int n = len(I);
@@ -511,7 +511,7 @@ void build_batch(gnk_ctx* c, Batch& B, int ndom, const gnk_domain* doms, const i
       D.chunk = ch;
       D.splits = sp;
       std::vector<int4> items;
-      if (direct == Direct::single && plan_sym(c, D.N, (int64_t)sp * (ncols[d] + 1), &B.sym.plan, &items)) {
+      if (direct == Direct::single && plan_sym(c, D.N, &B.sym.plan, &items)) {
         B.sym.on = true;
         B.sym.cnt = (int)items.size();
         B.sym.items = upload(c, "b_sym", items);
@@ -1178,8 +1178,9 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
   double* V = ws<double>(c, "V", (size_t)(restart + 1) * T);
   double* P1 = ws<double>(c, "gmP1", (size_t)ncol * nblk * ldp);
   double* P2 = ws<double>(c, "gmP2", (size_t)ncol * nblk * ldp);
-  // the partials of very many blocks are added up by a launch of their own
-  const bool fold = nblk > kFoldBlocks;
+  // the partials of very many blocks are added up by a launch of their own (which takes
+  // a little more workspace)
+  const bool fold = nblk > kFoldBlocks && !c->ws_limit;
   double* P3 = fold ? ws<double>(c, "gmP3", (size_t)ncol * ldp) : nullptr;
   GmresState st;
   st.ldh = restart + 1;
