@@ -186,6 +186,11 @@ typedef struct {
  * a caller stream must therefore be capturable (not the legacy null stream). */
 /* Environment (all optional):
  *   GNK_WORKSPACE_MB=m   cap the context's workspace at m MiB (GNK_ERR_OOM beyond)
+ *   GNK_DEVICE_MB=m      let the workspace's allocations fail beyond m MiB, as on a
+ *                        card that is otherwise full (for tests of what is done then:
+ *                        a call that runs out of memory is run again without the
+ *                        workspace of earlier calls, and from then on the context
+ *                        keeps to the direct kernels that take the least)
  *   GNK_GRAPH=0          launch every kernel directly instead of replaying graphs
  *   GNK_LOG=1            print each GMRES cycle's true residual to stderr
  *   GNK_TUNE, GNK_TUNE_CACHE   the batched autotuner (see gnk_fbie_batched)

@@ -53,6 +53,10 @@ struct gnk_ctx {
   int num_cu = 256;
   size_t ws_limit = 0;   // bytes, 0 = unlimited
   size_t ws_bytes = 0;
+  size_t dev_limit = 0;  // bytes at which allocations fail as on a full card (tests), 0 = none
+  // set once an allocation has failed: from then on without the kernels that take more
+  // workspace than the one-sided direct ones (two-sided sums, treecode of mixed products)
+  bool lean = false;
   bool log = false;
   struct Buf {
     void* p = nullptr;
@@ -155,7 +159,7 @@ T* ws(gnk_ctx* c, const std::string& name, size_t count) {
     throw Fail{GNK_ERR_OOM};
   }
   void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) {
+  if ((c->dev_limit && c->ws_bytes + bytes > c->dev_limit) || hipMalloc(&p, bytes) != hipSuccess) {
     (void)hipGetLastError();
     set_err(c, "hipMalloc of %zu bytes for '%s' failed", bytes, name.c_str());
     throw Fail{GNK_ERR_OOM};
@@ -414,15 +418,16 @@ void plan_single(gnk_ctx* c, int64_t N, int align, int cols, bool mixed, int* tp
 //     73729), four below, whose items are half as long (109.5/100.8 at 17408).
 //   * Not in the fixed scratch of gnk_cauchy_sum_noalloc nor under a workspace cap
 //     (its slots, items and weights come on top of what the right-hand side's two
-//     columns need, and what fitted by the one-sided kernel has to fit), nor with the
-//     launch-shape overrides, which are the one-sided kernel's.
+//     columns need, and what fitted by the one-sided kernel has to fit), nor in a
+//     context that has run out of memory, nor with the launch-shape overrides, which are
+//     the one-sided kernel's.
 // A block's stream is cut into F pieces, the same fractions for every block:
 // each layer of nb pieces takes 1/(2 resident workgroups) of the work left per
 // workgroup, but at least two chunks (every piece is a slot that the consumer
 // reads; at N = 17408 a piece is two or three chunks).
 constexpr int64_t kSymMinN = 8000, kSymMaxN = 600000, kSymWideN = 40000;
 bool plan_sym(gnk_ctx* c, int64_t N, SymPlan* P, std::vector<int4>* items) {
-  if (N < kSymMinN || N > kSymMaxN || c->arena || c->ws_limit || getenv("GNK_CAUCHY_TPT") || getenv("GNK_CAUCHY_SPLITS")) return false;
+  if (N < kSymMinN || N > kSymMaxN || c->arena || c->ws_limit || c->lean || getenv("GNK_CAUCHY_TPT") || getenv("GNK_CAUCHY_SPLITS")) return false;
   const int T = N >= kSymWideN ? 8 : 4;
   const int nb = (int)((N + 256 * T - 1) / (256 * T));
   const int nc = (int)((N + 63) / 64), per = 4 * T;
@@ -827,12 +832,13 @@ void build_tree(gnk_ctx* c, Batch& B, double far_tol, bool ext = false) {
 // whose other items share one launch, 1e9 (six domains of 1e8 to 4e8 each: 5.2 ms,
 // with them from 1.5e8 on 5.7; eight of 1e9 to 2e11: 213 ms from 1e9 or 4e8 on, 224
 // from 2e9, 645 without). Not under a workspace cap, whose callers count on the pair
-// kernels' buffers, nor with the overrides of those kernels.
+// kernels' buffers, nor in a context that has run out of memory, nor with the overrides
+// of those kernels.
 constexpr double kMixedTreeTol = 1e-9;
 constexpr int kMixedTreeMinN = 4096;
 constexpr double kMixedTreePairs = 4e8, kMixedTreePairsOfMany = 1e9;
 void build_mixed_trees(gnk_ctx* c, Batch& B) {
-  if (c->ws_limit || c->arena) return;
+  if (c->ws_limit || c->arena || c->lean) return;
   for (const char* e : {"GNK_MIXED_THETA", "GNK_CAUCHY_TPT", "GNK_CAUCHY_SPLITS"})
     if (getenv(e)) return;
   bool any = false;
@@ -841,26 +847,8 @@ void build_mixed_trees(gnk_ctx* c, Batch& B) {
     DomDev& D = B.dom[d];
     const double work = (double)D.N * (double)D.N * D.ncols;
     if (D.N < kMixedTreeMinN || work < (B.ndom == 1 ? kMixedTreePairs : kMixedTreePairsOfMany)) continue;
-    const std::string tag = "_m" + std::to_string(d);
-    try {
-      plan_tree(c, trees[d], D, B.shape.tpt, kMixedTreeTol, false, D.ncols, tag, nullptr, 0, D.splits);
-    } catch (const Fail& f) {
-      // no memory left for it: the pair kernels take the domain, as they would have
-      if (f.st != GNK_ERR_OOM) throw;
-      HIPCHK(c, hipStreamSynchronize(c->stream));
-      for (const char* n : {"t_bounds", "t_mom", "t_perm", "t_faroff", "t_nearoff", "t_far", "t_near", "t_loc",
-                            "t_terms", "t_tb"}) {
-        auto it = c->bufs.find(n + tag);
-        if (it == c->bufs.end()) continue;
-        if (it->second.p) {
-          HIPCHK(c, hipFree(it->second.p));
-          c->ws_bytes -= it->second.bytes;
-        }
-        c->bufs.erase(it);
-      }
-      trees[d] = Batch::Tree{};
-      continue;
-    }
+    plan_tree(c, trees[d], D, B.shape.tpt, kMixedTreeTol, false, D.ncols, "_m" + std::to_string(d), nullptr, 0,
+              D.splits);
     D.treeslots = trees[d].splits;
     any = true;
   }
@@ -1786,22 +1774,47 @@ GmresOut fbiead_batch(gnk_ctx* c, Batch& B, const double* gam, const gnk_opts& o
   return gmres(c, B, GNK_OP_GB, gam, o, mu, o.prec == GNK_MIXED);
 }
 
+// Gives the whole workspace back (the stream is idle).
+void drop_workspace(gnk_ctx* c) {
+  for (auto& kv : c->bufs)
+    if (kv.second.p) HIPCHK(c, hipFree(kv.second.p));
+  c->bufs.clear();
+  c->ws_bytes = 0;
+  c->up_last.clear();
+  c->tw_ready.clear();
+  for (auto& sig : c->step_sig) sig.clear();
+}
+
+// Runs an entry point's body. One that runs out of memory is run again without the
+// workspace of earlier calls and, from then on, without the kernels that take more of it
+// than the one-sided direct ones: no call that these fit fails.
 template <class F>
 gnk_status guarded(gnk_ctx* c, F&& f) {
   if (!c) return GNK_ERR_ARG;
-  c->err.clear();
-  try {
-    HIPCHK(c, hipSetDevice(c->device));
-    // uploads of the previous call have completed (every call ends synchronised)
-    c->host_keep.clear();
-    return f();
-  } catch (const Fail& e) {
-    (void)hipStreamSynchronize(c->stream);
-    return e.st;
-  } catch (const std::bad_alloc&) {
-    set_err(c, "host allocation failed");
-    (void)hipStreamSynchronize(c->stream);
-    return GNK_ERR_OOM;
+  const size_t recs = c->prof_pending.size();
+  const bool prof = c->prof;   // (the autotuner times its candidates with it off)
+  for (bool again = false;; again = true) {
+    c->err.clear();
+    try {
+      HIPCHK(c, hipSetDevice(c->device));
+      // uploads of the previous call have completed (every call ends synchronised)
+      c->host_keep.clear();
+      if (again) drop_workspace(c);
+      return f();
+    } catch (const Fail& e) {
+      (void)hipStreamSynchronize(c->stream);
+      if (e.st != GNK_ERR_OOM || again || c->ws_limit) return e.st;
+    } catch (const std::bad_alloc&) {
+      set_err(c, "host allocation failed");
+      (void)hipStreamSynchronize(c->stream);
+      return GNK_ERR_OOM;
+    }
+    c->lean = true;
+    c->prof = prof;
+    for (; c->prof_pending.size() > recs; c->prof_pending.pop_back()) {
+      c->ev_pool.push_back(c->prof_pending.back().a);
+      c->ev_pool.push_back(c->prof_pending.back().b);
+    }
   }
 }
 
@@ -2007,6 +2020,7 @@ gnk_status gnk_create(gnk_ctx** out, int device) {
   if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
     c->num_cu = prop.multiProcessorCount;
   if (const char* s = getenv("GNK_WORKSPACE_MB")) c->ws_limit = (size_t)atoll(s) << 20;
+  if (const char* s = getenv("GNK_DEVICE_MB")) c->dev_limit = (size_t)atoll(s) << 20;
   if (const char* s = getenv("GNK_LOG")) c->log = atoi(s) != 0;
   if (const char* s = getenv("GNK_GRAPH")) c->graphs = atoi(s) != 0;
   // a blocking stream of default priority: ordered with the legacy null
