@@ -46,8 +46,8 @@ FLOPS_PER_PAIR = 16.0            # one column: 2 sub, |d|^2 (3), reciprocal (1),
 # KiB, the factors from a 256 MiB copy of known size; profiles/*_hbm_counters.md).
 # Valid only for that N and the kernel sources they were taken on (hash below), else null.
 PAIR_TRAFFIC = {"sources": ("pairs_sym.hip", "gnk_device.h", "gnk_internal.h"),
-                "sha256": "ad79ea4be3d5d9a3f8f8c5738301587c2e656db3200f92e00ca9a2c559e3948e",
-                "N": 264192, "bytes_per_launch": 5961104169}
+                "sha256": "b15aa03df9fc06d9153cca01df40da93c63184b27eb94261cf2fe0e5eb72baaa",
+                "N": 264192, "bytes_per_launch": 5319538688}
 
 
 def pair_traffic(N):

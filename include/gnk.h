@@ -162,8 +162,9 @@ typedef struct {
  *   relres      : GMRES residual estimate at exit
  *   true_relres : ||b - A x|| / ||b|| recomputed with an FP64 product
  *   mixed_steps : Arnoldi steps whose product used FP32 far tiles or, in place of
- *                 them, the treecode at 1e-9 (GNK_MIXED); at most inner_it, and in a solve that switches to mixed products part-way it
- *                 may include up to seven speculative steps after the column stopped
+ *                 them, the treecode at 1e-9 (GNK_MIXED); at most inner_it, and in a
+ *                 solve that switches to mixed products part-way it may include up to
+ *                 seven speculative steps after the column stopped
  *   refine_steps: GNK_MIXED: restart cycles of this column that took mixed products,
  *                 each followed by an FP64 residual (refinement steps); 0 for GNK_FP64
  *   hist_count  : entries written to this column's residual history (0 without one) */
@@ -265,7 +266,8 @@ GNK_API gnk_status gnk_profile_read(gnk_ctx* ctx, gnk_prof* out, int reset);
  *   N     : number of nodes; eta: N complex.
  *   w     : N x nrhs complex; S: N x nrhs complex (output, must not alias w).
  * FP64; every pair is evaluated directly (no far-field approximation).
- * Coincident nodes (eta_i == eta_j, i != j) give non-finite sums. */
+ * Coincident nodes (eta_i == eta_j, i != j) give non-finite sums S_i and S_j and
+ * leave the other nodes' sums as they are. */
 GNK_API gnk_status gnk_cauchy_sum(gnk_ctx* ctx, int64_t N, const void* eta, const void* w, int nrhs,
                           void* S);
 
@@ -329,8 +331,9 @@ GNK_API gnk_status gnk_circular_slit_map(gnk_ctx* ctx, int64_t m1, int64_t n, co
                                          gnk_info* info);
 
 /* gnk_fcau with the two Cauchy sums from the treecode (see gnk_opts.far_tol):
- * the nodes' box tree, target tiles of 128 points, far boxes by p_e-term
- * expansions with (r/R)^p_e <= far_tol, near 64-node blocks summed directly.
+ * the nodes' box tree, target tiles of 64 points (in Hilbert order), far boxes by
+ * p_e-term expansions with (r/R)^p_e <= far_tol entering the tiles' local expansions,
+ * truncated at far_tol/64, near leaves of up to 64 nodes summed directly.
  * Same arguments, layout and results as gnk_fcau, plus far_tol (1e-15..0.1);
  * GNK_ERR_ARG for far_tol outside that range. For many points around a large
  * boundary (N in the millions), where the direct sums take N nz pairs. */
@@ -376,7 +379,8 @@ GNK_API gnk_status gnk_slit_map(gnk_ctx* ctx, int64_t m1, int64_t n, const void*
 
 /* gnk_cauchy_sum with the far field from the treecode (see gnk_opts.far_tol):
  * S_i = sum_{j != i} w_j / (eta_i - eta_j), near pairs summed directly, far
- * boxes by p-term expansions with (r/R)^p <= far_tol (1e-15..0.1). Same
+ * boxes by p-term expansions with (r/R)^p <= far_tol (1e-15..0.1) through local
+ * expansions of the target tiles. Same
  * arguments and layout as gnk_cauchy_sum; GNK_ERR_ARG for far_tol outside
  * that range. */
 GNK_API gnk_status gnk_cauchy_sum_tree(gnk_ctx* ctx, int64_t N, const void* eta, const void* w, int nrhs,

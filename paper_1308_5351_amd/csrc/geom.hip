@@ -9,10 +9,9 @@
 // with z_t = i c_t for f_B (B = Re(-i K), and the rows of diag(B1) - B give
 // u_i (v_i - v_j)) and z_t = c_t for fC. Grouping the terms by v (groups g with
 // vector V_g and U_g = sum_{t in g} z_t u_t, P = sum_g U_g V_g), the partial
-// derivatives of F = sum_{i != j} K_ij W_ij need only row and column sums:
-// and, with S1(w)_i = sum_{j != i} w_j/(eta_i - eta_j) (the matrix E of
-// eq. (e:fmm-E)), S2 the same with the square of the difference, kappa = 2/n,
-// q = 1/(eta_i - eta_j) and e_g = V_g,i - V_g,j,
+// derivatives of F = sum_{i != j} K_ij W_ij need only row and column sums: with
+// S1(w)_i = sum_{j != i} w_j/(eta_i - eta_j) (the matrix E of eq. (e:fmm-E)),
+// kappa = 2/n, q = 1/(eta_i - eta_j) and e_g = V_g,i - V_g,j,
 //   R1_i = sum_j K_ij W_ij = kappa a_i sum_g U_g,i F1_g,i,   F1_g,i = sum_j b_j e_g q
 //   R2_i = sum_j K_ij W_ij / (eta_j - eta_i) = -kappa a_i sum_g U_g,i F2_g,i  (q^2 for q)
 //   T1_i = sum_g V_g,i S1(a U_g)_i - S1(a P)_i = sum_j X q,  X = sum_g (a U_g)_j e_g

@@ -141,8 +141,8 @@ struct Pieces {
 // slots [b 2^l, (b + 1) 2^l); leafbox: the leaves' bounding boxes; bbox and
 // rbits: scratch of one entry per box
 hipError_t launch_box_bounds(const double2* eta, int N, Pieces leaves, const int* level_off, const int* level_nb,
-                             int levels, const double4* leafbox, const int* perm, double4* bbox, unsigned long long* rbits,
-                             double4* out, hipStream_t st);
+                             int levels, const double4* leafbox, const int* perm, double4* bbox,
+                             unsigned long long* rbits, double4* out, hipStream_t st);
 // bounding boxes {xmin, xmax, ymin, ymax} of the leaves (up to kLeaf consecutive nodes)
 hipError_t launch_leaf_boxes(const double2* eta, int N, Pieces leaves, int nleaf, double4* leafbox, hipStream_t st);
 // bounding circles {cx, cy, r, 0} of the tiles of consecutive nodes
@@ -153,11 +153,11 @@ hipError_t launch_piece_circles(const double2* eta, int N, Pieces tiles, int cou
 size_t hilbert_scratch(int64_t n);
 hipError_t launch_hilbert_order(const double2* pts, const double4* boxes, int n, void* scratch, int* perm,
                                 hipStream_t st);
-// Interaction lists of the target tiles (bounds tb) against
-// the boxes: far entries {box, p_e | chunks of 16 tile terms << 8} and near leaves (first
-// node, complemented where the leaf has fewer than kLeaf nodes). Count: offsets of every tile into the two lists (tiles + 1
-// each), its work (flops: 64 p_e per chunk of a far entry, 8 kTreeMaxP per target,
-// 16 per near pair) and the lists' lengths at total[0..1] (host-mapped).
+// Interaction lists of the target tiles (bounds tb) against the boxes: far entries
+// {box, p_e | chunks of 16 tile terms << 8} and near leaves (first node, complemented
+// where the leaf has fewer than kLeaf nodes). Count: offsets of every tile into the two
+// lists (tiles + 1 each), its work (flops: 64 p_e per chunk of a far entry, 8 kTreeMaxP
+// per target, 16 per near pair) and the lists' lengths at total[0..1] (host-mapped).
 struct TreeListArgs {
   const double4* bounds;
   const double4* tb;

@@ -17,7 +17,10 @@
 // (wave_rol; back in its own lane after 64 steps). The arrays in LDS are doubled,
 // entry k + 64 standing for entry k, so that l + r needs no wrap. The owned
 // nodes' sums stay in registers for the chunk. T = 8 (two waves per SIMD): 112
-// FP64 operations and 9 others per step; T = 4 (three waves): 56 and 9.
+// FP64 operations and 9 others per step; T = 4 (three waves): 56 and 9. With T = 8
+// 256 registers do not hold everything: 24 are spilled (68 bytes a lane), between the
+// chunks but for three accesses per two far steps, which the FP64 issue covers; at
+// N = 264192 12 % of the bytes written are not partial sums, but such registers.
 //
 // Measured (one column, launch us, one-sided / two-sided): 126 / 96 at N = 17408,
 // 407 / 318 at 33792, 1695 / 1415 at 73729. At the last the VALU is busy 93 % of

@@ -427,7 +427,8 @@ void plan_single(gnk_ctx* c, int64_t N, int align, int cols, bool mixed, int* tp
 // reads; at N = 17408 a piece is two or three chunks).
 constexpr int64_t kSymMinN = 8000, kSymMaxN = 600000, kSymWideN = 40000;
 bool plan_sym(gnk_ctx* c, int64_t N, SymPlan* P, std::vector<int4>* items) {
-  if (N < kSymMinN || N > kSymMaxN || c->arena || c->ws_limit || c->lean || getenv("GNK_CAUCHY_TPT") || getenv("GNK_CAUCHY_SPLITS")) return false;
+  if (N < kSymMinN || N > kSymMaxN || c->arena || c->ws_limit || c->lean) return false;
+  if (getenv("GNK_CAUCHY_TPT") || getenv("GNK_CAUCHY_SPLITS")) return false;
   const int T = N >= kSymWideN ? 8 : 4;
   const int nb = (int)((N + 256 * T - 1) / (256 * T));
   const int nc = (int)((N + 63) / 64), per = 4 * T;
@@ -892,8 +893,9 @@ void tree_pairs(gnk_ctx* c, Batch& B, int p, const int* active) {
     const int nc = std::min(2, wcols - col);
     // the flag of a single data column, whose masked steps skip the expansions too
     const int* act = active && nc == 1 && col >= lead ? active + D.c0 + col - lead : nullptr;
-    HIPCHK(c, launch_tree_moments(D.rec, slim_stride(wcols), 1 + col, nc, D.N, T.leaves, T.ev.bounds, T.perm, T.off.data(),
-                                  T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, T.ev.binom, act, c->stream));
+    HIPCHK(c, launch_tree_moments(D.rec, slim_stride(wcols), 1 + col, nc, D.N, T.leaves, T.ev.bounds, T.perm,
+                                  T.off.data(), T.nb.data(), T.levels, T.p, T.mom, T.ev.colstride, T.ev.binom, act,
+                                  c->stream));
     HIPCHK(c, launch_tree_eval(B.d_dom, T.tiles, B.shape.tpt, T.ev, nc, T.splits, col, wcols, active, lead, T.ext, act,
                                c->stream));
     col += nc;
@@ -927,7 +929,8 @@ void pairs(gnk_ctx* c, Batch& B, int p, bool mixed, const int* active) {
   const bool trees = p == P_GM_MIXED && !B.mtree.empty();
   int items = 0;
   for (int n : S.cnt) items += n;
-  if (mixed && items) HIPCHK(c, launch_records32(B.d_dom, B.ndom, records32_threads(B, p), kLead[p], kData[p], c->stream));
+  if (mixed && items)
+    HIPCHK(c, launch_records32(B.d_dom, B.ndom, records32_threads(B, p), kLead[p], kData[p], c->stream));
   gnk_ctx::ProfRec pr{};
   if (c->prof) {
     pr = gnk_ctx::ProfRec{pool_event(c), pool_event(c), S.pair_cols, S.flops, S.pairs1, mixed,
@@ -1160,7 +1163,8 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
   // less of that)
   // (an even number: entries are taken in twos)
   const int per_blk = (int)std::max<int64_t>(
-      kT, std::min<int64_t>(kMaxChunk, (std::max<int64_t>(((int64_t)B.maxN + 255) / 256, (T + 8191) / 8192) + 1) / 2 * 2));
+      kT, std::min<int64_t>(kMaxChunk,
+                            (std::max<int64_t>(((int64_t)B.maxN + 255) / 256, (T + 8191) / 8192) + 1) / 2 * 2));
   const int nblk = (B.maxN + per_blk - 1) / per_blk;
 
   double* V = ws<double>(c, "V", (size_t)(restart + 1) * T);
@@ -1284,10 +1288,9 @@ GmresOut gmres(gnk_ctx* c, Batch& B, int op, const double* b, const gnk_opts& o,
     const double* const p2 = fold ? P3 : P2;
     const int nin = fold ? 1 : nblk;
     const dim3 gf((unsigned)((ldp + 15) / 16), (unsigned)ncol);
-    k_epilogue_dots<<<gv, kT * groups, epilogue_lds(groups, mpart ? S : 0), c->stream>>>(B.d_dom, B.d_col, V, T, form.cout, form.dsel, form.a0, form.dsign,
-                                              form.cI, form.cR, mpart, S, st.active, sl.step, per_blk,
-                                              sym ? P_SYM : (use_mixed && !B.mtree.empty() ? P_TREE : P_SPLITS), P1,
-                                              ldp);
+    k_epilogue_dots<<<gv, kT * groups, epilogue_lds(groups, mpart ? S : 0), c->stream>>>(
+        B.d_dom, B.d_col, V, T, form.cout, form.dsel, form.a0, form.dsign, form.cI, form.cR, mpart, S, st.active,
+        sl.step, per_blk, sym ? P_SYM : (use_mixed && !B.mtree.empty() ? P_TREE : P_SPLITS), P1, ldp);
     LAUNCHCHK(c);
     if (fold) k_fold_partials<<<gf, kFoldT, 0, c->stream>>>(P1, nblk, ldp, st.active, sl.step, 1, P3);
     LAUNCHCHK(c);

@@ -115,7 +115,8 @@ struct LevelTable {
 // leaf would queue 70000 of them on the top box of 4460544 nodes).
 constexpr int kRadiiWaves = 16;
 __global__ __launch_bounds__(64 * kRadiiWaves) void k_box_radii(const double2* __restrict__ eta, int N,
-                                                                Pieces leaves, LevelTable lv, int levels, int nleaf, const int* __restrict__ perm,
+                                                                Pieces leaves, LevelTable lv, int levels, int nleaf,
+                                                                const int* __restrict__ perm,
                                                                 const double4* __restrict__ out,
                                                                 unsigned long long* __restrict__ rbits) {
   static_assert(kLeaf == 64, "one node per lane");
@@ -163,8 +164,9 @@ __global__ void k_box_finish(const unsigned long long* __restrict__ rbits, int n
 // loads (32 bytes a node with one column).
 template <int CH>
 __global__ __launch_bounds__(64) void k_leaf_moments(const double2* __restrict__ rec, int stride, int wo, int N,
-                                                     Pieces leaves, const double4* __restrict__ bounds, const int* __restrict__ perm,
-                                                     int nleaf, int p, double2* __restrict__ mom, size_t colstride,
+                                                     Pieces leaves, const double4* __restrict__ bounds,
+                                                     const int* __restrict__ perm, int nleaf, int p,
+                                                     double2* __restrict__ mom, size_t colstride,
                                                      const int* __restrict__ active) {
   if (active != nullptr && active[blockIdx.y] == 0) return;
   const int b = blockIdx.x * 16 + (threadIdx.x >> 2), q = threadIdx.x & 3;
@@ -601,7 +603,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NC == 1 ? 8
   const cptr<int64_t> off = (cptr<int64_t>)nearoff + tile;
   const int n0 = (int)off[0];
   const int64_t units = 16 * (off[1] - n0);   // of four sources
-  const int u0 = (int)(units * (4 * g + wv) / (4 * splits)) * 4, u1 = (int)(units * (4 * g + wv + 1) / (4 * splits)) * 4;
+  const int u0 = (int)(units * (4 * g + wv) / (4 * splits)) * 4;
+  const int u1 = (int)(units * (4 * g + wv + 1) / (4 * splits)) * 4;
 
   double2 tg[TPT];
   int ti[TPT];
@@ -947,8 +950,8 @@ __device__ __forceinline__ int wave_prefix(int v, int lane, int* total) {
 
 template <bool FILL>
 __global__ __launch_bounds__(256) void k_tree_lists(TreeWalk W, int64_t* __restrict__ nfar,
-                                                    int64_t* __restrict__ nnear, double* __restrict__ work, int2* __restrict__ far,
-                                                    int* __restrict__ near_) {
+                                                    int64_t* __restrict__ nnear, double* __restrict__ work,
+                                                    int2* __restrict__ far, int* __restrict__ near_) {
   extern __shared__ int stk[];                // 128 levels boxes per wave, deepest level last
   __shared__ int left[4][kTreeLevels];        // boxes of each level on the stack
   __shared__ double thr[kTreeMaxP + 1];
@@ -1102,14 +1105,16 @@ static TreeWalk tree_walk(const TreeListArgs& A) {
 hipError_t launch_tree_count(const TreeListArgs& A, int64_t* nfar, int64_t* nnear, double* work, int64_t* total,
                              hipStream_t st) {
   if (A.levels < 1 || A.levels > kTreeLevels || A.p > kTreeMaxP) return hipErrorInvalidValue;
-  k_tree_lists<false><<<(A.tiles + 3) / 4, 256, 4 * 128 * sizeof(int) * A.levels, st>>>(tree_walk(A), nfar, nnear, work, nullptr, nullptr);
+  k_tree_lists<false><<<(A.tiles + 3) / 4, 256, 4 * 128 * sizeof(int) * A.levels, st>>>(tree_walk(A), nfar, nnear,
+                                                                                        work, nullptr, nullptr);
   k_list_offsets<<<2, 1024, 0, st>>>(nfar, nnear, A.tiles, total);
   return hipGetLastError();
 }
 
 hipError_t launch_tree_fill(const TreeListArgs& A, int64_t* nfar, int64_t* nnear, int2* far, int* near_,
                             hipStream_t st) {
-  k_tree_lists<true><<<(A.tiles + 3) / 4, 256, 4 * 128 * sizeof(int) * A.levels, st>>>(tree_walk(A), nfar, nnear, nullptr, far, near_);
+  k_tree_lists<true><<<(A.tiles + 3) / 4, 256, 4 * 128 * sizeof(int) * A.levels, st>>>(tree_walk(A), nfar, nnear,
+                                                                                       nullptr, far, near_);
   return hipGetLastError();
 }
 
@@ -1124,8 +1129,8 @@ hipError_t launch_piece_circles(const double2* eta, int N, Pieces tiles, int cou
 }
 
 hipError_t launch_box_bounds(const double2* eta, int N, Pieces leaves, const int* level_off, const int* level_nb,
-                             int levels, const double4* leafbox, const int* perm, double4* bbox, unsigned long long* rbits,
-                             double4* out, hipStream_t st) {
+                             int levels, const double4* leafbox, const int* perm, double4* bbox,
+                             unsigned long long* rbits, double4* out, hipStream_t st) {
   if (levels < 1 || levels > 32) return hipErrorInvalidValue;
   k_bbox_gather<<<(level_nb[0] + 255) / 256, 256, 0, st>>>(leafbox, perm, level_nb[0], bbox);
   hipError_t e = hipGetLastError();

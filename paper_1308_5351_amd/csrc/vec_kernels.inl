@@ -1083,14 +1083,14 @@ __device__ void arnoldi_close(GmresState st, int c, int col, const double* h2, d
 // records and component sums. The last block of each column has no chunk and
 // closes Hessenberg column l meanwhile (its chain of rotations and the store
 // to the host took the chunk's block 3 us longer than the others). Those
-// blocks count themselves in *st.done (after a device-scope fence); the last publishes the number of iterating columns to host_live[l]
-// and, when given, the residual estimates to host_rel[l*ncol ..] (host-mapped
-// memory the host reads after an event) and sets *step_next = l + 1. The
-// step index is double-buffered (st.step is read by all of this step's
-// launches, step_next by the next step's), so no block can read an index
-// that another has already advanced. A block of a column that has just
-// been stopped may still write V_{l+1} and its records: no later step or the
-// solution update reads them.
+// blocks count themselves in *st.done (after a device-scope fence); the last publishes
+// the number of iterating columns to host_live[l] and, when given, the residual
+// estimates to host_rel[l*ncol ..] (host-mapped memory the host reads after an event)
+// and sets *step_next = l + 1. The step index is double-buffered (st.step is read by
+// all of this step's launches, step_next by the next step's), so no block can read an
+// index that another has already advanced. A block of a column that has just been
+// stopped may still write V_{l+1} and its records: no later step or the solution update
+// reads them.
 __global__ __launch_bounds__(kT) void k_gs_finish(const DomDev* __restrict__ doms, const ColDev* __restrict__ cols,
                                                   double* __restrict__ V, int64_t T, int per_blk,
                                                   const double* __restrict__ pin, int nin, int ldp,
